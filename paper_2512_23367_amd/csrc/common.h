@@ -57,7 +57,7 @@ __host__ __device__ inline int w4_nibble_pos(int k)    // nibble index 0..7 insi
     return 2 * (j8 % 4) + (j8 / 4);
 }
 
-inline size_t act_kernel_bytes(int M, int K) { return (size_t)round_up(M, TILE_ROWS) * K; }
+__host__ __device__ inline size_t act_kernel_bytes(int M, int K) { return (size_t)round_up(M, TILE_ROWS) * K; }
 inline size_t w8_kernel_bytes(int N, int K) { return (size_t)round_up(N, TILE_ROWS) * K; }
 inline size_t w4_codes_bytes(int N, int K) { return (size_t)round_up(N, TILE_ROWS) * K / 2; }
 inline size_t w4_scales_offset(int N, int K) { return (w4_codes_bytes(N, K) + 255) & ~(size_t)255; }

@@ -19,14 +19,13 @@ struct alignas(16) Half16 {
 
 __device__ inline unsigned abs_max_bits(const Half16 &v, unsigned m)
 {
-    // |h| as an integer is monotonic in |value| for finite fp16, so the maximum can be taken on bits
+    // |h| as an integer is monotonic in |value| for finite fp16, so the maximum can be taken on bits, two at a time
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
     const unsigned w[8] = {v.lo.x, v.lo.y, v.lo.z, v.lo.w, v.hi.x, v.hi.y, v.hi.z, v.hi.w};
+    us2 p = __builtin_bit_cast(us2, w[0] & 0x7fff7fffu);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        m = max(m, w[i] & 0x7fffu);
-        m = max(m, (w[i] >> 16) & 0x7fffu);
-    }
-    return m;
+    for (int i = 1; i < 8; ++i) p = __builtin_elementwise_max(p, __builtin_bit_cast(us2, w[i] & 0x7fff7fffu));
+    return max(m, max((unsigned)p[0], (unsigned)p[1]));
 }
 
 __device__ inline float half_bits_to_float(unsigned bits)
@@ -34,21 +33,24 @@ __device__ inline float half_bits_to_float(unsigned bits)
     return __half2float(__ushort_as_half((unsigned short)bits));
 }
 
-__device__ inline int quant_code(unsigned hbits, float inv)
+// Codes of four values t = x * inv (one fp32 multiply each, already within +-127): adding 1.5 * 2^23 rounds to the nearest
+// integer, ties to even, and leaves the code's two's complement in the low byte -- an addition and 3/4 of a byte
+// permute per code instead of a round, a clamp, a conversion and the masks and shifts that assemble the word.
+__device__ inline unsigned code_word(float t0, float t1, float t2, float t3)
 {
-    const float t = half_bits_to_float(hbits) * inv;    // one fp32 multiply
-    float r = rintf(t);                                 // round half to even
-    r = fminf(fmaxf(r, -127.0f), 127.0f);
-    return (int)r;
+    const float magic = 12582912.0f;
+    const unsigned u0 = __float_as_uint(t0 + magic), u1 = __float_as_uint(t1 + magic);
+    const unsigned u2 = __float_as_uint(t2 + magic), u3 = __float_as_uint(t3 + magic);
+    const unsigned lo = __builtin_amdgcn_perm(u1, u0, 0x0c0c0400u), hi = __builtin_amdgcn_perm(u3, u2, 0x0c0c0400u);
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
 __device__ inline unsigned quant_word(unsigned w0, unsigned w1, float inv)   // 4 halves -> 4 codes
 {
-    const unsigned a = quant_code(w0 & 0xffffu, inv) & 0xff;
-    const unsigned b = quant_code(w0 >> 16, inv) & 0xff;
-    const unsigned c = quant_code(w1 & 0xffffu, inv) & 0xff;
-    const unsigned d = quant_code(w1 >> 16, inv) & 0xff;
-    return a | (b << 8) | (c << 16) | (d << 24);
+    // |x| <= amax and inv = 127 / amax rounded: |x * inv| <= 127 + one ulp, which rounds to 127 -- no clamp.  The widening
+    // and the multiply are one instruction (fma with 0: the sum with +0 changes nothing but the sign of a zero).
+    return code_word(__builtin_fmaf(half_bits_to_float(w0 & 0xffffu), inv, 0.0f), __builtin_fmaf(half_bits_to_float(w0 >> 16), inv, 0.0f),
+                     __builtin_fmaf(half_bits_to_float(w1 & 0xffffu), inv, 0.0f), __builtin_fmaf(half_bits_to_float(w1 >> 16), inv, 0.0f));
 }
 
 __device__ inline uint4 quant_chunk(const Half16 &v, float inv)
@@ -61,19 +63,20 @@ __device__ inline uint4 quant_chunk(const Half16 &v, float inv)
     return q;
 }
 
-// the same code decision for an fp32 value (operands after one of the paper's transforms, Eq. 3-4)
-__device__ inline int quant_code_f32(float x, float inv)
-{
-    float r = rintf(x * inv);                           // one fp32 multiply, round half to even
-    r = fminf(fmaxf(r, -127.0f), 127.0f);
-    return (int)r;
-}
-
+// the same code decision for fp32 values (operands after one of the paper's transforms, Eq. 3-4).  Here inv overflows when
+// amax is below 127 / FLT_MAX: such tokens take the products through the clamp (which commutes with the rounding, its
+// bounds are integers); inv is the same for the whole token, so the branch is uniform.
 __device__ inline uint4 quant_chunk_f32(const float (&v)[16], float inv)
 {
-    unsigned q[4] = {0, 0, 0, 0};
+    unsigned q[4];
+    if (inv <= 3.402823466e38f) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) q[i / 4] |= (unsigned)(quant_code_f32(v[i], inv) & 0xff) << (8 * (i % 4));
+        for (int i = 0; i < 4; ++i) q[i] = code_word(v[4 * i] * inv, v[4 * i + 1] * inv, v[4 * i + 2] * inv, v[4 * i + 3] * inv);
+    } else {
+        auto clamped = [&](float x) { return fminf(fmaxf(x * inv, -127.0f), 127.0f); };
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q[i] = code_word(clamped(v[4 * i]), clamped(v[4 * i + 1]), clamped(v[4 * i + 2]), clamped(v[4 * i + 3]));
+    }
     return make_uint4(q[0], q[1], q[2], q[3]);
 }
 
@@ -90,8 +93,11 @@ __device__ inline void token_scales_f32(float amax, float &scale, float &inv)
 // polynomial (multiply, then add), exact scaling by 2^n -- so that the codes are a function of the inputs alone.
 __device__ inline float exp_steps(float t)      // t in [-80, 80]
 {
-    const float n = rintf(t * 1.4426950408889634f);
-    float r = t - n * 0.693359375f;
+    // n = rint(t log2 e): adding 1.5 * 2^23 rounds to the nearest integer, ties to even, and leaves n in the low bits
+    const float magic = 12582912.0f;
+    const float z = t * 1.4426950408889634f + magic;
+    const float n = z - magic;
+    float r = __builtin_fmaf(-n, 0.693359375f, t);      // n * (355 / 512) is exact: the same as multiply, then subtract
     r = r - n * -2.12194440e-4f;
     float p = (float)(1.0 / 5040);
     p = p * r + (float)(1.0 / 720);
@@ -101,15 +107,24 @@ __device__ inline float exp_steps(float t)      // t in [-80, 80]
     p = p * r + 0.5f;
     p = p * r + 1.0f;
     p = p * r + 1.0f;
-    return p * __int_as_float(((int)n + 127) << 23);   // times 2^n, exact: |n| <= 116
+    // times 2^n by adding n to the exponent, exact: |n| <= 116 and 0.7 < p < 1.42 (the shift leaves n of z's bits only)
+    return __uint_as_float((__float_as_uint(z) << 23) + __float_as_uint(p));
+}
+
+// 1 / d correctly rounded for the d = 1 + exp(t) that an fp16 gate can give (1 <= d < 2^116: no operand or result near the
+// ends of the exponent range, where the general division spends most of its instructions): the hardware's
+// approximation and one Newton step in fused operations.  Checked for every fp16 gate against the IEEE division.
+__device__ inline float reciprocal_of_sum(float d)
+{
+    const float y = __builtin_amdgcn_rcpf(d);
+    return __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
 }
 
 __device__ inline float swiglu_f32(float g, float u)
 {
     const float t = fminf(fmaxf(-g, -80.0f), 80.0f);
     const float d = 1.0f + exp_steps(t);
-    const float sg = 1.0f / d;                          // IEEE fp32 division
-    return (g * sg) * u;
+    return (g * reciprocal_of_sum(d)) * u;
 }
 
 // token scale and its reciprocal from the bit pattern of the largest |x|
