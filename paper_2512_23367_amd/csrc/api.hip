@@ -526,12 +526,8 @@ int ql_quant_weight_transformed(const void *w, int N, int K, int bits, int group
         (wq_kernel && !aligned(wq_kernel, 256)))
         return fail(QL_ERR_ALIGN, "w/w32/smooth/wq_canonical/scales need 16-byte, wq_kernel 256-byte alignment");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    QL_TRY(launch_weight_transform(static_cast<const __half *>(w), N, K, smooth, hadamard_block, w32, st));
-    if (bits == 8)
-        return launch_weight_quant8_f32(w32, N, K, static_cast<int8_t *>(wq_canonical), static_cast<float *>(scales),
-                                        static_cast<int8_t *>(wq_kernel), st);
-    return launch_weight_quant4_f32(w32, N, K, group, static_cast<uint8_t *>(wq_canonical),
-                                    static_cast<__half *>(scales), static_cast<uint8_t *>(wq_kernel), st);
+    return launch_weight_transform_quant(static_cast<const __half *>(w), N, K, bits, group, smooth, hadamard_block, w32, wq_canonical,
+                                         scales, wq_kernel, st);
 }
 
 int ql_export_canonical(const void *wq_kernel, int N, int K, int bits, int group, void *wq_canonical,

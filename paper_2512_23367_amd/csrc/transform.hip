@@ -10,226 +10,484 @@
 // divides K (at most 4096) so that any K % 64 == 0 works.  It is applied as the in-place butterfly in fp32,
 // stages h = 1, 2, ..., B/2 in that order, every output one addition or subtraction, then one multiply by
 // fp32(1/sqrt(B)): a fixed sequence of single fp32 operations per element, whatever lane does them.
-// A lane holds chunks of 16 consecutive elements: stages h <= 8 in registers, the next six across the lanes
-// of a wavefront (four of them as vector-ALU lane permutes), the last two (B > 1024) across wavefronts through LDS.
+// A wavefront holds whole blocks: one chunk of 16 consecutive elements per lane covers 1024 elements, larger blocks take two
+// or four chunks per lane.  So no stage leaves the wavefront: stages h <= 8 and h >= 1024 are in registers, the four in
+// between inside a row of 16 lanes are one lane-permuting multiply-add each, the two across the rows swap registers.
 #include "common.h"
 #include "quant_math.h"
 #include <cmath>
+#include <type_traits>
 
 namespace ql {
 namespace {
 
-constexpr int TW = 256;                 // threads per workgroup (one token / one weight row); at most 4 chunks of 16 per thread: K <= 16384
+// ---- Hadamard transform of blocks of 2^LB elements held by one wavefront.  NIT = chunks per lane; element
+//   k = (it * 64 + l) * 16 + i   of the wavefront's piece sits in v[it][i] of the lane whose logical number is l.
+// Logical lane l of physical lane p: l = p ^ (p & 4 ? 3 : 0), so that a step of one bit in l is a step in p that a
+// lane-permuting operand modifier can make: l^1 and l^2 are p^1, p^2 (quad permutes), l^4 is p^7 (half-row mirror), l^8
+// is p^8 (row rotation).
+constexpr int hadamard_chunks(int lb) { return lb > 10 ? 1 << (lb - 10) : 1; }
 
-__device__ inline void load_chunk(const __half *row, int c, float (&v)[16])
-{
-    const Half16 h = reinterpret_cast<const Half16 *>(row)[c];
-    const unsigned w[8] = {h.lo.x, h.lo.y, h.lo.z, h.lo.w, h.hi.x, h.hi.y, h.hi.z, h.hi.w};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        v[2 * i] = half_bits_to_float(w[i] & 0xffffu);
-        v[2 * i + 1] = half_bits_to_float(w[i] >> 16);
+__device__ inline int logical_lane(int p) { return p ^ ((p & 4) ? 3 : 0); }
+
+// One stage between logical lanes that differ in one bit.  The lower lane needs a + b and the upper a - b; both compute
+// (own value) + s * (partner's), s = +1 below and -1 above, a single rounding each: the upper lane is left with the negative
+// of its result.  Every value of a lane then carries the same sign, -1 to the number of such stages in which the lane was
+// the upper one; partners agree in it (they differ in the stage's own bit only), and the final multiply takes it out.
+// Written as one block of multiply-adds whose first operand is permuted (the compiler keeps the permutation a move of its
+// own, with wait states in front of each); the leading s_nop covers the two wait states between the last write of a
+// register and its permuted read.  Every lane of the wavefront is active here and every source lane exists.
+#define QL_FMAC_DPP(i, ctrl) "v_fmac_f32_dpp %" #i ", %" #i ", %16 " ctrl " row_mask:0xf bank_mask:0xf\n\t"
+#define QL_LANE_STAGE(name, ctrl)                                                                                                     \
+    __device__ inline void name(float (&v)[16], float s)                                                                              \
+    {                                                                                                                                 \
+        asm("s_nop 1\n\t" QL_FMAC_DPP(0, ctrl) QL_FMAC_DPP(1, ctrl) QL_FMAC_DPP(2, ctrl) QL_FMAC_DPP(3, ctrl) QL_FMAC_DPP(4, ctrl)      \
+                QL_FMAC_DPP(5, ctrl) QL_FMAC_DPP(6, ctrl) QL_FMAC_DPP(7, ctrl) QL_FMAC_DPP(8, ctrl) QL_FMAC_DPP(9, ctrl)               \
+                    QL_FMAC_DPP(10, ctrl) QL_FMAC_DPP(11, ctrl) QL_FMAC_DPP(12, ctrl) QL_FMAC_DPP(13, ctrl) QL_FMAC_DPP(14, ctrl)       \
+                        QL_FMAC_DPP(15, ctrl)                                                                                         \
+            : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]), "+v"(v[8]), "+v"(v[9]),  \
+              "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15])                                            \
+            : "v"(s));                                                                                                                \
     }
+QL_LANE_STAGE(stage_lane1, "quad_perm:[1,0,3,2]")
+QL_LANE_STAGE(stage_lane2, "quad_perm:[2,3,0,1]")
+QL_LANE_STAGE(stage_lane4, "row_half_mirror")
+QL_LANE_STAGE(stage_lane8, "row_ror:8")
+#undef QL_LANE_STAGE
+#undef QL_FMAC_DPP
+
+// Swap between two registers and lanes 16 (32) apart: afterwards `a` holds, in lanes with that bit clear, what it held
+// there, and in lanes with it set, what `b` held in the lane 16 (32) below; `b` the rest.  Its own inverse.
+template <int DIST>
+__device__ inline void lane_register_swap(unsigned &a, unsigned &b)
+{
+    const auto r = DIST == 16 ? __builtin_amdgcn_permlane16_swap(a, b, false, false) : __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0], b = r[1];
 }
 
-__device__ inline void scale_chunk(const float *__restrict__ s, int c, float (&v)[16])
+template <int DIST>
+__device__ inline void lane_register_swap(float &a, float &b)
 {
+    unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+    lane_register_swap<DIST>(x, y);
+    a = __uint_as_float(x), b = __uint_as_float(y);
+}
+
+// The transform, multiplied by `norm`.  Where LB >= 9 (10) lane bit 4 (5) and register bit 2 (3) have changed places on
+// return: v[it][8 * c5 + 4 * c4 + j] is then element 8 * (lane bit 5) + 4 * (lane bit 4) + j of the chunk of logical lane
+// (l & 15) + 16 * c4 + 32 * c5 (LB = 9: bit 4 only).  unswap_words / unswap_values put things back.
+template <int LB, int NIT>
+__device__ inline void hadamard_wave(float (&v)[NIT][16], int l, float norm)
+{
+    static_assert(LB == 0 || LB >= 4, "no transform, or whole chunks");
+    if (LB > 0) {
 #pragma unroll
-    for (int i = 0; i < 16; i += 4) {
-        const float4 f = *reinterpret_cast<const float4 *>(s + (size_t)c * 16 + i);
-        v[i] *= f.x, v[i + 1] *= f.y, v[i + 2] *= f.z, v[i + 3] *= f.w;   // one fp32 multiply each
+        for (int it = 0; it < NIT; ++it)
+#pragma unroll
+            for (int h = 1; h < 16; h <<= 1)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if ((i & h) == 0) {
+                        const float a = v[it][i], b = v[it][i | h];
+                        v[it][i] = a + b;
+                        v[it][i | h] = a - b;
+                    }
     }
-}
-
-// Value of the same register in lane (lane ^ bit).  Inside a row of 16 lanes the data-parallel-primitive
-// modifiers do it on the vector ALU (quad permutes for 1 and 2; 4 = reverse each half-row of 8, then reverse
-// each quad; 8 = rotate the row by 8); 16 and 32 go through the LDS crossbar.
-template <int CTRL>
-__device__ inline float dpp_move(float v)
-{
-    // all rows and banks enabled and every source lane exists: the 'old' operand is never read
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
-
-template <int BIT>
-__device__ inline float lane_xor(float v)
-{
-    if constexpr (BIT == 1) return dpp_move<0xB1>(v);                        // quad_perm [1,0,3,2]
-    else if constexpr (BIT == 2) return dpp_move<0x4E>(v);                   // quad_perm [2,3,0,1]
-    else if constexpr (BIT == 4) return dpp_move<0x1B>(dpp_move<0x141>(v));  // row_half_mirror (i ^ 7), then quad_perm [3,2,1,0] (i ^ 3)
-    else if constexpr (BIT == 8) return dpp_move<0x128>(v);                  // row_ror:8
-    else return __shfl_xor(v, BIT, 64);
-}
-
-// one butterfly stage between lanes BIT apart: the lower lane keeps a + b, the upper one a - b (a = the lower lane's value)
-template <int BIT, int NIT>
-__device__ inline void lane_stage(float (&v)[NIT][16])
-{
-    // a + b below, b' - a' above: one fused multiply-add by +-1 (exact product, so the single rounding is that of
-    // the addition or subtraction itself)
-    const float sgn = (threadIdx.x & BIT) != 0 ? -1.0f : 1.0f;
-#pragma unroll
-    for (int it = 0; it < NIT; ++it)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v[it][i] = __builtin_fmaf(sgn, v[it][i], lane_xor<BIT>(v[it][i]));
-}
-
-// Block-diagonal Hadamard transform of the row whose chunk (it * TW + tid) sits in v[it]; lanes per block
-// = hblock / 16 (a power of two that divides TW and the number of chunks, so a block never straddles an `it`).
-// LB: log2(hblock) when it is known at compile time (every stage's presence is then resolved at compile time,
-// which saves the register copies that merge the skipped and the executed path of each stage), -1 otherwise.
-template <int NIT, int LB = -1>
-__device__ inline void fwht_row(float (&v)[NIT][16], int hblock, float norm, float *xchg /* [TW][16] */)
-{
-    const int tid = threadIdx.x;
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
+        if (LB > 4) stage_lane1(v[it], (l & 1) ? -1.0f : 1.0f);
+        if (LB > 5) stage_lane2(v[it], (l & 2) ? -1.0f : 1.0f);
+        if (LB > 6) stage_lane4(v[it], (l & 4) ? -1.0f : 1.0f);
+        if (LB > 7) stage_lane8(v[it], (l & 8) ? -1.0f : 1.0f);
+    }
+    // across the rows: after the swap both operands of a pair sit in one lane
+    if (LB > 8) {
 #pragma unroll
-        for (int h = 1; h < 16; h <<= 1)
+        for (int it = 0; it < NIT; ++it)
 #pragma unroll
             for (int i = 0; i < 16; ++i)
-                if ((i & h) == 0) {
-                    const float a = v[it][i], b = v[it][i | h];
+                if ((i & 4) == 0) {
+                    lane_register_swap<16>(v[it][i], v[it][i | 4]);
+                    const float a = v[it][i], b = v[it][i | 4];
                     v[it][i] = a + b;
-                    v[it][i | h] = a - b;
+                    v[it][i | 4] = a - b;
                 }
     }
-    const int lanes = LB >= 0 ? (1 << (LB >= 0 ? LB : 0)) / 16 : hblock / 16;
-    if (lanes > 1) lane_stage<1>(v);
-    if (lanes > 2) lane_stage<2>(v);
-    if (lanes > 4) lane_stage<4>(v);
-    if (lanes > 8) lane_stage<8>(v);
-    if (lanes > 16) lane_stage<16>(v);
-    if (lanes > 32) lane_stage<32>(v);
-    for (int bit = 64; bit < lanes; bit <<= 1) {   // across wavefronts
-        const float sgn = (tid & bit) != 0 ? -1.0f : 1.0f;
+    if (LB > 9) {
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            float o[16];
-            __syncthreads();
+        for (int it = 0; it < NIT; ++it)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) xchg[i * TW + tid] = v[it][i];
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 16; ++i) o[i] = xchg[i * TW + (tid ^ bit)];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) v[it][i] = __builtin_fmaf(sgn, v[it][i], o[i]);
-        }
+            for (int i = 0; i < 16; ++i)
+                if ((i & 8) == 0) {
+                    lane_register_swap<32>(v[it][i], v[it][i | 8]);
+                    const float a = v[it][i], b = v[it][i | 8];
+                    v[it][i] = a + b;
+                    v[it][i | 8] = a - b;
+                }
     }
+#pragma unroll
+    for (int bit = 1; bit < NIT; bit <<= 1)
+#pragma unroll
+        for (int it = 0; it < NIT; ++it)
+            if ((it & bit) == 0) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float a = v[it][i], b = v[it | bit][i];
+                    v[it][i] = a + b;
+                    v[it | bit][i] = a - b;
+                }
+            }
+    if (LB > 0) {
+        const int dpp_bits = LB >= 8 ? 15 : LB == 7 ? 7 : LB == 6 ? 3 : LB == 5 ? 1 : 0;
+        const float scale = (__popc(l & dpp_bits) & 1) ? -norm : norm;
+#pragma unroll
+        for (int it = 0; it < NIT; ++it)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[it][i] *= scale;
+    }
+}
+
+template <int LB>
+__device__ inline void unswap_words(unsigned (&w)[4])   // one 32-bit word per four registers of a chunk
+{
+    if (LB > 9) lane_register_swap<32>(w[0], w[2]), lane_register_swap<32>(w[1], w[3]);
+    if (LB > 8) lane_register_swap<16>(w[0], w[1]), lane_register_swap<16>(w[2], w[3]);
+}
+
+template <int LB>
+__device__ inline void unswap_values(float (&v)[16])
+{
+    if (LB > 9) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) lane_register_swap<32>(v[i], v[i | 8]);
+    }
+    if (LB > 8) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if ((i & 4) == 0) lane_register_swap<16>(v[i], v[i | 4]);
+    }
+}
+
+__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void *p, size_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)(unsigned)bytes, 0x00020000);
+}
+
+// the wavefront's chunks of one row as fp32, times the optional per-channel factors (one fp32 multiply each)
+template <int NIT>
+__device__ inline void load_row(const __half *row, bool present, int K, const float *factor, int c0, float (&v)[NIT][16])
+{
+    typedef unsigned v4u __attribute__((ext_vector_type(4)));
+    const __amdgpu_buffer_rsrc_t rs = buffer_of(row, present ? (size_t)K * sizeof(__half) : 0);
+    const __amdgpu_buffer_rsrc_t rf = buffer_of(factor, factor ? (size_t)K * sizeof(float) : 0);
+    v4u raw[NIT][2];
 #pragma unroll
     for (int it = 0; it < NIT; ++it)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[it][i] *= norm;
-}
-
-// One workgroup per token: load, transform, per-token abs-max, quantize, store (row-major and/or tile order).
-// (Collecting 8 tokens per workgroup for whole-line writes of the tile order, as the plain quantizer does at
-// large M, was measured and is slower here: a workgroup transforms its tokens one after the other, and that
-// serial latency costs more than the 16-byte writes save -- 37 us against 27 us for 4096 x 4096.)
-template <int NIT, int LB>
-__global__ __launch_bounds__(TW) void act_quant_transform_kernel(const __half *__restrict__ x, int64_t ldx, int K,
-                                                                 const float *__restrict__ inv_smooth, int hblock,
-                                                                 float norm, int8_t *__restrict__ xq_rm,
-                                                                 int8_t *__restrict__ xq_kl, float *__restrict__ sx)
-{
-    __shared__ float xchg[16 * TW];
-    __shared__ float red[TW / 64];
-    const int m = blockIdx.x, tid = threadIdx.x;
-    const int nchunks = K / 16;
-    const __half *row = x + (size_t)m * ldx;
-    float v[NIT][16];
+        for (int q = 0; q < 2; ++q)
+            raw[it][q] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rs, (unsigned)(c0 + it * 64) * 32u + q * 16u, 0, 0));
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int c = it * TW + tid;
-        if (c < nchunks) {
-            load_chunk(row, c, v[it]);
-            if (inv_smooth) scale_chunk(inv_smooth, c, v[it]);
-        } else {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[it][i] = 0.0f;
+        for (int i = 0; i < 8; ++i) {
+            v[it][2 * i] = half_bits_to_float(raw[it][i / 4][i % 4] & 0xffffu);
+            v[it][2 * i + 1] = half_bits_to_float(raw[it][i / 4][i % 4] >> 16);
+        }
+        if (factor) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const v4u f = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rf, (unsigned)(c0 + it * 64) * 64u + q * 16u, 0, 0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[it][4 * q + e] *= __uint_as_float(f[e]);
+            }
         }
     }
-    if (LB > 0) fwht_row<NIT, LB>(v, hblock, norm, xchg);
+}
 
+// Row of this workgroup: workgroup ids go to the 8 XCDs in turn, every XCD takes one contiguous range of whole groups of
+// `unit` rows (rows that share 128-byte lines of the tile order), so that the lines are completed in one L2.
+__device__ inline int row_of_workgroup(int rows, int unit)
+{
+    const int groups = (rows + unit - 1) / unit, xcd = blockIdx.x % 8, in_xcd = blockIdx.x / 8;
+    const int mine = groups / 8 + (xcd < groups % 8 ? 1 : 0);
+    if (in_xcd >= unit * mine) return rows;
+    return unit * (xcd * (groups / 8) + (xcd < groups % 8 ? xcd : groups % 8)) + in_xcd;
+}
+
+inline int workgroups_for(int rows, int unit) { return 8 * unit * ceil_div(ceil_div(rows, unit), 8); }
+
+constexpr int MAX_WAVES = 16;
+
+// Activations: one workgroup per token, one chunk per lane whatever the block.  The stages of blocks of 2048 and 4096 that
+// lie above a wavefront's 1024 elements are taken behind one exchange through LDS in which each of the W = 2 or 4
+// wavefronts of a block gets its 16 / W values of every lane from all of them; the codes go back the same way, a quarter
+// of the bytes.  (Bound by the 3 bytes per element and, where all tokens are resident at once, by the time the last of them
+// takes from its last byte on: with W chunks per lane in one wavefront 1 x 4096 took 5.4 us instead of 3.8 and
+// 4096 x 4096 20.2 instead of 18.2; with 256 lanes per token, two operations per element and lane stage, a
+// bpermute for the stages across rows and two exchanges of all values, 22.2.)
+template <int LB>
+__global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_hadamard_kernel(const __half *__restrict__ x, int64_t ldx, int M, int K,
+                                                                             const float *__restrict__ inv_smooth, float norm,
+                                                                             int8_t *__restrict__ xq_rm, int8_t *__restrict__ xq_kl,
+                                                                             float *__restrict__ sx)
+{
+    constexpr int W = hadamard_chunks(LB);          // wavefronts per block
+    constexpr int LANE_LB = LB > 10 ? 10 : LB;
+    __shared__ float red[MAX_WAVES];
+    extern __shared__ __attribute__((aligned(16))) float4 exch[];   // W > 1: [wavefront][4 planes of 4 registers][64 lanes]
+    const int m = row_of_workgroup(M, 8);
+    if (m >= M) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+    const int l = logical_lane(lane), c = wave * 64 + l;            // chunk of this lane
+    float v[1][16];
+    load_row<1>(x + (size_t)m * ldx, true, K, inv_smooth, c, v);
+    hadamard_wave<LANE_LB>(v, l, W > 1 ? 1.0f : norm);
+    const int first = wave / W * W, part = wave % W;                // wavefronts of the block; this one's share of the registers
+    constexpr int P = 4 / W;                                        // planes per share
+    if constexpr (W > 1) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) exch[(wave * 4 + p) * 64 + lane] = make_float4(v[0][4 * p], v[0][4 * p + 1], v[0][4 * p + 2], v[0][4 * p + 3]);
+        __syncthreads();
+#pragma unroll
+        for (int src = 0; src < W; ++src)
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                const float4 f = exch[((first + src) * 4 + part * P + p) * 64 + lane];
+                const int at = 4 * (src * P + p);
+                v[0][at] = f.x, v[0][at + 1] = f.y, v[0][at + 2] = f.z, v[0][at + 3] = f.w;
+            }
+#pragma unroll
+        for (int bit = 1; bit < W; bit <<= 1)
+#pragma unroll
+            for (int src = 0; src < W; ++src)
+                if ((src & bit) == 0) {
+#pragma unroll
+                    for (int e = 0; e < 4 * P; ++e) {
+                        const float f = v[0][4 * src * P + e], g = v[0][4 * (src | bit) * P + e];
+                        v[0][4 * src * P + e] = f + g;
+                        v[0][4 * (src | bit) * P + e] = f - g;
+                    }
+                }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[0][i] *= norm;
+    }
     float amax = 0.0f;
 #pragma unroll
-    for (int it = 0; it < NIT; ++it)
+    for (int i = 0; i < 16; ++i) amax = __builtin_elementwise_maximum(amax, fabsf(v[0][i]));   // passes a NaN on
 #pragma unroll
-        for (int i = 0; i < 16; ++i) amax = fmaxf(amax, fabsf(v[it][i]));
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
-    if ((tid & 63) == 0) red[tid >> 6] = amax;
-    __syncthreads();
-    amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    for (int off = 32; off > 0; off >>= 1) amax = __builtin_elementwise_maximum(amax, __shfl_xor(amax, off, 64));
+    if (nwaves > 1) {
+        if (lane == 0) red[wave] = amax;
+        __syncthreads();
+        for (int w = 0; w < nwaves; ++w) amax = __builtin_elementwise_maximum(amax, red[w]);
+    }
     float scale, inv;
     token_scales_f32(amax, scale, inv);
-    if (tid == 0) sx[m] = scale;
+    if (threadIdx.x == 0) sx[m] = scale;
+    const uint4 s = quant_chunk_f32(v[0], inv);
+    unsigned w[4] = {s.x, s.y, s.z, s.w};
+    if constexpr (W > 1) {   // word (src, p) of this share is word part * P + p of the chunk that wavefront `src` started from
+        unsigned *words = reinterpret_cast<unsigned *>(exch);
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int c = it * TW + tid;
-        if (c < nchunks) {
-            const uint4 q = quant_chunk_f32(v[it], inv);
-            if (xq_rm) *reinterpret_cast<uint4 *>(xq_rm + (size_t)m * K + (size_t)c * 16) = q;
-            if (xq_kl) *reinterpret_cast<uint4 *>(xq_kl + tile_offset_i8(m, c * 16, K)) = q;
-        }
+        for (int src = 0; src < W; ++src)
+#pragma unroll
+            for (int p = 0; p < P; ++p) words[((first + src) * 64 + lane) * 4 + part * P + p] = w[src * P + p];
+        __syncthreads();
+        const uint4 q = *reinterpret_cast<const uint4 *>(words + (wave * 64 + lane) * 4);
+        w[0] = q.x, w[1] = q.y, w[2] = q.z, w[3] = q.w;
+    }
+    unswap_words<LANE_LB>(w);
+    if (c < K / 16) {
+        const uint4 q = make_uint4(w[0], w[1], w[2], w[3]);
+        if (xq_rm) *reinterpret_cast<uint4 *>(xq_rm + (size_t)m * K + (size_t)c * 16) = q;
+        if (xq_kl) *reinterpret_cast<uint4 *>(xq_kl + tile_offset_i8(m, c * 16, K)) = q;
     }
 }
 
-// Offline: one workgroup per weight row (output channel): S W and/or H^T W as fp32
-template <int NIT>
-__global__ __launch_bounds__(TW) void weight_transform_kernel(const __half *__restrict__ w, int K,
-                                                              const float *__restrict__ smooth, int hblock, float norm,
-                                                              float *__restrict__ out)
+__device__ inline int weight_code(float w, float s, float limit)   // the quantizer of weight_quant.hip, symmetric range
 {
-    __shared__ float xchg[16 * TW];
-    const int n = blockIdx.x, tid = threadIdx.x;
-    const int nchunks = K / 16;
+    return (int)fminf(fmaxf(rintf(w / s), -limit), limit);         // IEEE fp32 division by the stored scale, ties to even
+}
+
+// Offline: S W and / or H^T W of one weight row (output channel) per workgroup, its fp32 values stored (w32) and quantized
+// from the registers in the same pass (bound by HBM: 2 bytes in, 4 + 2 x codes out per weight; as two kernels the
+// fp32 values were read back: 145 us for 4096 x 11008, int4, against 87 in one).  Rows N .. 32-row padding: zero codes.
+template <int LB, int BITS>
+__global__ __launch_bounds__(MAX_WAVES * 64) void weight_transform_quant_kernel(const __half *__restrict__ w, int N, int Npad, int K,
+                                                                                 const float *__restrict__ smooth, float norm,
+                                                                                 float *__restrict__ w32, uint8_t *__restrict__ canon,
+                                                                                 void *__restrict__ scales, uint8_t *__restrict__ kl,
+                                                                                 __half *__restrict__ kl_scales, __half *__restrict__ kl_scales_dec)
+{
+    constexpr int NIT = hadamard_chunks(LB);
+    __shared__ float red[MAX_WAVES];
+    const int n = row_of_workgroup(Npad, 32);
+    if (n >= Npad) return;
+    const bool real = n < N;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+    const int l = logical_lane(lane), c0 = wave * NIT * 64 + l, G = K / 128;
     float v[NIT][16];
+    load_row<NIT>(w + (size_t)(real ? n : 0) * K, real, K, smooth, c0, v);
+    hadamard_wave<LB>(v, l, norm);
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) unswap_values<LB>(v[it]);
+    float amax[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int c = it * TW + tid;
-        if (c < nchunks) {
-            load_chunk(w + (size_t)n * K, c, v[it]);
-            if (smooth) scale_chunk(smooth, c, v[it]);
-        } else {
+        const int c = c0 + it * 64;
+        amax[it] = 0.0f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[it][i] = 0.0f;
-        }
-    }
-    if (hblock > 1) fwht_row<NIT>(v, hblock, norm, xchg);
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int c = it * TW + tid;
-        if (c < nchunks) {
+        for (int i = 0; i < 16; ++i) amax[it] = fmaxf(amax[it], fabsf(v[it][i]));
+        if (real && c < K / 16) {
 #pragma unroll
             for (int i = 0; i < 16; i += 4)
-                *reinterpret_cast<float4 *>(out + (size_t)n * K + (size_t)c * 16 + i) =
-                    make_float4(v[it][i], v[it][i + 1], v[it][i + 2], v[it][i + 3]);
+                *reinterpret_cast<float4 *>(w32 + (size_t)n * K + (size_t)c * 16 + i) = make_float4(v[it][i], v[it][i + 1], v[it][i + 2], v[it][i + 3]);
+        }
+    }
+    if constexpr (BITS == 8) {
+        float mx = amax[0];
+#pragma unroll
+        for (int it = 1; it < NIT; ++it) mx = fmaxf(mx, amax[it]);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+        if (lane == 0) red[wave] = mx;
+        __syncthreads();
+        for (int i = 0; i < nwaves; ++i) mx = fmaxf(mx, red[i]);
+        float s = mx / 127.0f;
+        if (s == 0.0f) s = 1.0f;
+        if (real && scales && threadIdx.x == 0) static_cast<float *>(scales)[n] = s;
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int c = c0 + it * 64;
+            unsigned q[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int i = 0; i < 16; ++i) q[i / 4] |= (unsigned)(weight_code(v[it][i], s, 127.0f) & 0xff) << (8 * (i % 4));
+            const uint4 o = make_uint4(q[0], q[1], q[2], q[3]);
+            if (c < K / 16) {
+                if (real && canon) *reinterpret_cast<uint4 *>(canon + (size_t)n * K + (size_t)c * 16) = o;
+                if (kl) *reinterpret_cast<uint4 *>(kl + tile_offset_i8(n, c * 16, K)) = o;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int c = c0 + it * 64;
+            float mx = amax[it];   // a group of 128 is the eight chunks of lanes 8i .. 8i + 7
+            mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 4, 64));
+            __half s16 = __float2half_rn(mx / 7.0f);
+            if (__half2float(s16) == 0.0f) s16 = __float2half_rn(1.0f);
+            const float s = __half2float(s16);
+            int q[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) q[i] = weight_code(v[it][i], s, 7.0f) & 0xf;
+            if (c >= K / 16) continue;
+            const int g = c / 8;
+            if (c % 8 == 0) {
+                if (real && scales) static_cast<__half *>(scales)[(size_t)n * G + g] = s16;
+                if (kl) {
+                    kl_scales[(size_t)g * Npad + n] = s16;
+                    kl_scales_dec[((size_t)(n / 16) * G + g) * 16 + n % 16] = s16;
+                }
+            }
+            if (real && canon) {
+                unsigned lo = 0, hi = 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    lo |= (unsigned)(q[2 * i] | (q[2 * i + 1] << 4)) << (8 * i);
+                    hi |= (unsigned)(q[8 + 2 * i] | (q[8 + 2 * i + 1] << 4)) << (8 * i);
+                }
+                *reinterpret_cast<uint2 *>(canon + (size_t)n * (K / 2) + (size_t)c * 8) = make_uint2(lo, hi);
+            }
+            if (kl) {
+                unsigned w0 = 0, w1 = 0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    w0 |= (unsigned)q[i] << (4 * w4_nibble_pos(i));
+                    w1 |= (unsigned)q[8 + i] << (4 * w4_nibble_pos(i));
+                }
+                *reinterpret_cast<uint2 *>(kl + tile_offset_w4_word(n, c * 16, K)) = make_uint2(w0, w1);
+            }
         }
     }
 }
 
-// Calibration: running max|X_j| per input channel (non-negative floats order like their bit patterns)
-__global__ void channel_absmax_kernel(const __half *__restrict__ x, int64_t ldx, int M, int K, int rows_per_block,
-                                      unsigned *__restrict__ xmax_bits)
+// Calibration: running max|X_j| per input channel (non-negative floats order like their bit patterns).  A workgroup takes
+// 256 channels x 64 tokens: 8 channels (16 bytes) per lane, 8 tokens side by side, one atomic per channel at the end.
+__global__ __launch_bounds__(256) void channel_absmax_kernel(const __half *__restrict__ x, int64_t ldx, int M, int K,
+                                                             unsigned *__restrict__ xmax_bits)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ float red[8][256 + 8];
+    const int col = threadIdx.x & 31, r = threadIdx.x >> 5;
+    const int k0 = blockIdx.x * 256 + col * 8, m0 = blockIdx.y * 64;
+    float mx[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (k0 < K) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int m = m0 + r + 8 * i;
+            if (m < M) {
+                const uint4 h = *reinterpret_cast<const uint4 *>(x + (size_t)m * ldx + k0);
+                const unsigned w[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    mx[2 * e] = fmaxf(mx[2 * e], fabsf(half_bits_to_float(w[e] & 0xffffu)));
+                    mx[2 * e + 1] = fmaxf(mx[2 * e + 1], fabsf(half_bits_to_float(w[e] >> 16)));
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[r][col * 8 + e] = mx[e];
+    __syncthreads();
+    const int k = blockIdx.x * 256 + threadIdx.x;
     if (k >= K) return;
-    const int m0 = blockIdx.y * rows_per_block;
-    const int m1 = min(M, m0 + rows_per_block);
-    float mx = 0.0f;
-    for (int m = m0; m < m1; ++m) mx = fmaxf(mx, fabsf(__half2float(x[(size_t)m * ldx + k])));
-    atomicMax(xmax_bits + k, __float_as_uint(mx));
+    float a = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a = fmaxf(a, red[i][threadIdx.x]);
+    atomicMax(xmax_bits + k, __float_as_uint(a));
 }
 
-// s_j = xmax_j^alpha / wmax_j^(1-alpha), 1 where either maximum is 0; inv_j = 1 / s_j (IEEE fp32 division)
-__global__ void smooth_scales_kernel(const float *__restrict__ xmax, const __half *__restrict__ w, int N, int K,
-                                     float alpha, float *__restrict__ s, float *__restrict__ inv_s)
+// s_j = xmax_j^alpha / wmax_j^(1-alpha), 1 where either maximum is 0; inv_j = 1 / s_j (IEEE fp32 division).  A workgroup
+// finds the column maxima of 64 channels over all N rows (8 channels per lane, 64 rows side by side, 8 loads of each lane in
+// flight: a strip of 128 bytes per row streams at the rate one CU can pull) -- one lane per channel walking
+// down the rows took 1570 us for 4096 x 11008.
+__global__ __launch_bounds__(512) void smooth_scales_kernel(const float *__restrict__ xmax, const __half *__restrict__ w, int N, int K,
+                                                            float alpha, float *__restrict__ s, float *__restrict__ inv_s)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= K) return;
+    __shared__ float red[8][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 7;
+    const __half *base = w + (size_t)blockIdx.x * 64 + col * 8;
+    float mx[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int n0 = 0; n0 < N; n0 += 512) {
+        uint4 h[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {   // (a row behind the last one: the last one again)
+            const int n = n0 + i * 64 + wave * 8 + (lane >> 3);
+            h[i] = *reinterpret_cast<const uint4 *>(base + (size_t)(n < N ? n : N - 1) * K);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const unsigned q[4] = {h[i].x, h[i].y, h[i].z, h[i].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                mx[2 * e] = fmaxf(mx[2 * e], fabsf(half_bits_to_float(q[e] & 0xffffu)));
+                mx[2 * e + 1] = fmaxf(mx[2 * e + 1], fabsf(half_bits_to_float(q[e] >> 16)));
+            }
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+#pragma unroll
+        for (int off = 8; off < 64; off <<= 1) mx[e] = fmaxf(mx[e], __shfl_xor(mx[e], off, 64));
+        if (lane < 8) red[wave][col * 8 + e] = mx[e];
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
     float wmax = 0.0f;
-    for (int n = 0; n < N; ++n) wmax = fmaxf(wmax, fabsf(__half2float(w[(size_t)n * K + k])));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) wmax = fmaxf(wmax, red[i][threadIdx.x]);
+    const int k = blockIdx.x * 64 + threadIdx.x;
     const float xm = xmax[k];
     float sj = 1.0f;
     if (xm > 0.0f && wmax > 0.0f) sj = (float)(pow((double)xm, (double)alpha) / pow((double)wmax, 1.0 - (double)alpha));
@@ -247,67 +505,75 @@ int hadamard_block_of(int K)
     return b < 4096 ? b : 4096;
 }
 
+// calls f(integral constant LB) for the block's exponent (0: no transform)
+template <typename F>
+static int by_block(int hblock, F f)
+{
+    int lb = 0;
+    while (hblock > 1 && (1 << lb) < hblock) ++lb;
+    switch (lb) {
+    case 0: return f(std::integral_constant<int, 0>{});
+    case 4: return f(std::integral_constant<int, 4>{});
+    case 5: return f(std::integral_constant<int, 5>{});
+    case 6: return f(std::integral_constant<int, 6>{});
+    case 7: return f(std::integral_constant<int, 7>{});
+    case 8: return f(std::integral_constant<int, 8>{});
+    case 9: return f(std::integral_constant<int, 9>{});
+    case 10: return f(std::integral_constant<int, 10>{});
+    case 11: return f(std::integral_constant<int, 11>{});
+    case 12: return f(std::integral_constant<int, 12>{});
+    default: return fail(QL_ERR_UNSUPPORTED, "hadamard_block=%d", hblock);
+    }
+}
+
 int launch_act_quant_transform(const __half *x, int64_t ldx, int M, int K, const float *inv_smooth, int hblock,
                                int8_t *xq_rm, int8_t *xq_kl, float *sx, hipStream_t st)
 {
     if (M == 0) return QL_OK;
-    const int nit = ceil_div(K / 16, TW);
     const float norm = block_norm(hblock > 1 ? hblock : 1);
-    int lb = 0;
-    while (hblock > 1 && (1 << lb) < hblock) ++lb;
-#define QL_LAUNCH(NIT, LB)                                                                                        \
-    hipLaunchKernelGGL((act_quant_transform_kernel<NIT, LB>), dim3(M), dim3(TW), 0, st, x, ldx, K, inv_smooth,    \
-                       hblock, norm, xq_rm, xq_kl, sx)
-#define QL_BY_BLOCK(NIT)                                                                                          \
-    switch (lb) {                                                                                                 \
-    case 0: QL_LAUNCH(NIT, 0); break;                                                                             \
-    case 4: QL_LAUNCH(NIT, 4); break;                                                                             \
-    case 5: QL_LAUNCH(NIT, 5); break;                                                                             \
-    case 6: QL_LAUNCH(NIT, 6); break;                                                                             \
-    case 7: QL_LAUNCH(NIT, 7); break;                                                                             \
-    case 8: QL_LAUNCH(NIT, 8); break;                                                                             \
-    case 9: QL_LAUNCH(NIT, 9); break;                                                                             \
-    case 10: QL_LAUNCH(NIT, 10); break;                                                                           \
-    case 11: QL_LAUNCH(NIT, 11); break;                                                                           \
-    case 12: QL_LAUNCH(NIT, 12); break;                                                                           \
-    default: return fail(QL_ERR_UNSUPPORTED, "hadamard_block=%d", hblock);                                        \
-    }
-    if (nit == 1) { QL_BY_BLOCK(1) }
-    else if (nit == 2) { QL_BY_BLOCK(2) }
-    else if (nit == 3) { QL_BY_BLOCK(3) }
-    else { QL_BY_BLOCK(4) }
-#undef QL_BY_BLOCK
-#undef QL_LAUNCH
-    return check_hip(hipGetLastError(), "act_quant_transform launch");
+    return by_block(hblock, [&](auto lb) {
+        constexpr int LB = decltype(lb)::value;
+        const int waves = ceil_div(K / 16, 64);   // (a block of W > 1 wavefronts divides K: every block is complete)
+        const unsigned lds = LB > 10 ? waves * 4096u : 0u;
+        hipLaunchKernelGGL((act_quant_hadamard_kernel<LB>), dim3(workgroups_for(M, 8)), dim3(waves * 64), lds, st, x, ldx, M, K, inv_smooth,
+                           norm, xq_rm, xq_kl, sx);
+        return check_hip(hipGetLastError(), "act_quant_hadamard launch");
+    });
 }
 
-int launch_weight_transform(const __half *w, int N, int K, const float *smooth, int hblock, float *out, hipStream_t st)
+int launch_weight_transform_quant(const __half *w, int N, int K, int bits, int group, const float *smooth, int hblock, float *w32,
+                                  void *canon, void *scales, void *kl, hipStream_t st)
 {
-    const int nit = ceil_div(K / 16, TW);
     const float norm = block_norm(hblock > 1 ? hblock : 1);
-#define QL_LAUNCH(NIT) \
-    hipLaunchKernelGGL((weight_transform_kernel<NIT>), dim3(N), dim3(TW), 0, st, w, K, smooth, hblock, norm, out)
-    if (nit == 1) QL_LAUNCH(1);
-    else if (nit == 2) QL_LAUNCH(2);
-    else if (nit == 3) QL_LAUNCH(3);
-    else QL_LAUNCH(4);
-#undef QL_LAUNCH
-    return check_hip(hipGetLastError(), "weight_transform launch");
+    const int Npad = round_up(N, TILE_ROWS), rows = kl ? Npad : N;   // padding rows exist in the kernel layout only
+    uint8_t *blob = static_cast<uint8_t *>(kl);
+    __half *kls = (kl && bits == 4) ? reinterpret_cast<__half *>(blob + w4_scales_offset(N, K)) : nullptr;
+    __half *klsd = (kl && bits == 4) ? reinterpret_cast<__half *>(blob + w4_scales_dec_offset(N, K, group)) : nullptr;
+    return by_block(hblock, [&](auto lb) {
+        constexpr int LB = decltype(lb)::value;
+        const dim3 grid(workgroups_for(rows, 32)), block(ceil_div(K / 16, 64 * hadamard_chunks(LB)) * 64);
+        if (bits == 8)
+            hipLaunchKernelGGL((weight_transform_quant_kernel<LB, 8>), grid, block, 0, st, w, N, rows, K, smooth, norm, w32,
+                               static_cast<uint8_t *>(canon), scales, blob, kls, klsd);
+        else
+            hipLaunchKernelGGL((weight_transform_quant_kernel<LB, 4>), grid, block, 0, st, w, N, rows, K, smooth, norm, w32,
+                               static_cast<uint8_t *>(canon), scales, blob, kls, klsd);
+        return check_hip(hipGetLastError(), "weight_transform_quant launch");
+    });
 }
 
 int launch_channel_absmax(const __half *x, int64_t ldx, int M, int K, float *xmax, hipStream_t st)
 {
     if (M == 0) return QL_OK;
-    const int rows_per_block = 64;
-    hipLaunchKernelGGL(channel_absmax_kernel, dim3(ceil_div(K, 256), ceil_div(M, rows_per_block)), dim3(256), 0, st, x,
-                       ldx, M, K, rows_per_block, reinterpret_cast<unsigned *>(xmax));
+    hipLaunchKernelGGL(channel_absmax_kernel, dim3(ceil_div(K, 256), ceil_div(M, 64)), dim3(256), 0, st, x, ldx, M, K,
+                       reinterpret_cast<unsigned *>(xmax));
     return check_hip(hipGetLastError(), "channel_absmax launch");
 }
 
 int launch_smooth_scales(const float *xmax, const __half *w, int N, int K, float alpha, float *s, float *inv_s,
                          hipStream_t st)
 {
-    hipLaunchKernelGGL(smooth_scales_kernel, dim3(ceil_div(K, 256)), dim3(256), 0, st, xmax, w, N, K, alpha, s, inv_s);
+    hipLaunchKernelGGL(smooth_scales_kernel, dim3(K / 64), dim3(512), 0, st, xmax, w, N, K, alpha, s, inv_s);
     return check_hip(hipGetLastError(), "smooth_scales launch");
 }
 

@@ -20,7 +20,7 @@ struct alignas(16) Half16 {
     uint4 lo, hi;
 };
 
-// 16 consecutive weights as fp32: from fp16 (exact widening) or from the fp32 output of a transform kernel
+// 16 consecutive weights as fp32 (exact widening)
 __device__ inline void load16(const __half *row, int c, float (&v)[16])
 {
     const Half16 h = reinterpret_cast<const Half16 *>(row)[c];
@@ -29,15 +29,6 @@ __device__ inline void load16(const __half *row, int c, float (&v)[16])
     for (int i = 0; i < 8; ++i) {
         v[2 * i] = __half2float(__ushort_as_half((unsigned short)(w[i] & 0xffffu)));
         v[2 * i + 1] = __half2float(__ushort_as_half((unsigned short)(w[i] >> 16)));
-    }
-}
-
-__device__ inline void load16(const float *row, int c, float (&v)[16])
-{
-#pragma unroll
-    for (int i = 0; i < 16; i += 4) {
-        const float4 f = *reinterpret_cast<const float4 *>(row + (size_t)c * CHUNK + i);
-        v[i] = f.x, v[i + 1] = f.y, v[i + 2] = f.z, v[i + 3] = f.w;
     }
 }
 
@@ -63,8 +54,7 @@ __device__ inline float scale_of(float amax, int range, float qmax)
     return range == QL_RANGE_EQ2 ? (2.0f * amax) / (2.0f * qmax + 1.0f) : amax / qmax;   // one IEEE fp32 division
 }
 
-template <typename T>
-__global__ void weight_quant8_kernel(const T *__restrict__ w, int N, int K, int range,
+__global__ void weight_quant8_kernel(const __half *__restrict__ w, int N, int K, int range,
                                      const unsigned *__restrict__ tensor_amax,
                                      int8_t *__restrict__ canon, float *__restrict__ scales,
                                      int8_t *__restrict__ kl)
@@ -78,7 +68,7 @@ __global__ void weight_quant8_kernel(const T *__restrict__ w, int N, int K, int 
                 *reinterpret_cast<uint4 *>(kl + tile_offset_i8(n, c * CHUNK, K)) = make_uint4(0, 0, 0, 0);
         return;
     }
-    const T *row = w + (size_t)n * K;
+    const __half *row = w + (size_t)n * K;
     float mx = 0.0f;
     if (tensor_amax) {
         mx = __uint_as_float(*tensor_amax);
@@ -113,8 +103,7 @@ __global__ void weight_quant8_kernel(const T *__restrict__ w, int N, int K, int 
 }
 
 // group == 128: eight consecutive lanes hold one group.
-template <typename T>
-__global__ void weight_quant4_kernel(const T *__restrict__ w, int N, int Npad, int K, int range,
+__global__ void weight_quant4_kernel(const __half *__restrict__ w, int N, int Npad, int K, int range,
                                      const unsigned *__restrict__ tensor_amax,
                                      uint8_t *__restrict__ canon, __half *__restrict__ scales,
                                      uint8_t *__restrict__ kl_codes, __half *__restrict__ kl_scales,
@@ -172,8 +161,7 @@ __global__ void weight_quant4_kernel(const T *__restrict__ w, int N, int Npad, i
 
 // max |w| over the whole matrix as a bit pattern (non-negative floats order like unsigned integers);
 // *out must hold 0 (or an earlier maximum) on entry
-template <typename T>
-__global__ void tensor_absmax_kernel(const T *__restrict__ w, size_t nchunks, unsigned *__restrict__ out)
+__global__ void tensor_absmax_kernel(const __half *__restrict__ w, size_t nchunks, unsigned *__restrict__ out)
 {
     float mx = 0.0f;
     for (size_t c = blockIdx.x * (size_t)blockDim.x + threadIdx.x; c < nchunks; c += (size_t)gridDim.x * blockDim.x) {
@@ -222,25 +210,23 @@ __global__ void export4_kernel(const uint8_t *__restrict__ kl_codes, const __hal
 
 }  // namespace
 
-template <typename T>
-static int launch_wq8(const T *w, int N, int K, int8_t *canon, float *scales, int8_t *kl, hipStream_t st,
+static int launch_wq8(const __half *w, int N, int K, int8_t *canon, float *scales, int8_t *kl, hipStream_t st,
                       int range = QL_RANGE_SYMMETRIC, const unsigned *tensor_amax = nullptr)
 {
     const int rows = kl ? round_up(N, TILE_ROWS) : N;
-    hipLaunchKernelGGL(weight_quant8_kernel<T>, dim3(rows), dim3(256), 0, st, w, N, K, range, tensor_amax, canon,
+    hipLaunchKernelGGL(weight_quant8_kernel, dim3(rows), dim3(256), 0, st, w, N, K, range, tensor_amax, canon,
                        scales, kl);
     return check_hip(hipGetLastError(), "weight_quant8 launch");
 }
 
-template <typename T>
-static int launch_wq4(const T *w, int N, int K, int group, uint8_t *canon, __half *scales, uint8_t *kl, hipStream_t st,
+static int launch_wq4(const __half *w, int N, int K, int group, uint8_t *canon, __half *scales, uint8_t *kl, hipStream_t st,
                       int range = QL_RANGE_SYMMETRIC, const unsigned *tensor_amax = nullptr)
 {
     const int Npad = round_up(N, TILE_ROWS);
     const int rows = kl ? Npad : N;
     __half *kls = kl ? reinterpret_cast<__half *>(kl + w4_scales_offset(N, K)) : nullptr;
     __half *klsd = kl ? reinterpret_cast<__half *>(kl + w4_scales_dec_offset(N, K, group)) : nullptr;
-    hipLaunchKernelGGL(weight_quant4_kernel<T>, dim3(rows), dim3(256), 0, st, w, N, Npad, K, range, tensor_amax,
+    hipLaunchKernelGGL(weight_quant4_kernel, dim3(rows), dim3(256), 0, st, w, N, Npad, K, range, tensor_amax,
                        canon, scales, kl, kls, klsd);
     return check_hip(hipGetLastError(), "weight_quant4 launch");
 }
@@ -265,7 +251,7 @@ int launch_weight_quant_opt(const __half *w, int N, int K, int bits, int group, 
         const size_t nchunks = (size_t)N * K / CHUNK;
         const int blocks = (int)((nchunks + 255) / 256 < 2048 ? (nchunks + 255) / 256 : 2048);
         hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(1), 0, st, amax_scratch, 0u);
-        hipLaunchKernelGGL(tensor_absmax_kernel<__half>, dim3(blocks), dim3(256), 0, st, w, nchunks, amax_scratch);
+        hipLaunchKernelGGL(tensor_absmax_kernel, dim3(blocks), dim3(256), 0, st, w, nchunks, amax_scratch);
         QL_TRY(check_hip(hipGetLastError(), "tensor_absmax launch"));
     }
     const unsigned *ta = per_tensor ? amax_scratch : nullptr;
@@ -274,19 +260,6 @@ int launch_weight_quant_opt(const __half *w, int N, int K, int bits, int group, 
                           static_cast<int8_t *>(kl), st, range, ta);
     return launch_wq4(w, N, K, group, static_cast<uint8_t *>(canon), static_cast<__half *>(scales),
                       static_cast<uint8_t *>(kl), st, range, ta);
-}
-
-// the same quantizers on fp32 weights (the output of a transform, Eq. 3-4)
-int launch_weight_quant8_f32(const float *w, int N, int K, int8_t *canon, float *scales, int8_t *kl,
-                             hipStream_t st)
-{
-    return launch_wq8(w, N, K, canon, scales, kl, st);
-}
-
-int launch_weight_quant4_f32(const float *w, int N, int K, int group, uint8_t *canon, __half *scales,
-                             uint8_t *kl, hipStream_t st)
-{
-    return launch_wq4(w, N, K, group, canon, scales, kl, st);
 }
 
 int launch_export8(const int8_t *kl, int N, int K, int8_t *canon, hipStream_t st)
