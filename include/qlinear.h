@@ -198,7 +198,10 @@ int ql_w4a8_gemm_acc_i32(const int8_t *xq_kernel, int M, int K, const void *w4_k
  *   shapes 6, 15, 17, 19, 23 on the 16x16x64 matrix instruction); 202..232 / 302..332
  *   split-K with that many splits on 128x128 / 256x256 tiles; 101..104, 106, 108 decode kernels with that many
  *   groups of 16 channels per workgroup; 111 sixteen wavefronts; 121 tokens never staged in LDS; 122 / 123 token
- *   blocks of 32 / 64; 130 quantizer never fused into the decode GEMM.  Unknown values -> QL_ERR_UNSUPPORTED. */
+ *   blocks of 32 / 64; 130 quantizer never fused into the decode GEMM.  int4 weights have five tile forms of their own:
+ *   6, 26 = 256x256; 15, 35 = 192x256 (tokens x channels); 4, 11, 13, 19, 20, 39 = 128x128; 23, 43 = 256x256 with the last
+ *   third of the channels in 128x256 tiles; 202..232 split-K on 128x128; every other tile value = 128x256.
+ *   Unknown values -> QL_ERR_UNSUPPORTED. */
 int ql_set_kernel_variant(int variant);
 
 /* What the automatic choice launches for a GEMM of this shape, and the time estimate it goes by (host
@@ -211,7 +214,7 @@ enum { QL_FAMILY_DECODE = 1, QL_FAMILY_TILE = 2 };
 typedef struct ql_plan {
     int family;         /* QL_FAMILY_DECODE: weight-streaming kernels (every workgroup owns tile_channels channels and
                            the whole K for a block of tile_tokens tokens); QL_FAMILY_TILE: prefill tile kernels */
-    int variant;        /* the ql_set_kernel_variant value closest to this choice (0: int4 tiles, which have one shape) */
+    int variant;        /* the ql_set_kernel_variant value closest to this choice */
     int tile_tokens;    /* tokens x channels one workgroup owns */
     int tile_channels;
     int splits;         /* workgroups sharing one tile's K range (1: unsplit; > 1 needs the scratch) */

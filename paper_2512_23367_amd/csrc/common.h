@@ -127,6 +127,10 @@ struct GemmArgs {
 };
 int launch_gemm_prefill(const GemmArgs &a, int variant, hipStream_t st);
 int launch_gemm_decode(const GemmArgs &a, int variant, hipStream_t st);
+// the int4 half of the tile kernels (gemm_prefill_w4.hip)
+int launch_gemm_prefill_w4(const GemmArgs &a, int variant, hipStream_t st);
+double prefill_w4_estimate_us(const GemmArgs &a);
+void prefill_w4_plan(const GemmArgs &a, int *variant, int *tile_tokens, int *tile_channels, int *splits);
 // estimated time (us) of the automatic choice of the tile kernels / of the decode kernels (33 tokens and more)
 double prefill_estimate_us(const GemmArgs &a);
 double decode_estimate_us(const GemmArgs &a);

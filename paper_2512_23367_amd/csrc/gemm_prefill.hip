@@ -1,6 +1,6 @@
-// Prefill GEMM + dequantization epilogue of the W8A8 / W4A8 linear layer for gfx950
-// (the int8 / W4A8 matrix multiplication and "dequantization logic" of the paper's
-// inference framework, Method section; integer accumulation, Y = XW).
+// Prefill GEMM + dequantization epilogue of the W8A8 linear layer for gfx950
+// (the int8 matrix multiplication and "dequantization logic" of the paper's
+// inference framework, Method section; integer accumulation, Y = XW).  int4 weights: gemm_prefill_w4.hip.
 //
 // Both operands arrive in tile order (32 rows x 32 k per 1024-byte tile, already in the lane order
 // of the 32x32x32 int8 matrix instruction), so:
@@ -14,7 +14,7 @@
 // Pipeline: STAGES LDS buffers of KBS k-blocks each, loads issued STAGES-1 stages ahead.  The default
 // main loop is a ping-pong: the 8 wavefronts form two groups (one wavefront of each per SIMD) that run
 // one phase apart, so that on every SIMD one wavefront issues matrix instructions while the other reads
-// fragments from LDS, issues global loads and (int4) does the vector-ALU work; every phase ends with the
+// fragments from LDS and issues global loads; every phase ends with the
 // workgroup barrier.  Other configurations (256x384, 256x192 and 128x256 tiles, 128x128 tiles with 4 wavefronts or
 // with the two groups splitting the k-blocks of every stage, a rotated single-phase loop) serve shapes whose
 // 256x256 tile count fills the 256 CUs badly or whose N suits wider tiles; the automatic choice compares
@@ -23,11 +23,7 @@
 // Few tokens (a weight byte is needed by one workgroup only, the layer is bound by streaming the weights) go to
 // the decode kernels instead when their estimated time is lower (prefill_estimate_us below is this file's side
 // of that comparison).
-//
-// W4A8: weight tiles hold nibbles; the unpack (shift + mask, giving 16 * code in each byte) sits
-// between the LDS read and the matrix instruction, and every 128 k the int32 partial is folded into
-// an fp32 accumulator with the group's scale.
-#include "common.h"
+#include "gemm_tiles.h"
 #include <cmath>
 #include <algorithm>
 #include <type_traits>
@@ -35,79 +31,24 @@
 namespace ql {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
-typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-
-enum { EPI_F16 = 0, EPI_ACC = 1, EPI_PART = 2 };   // EPI_PART: split-K, raw partial sums to the workspace
 
 struct PrefillParams {
     const int8_t *xq;
     const void *wq;
     const float *sx;
     const float *sw;
-    const __half *wscales;   // W4A8: [G][Npad] fp16
     const __half *bias;
     __half *y;
     int64_t ldy;
     int32_t *acc;
     int64_t ldacc;           // row stride of acc
-    int32_t *partials;
-    int row0, nrows;
-    int M, N, K, Npad;
+    int M, N, K;
     int tiles_m, tiles_n, group_m;   // group_m: token tiles per strip of the tile order (see tile_coords)
     unsigned x_bytes, w_bytes;
     void *part;              // split-K: partial sums [split][workgroup][wavefront][block][quad][64 lanes x 16 B]
     int stages_per_split;    // split-K: blockIdx.y takes stages [y * stages_per_split, ...); otherwise all of them
 };
-
-#define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
-
-template <int N>
-__device__ inline void wait_vmcnt()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
-}
-
-// Hardware hands consecutive workgroup ids to the 8 XCDs in turn; give every XCD one contiguous
-// range of logical tiles, ordered (strips of `group` token tiles, channel tile by channel tile) so that the
-// tiles an XCD runs together form a block that shares activation and weight strips in that XCD's L2.
-__device__ inline void tile_coords(int bid, int tiles_m, int tiles_n, int group, int &tm, int &tn)
-{
-    const int nt = tiles_m * tiles_n;
-    const int xcd = bid % 8, idx = bid / 8;
-    const int per = nt / 8, rem = nt % 8;
-    const int logical = xcd * per + (xcd < rem ? xcd : rem) + idx;
-    const int per_group = group * tiles_n;
-    const int g = logical / per_group, in_g = logical % per_group;
-    const int first_m = g * group;
-    const int gsize = (tiles_m - first_m) < group ? (tiles_m - first_m) : group;
-    tm = first_m + in_g % gsize;
-    tn = in_g / gsize;
-}
-
-// Strip height: the tiles resident on one XCD together (32 CUs x occupancy, or all of its tiles if fewer) should
-// form the block that fetches the fewest operand bytes -- a x b tiles cost a*TM + b*TN rows of K bytes.  Only
-// divisors of tiles_m are considered (equal strips; a ragged last strip costs more than it saves), ties go to
-// the shorter strip (measured: fewer bytes fetched when the block does not fit the 4 MB L2 anyway).
-inline int strip_height(int tiles_m, int tiles_n, int TM, int TN, int occupancy)
-{
-    const long per_xcd = ((long)tiles_m * tiles_n + 7) / 8;
-    const long together = per_xcd < 32L * occupancy ? per_xcd : 32L * occupancy;
-    int best = 1;
-    long best_cost = -1;
-    for (int d = 1; d <= tiles_m; ++d) {
-        if (tiles_m % d) continue;
-        const long cost = (long)d * TM + ((together + d - 1) / d) * TN;
-        if (best_cost < 0 || cost < best_cost) best = d, best_cost = cost;
-    }
-    return best;
-}
 
 // WK = 2: the k-blocks of every stage are split between two sets of WAVES_M x WAVES_N wavefronts (the two
 // ping-pong groups) that work on the same output tile and add their accumulators through LDS at the end;
@@ -117,27 +58,23 @@ inline int strip_height(int tiles_m, int tiles_n, int TM, int TN, int occupancy)
 // instructions; measured on MI355X, the 16x16x64 form sustains ~20 % more operations per second on random operands
 // before the power limit lowers the shader clock.  A 32x32 block of the output is then four 16x16 quads
 // (channel half, token half) instead of four 8-channel strips.
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KBS, int STAGES, bool W4, int EPI, int OCC, bool PP, int WK, bool MI16>
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KBS, int STAGES, int EPI, int OCC, bool PP, int WK, bool MI16>
 __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_kernel(PrefillParams p)
 {
     constexpr int NW = WAVES_M * WAVES_N * WK;
-    static_assert(WK == 1 || (WK == 2 && PP && !W4 && WM % 2 == 0), "k-split: int8 ping-pong kernels only");
-    static_assert(!MI16 || (!W4 && PP && EPI != EPI_PART), "16x16x64: int8 ping-pong kernels, fused epilogues");
+    static_assert(WK == 1 || (WK == 2 && PP && WM % 2 == 0), "k-split: ping-pong kernels only");
+    static_assert(!MI16 || (PP && EPI != EPI_PART), "16x16x64: ping-pong kernels, fused epilogues");
     constexpr int TMB = WAVES_M * WM;                    // activation row-blocks per workgroup tile
     constexpr int TNB = WAVES_N * WN;                    // weight row-blocks per workgroup tile
     constexpr int XFR = TMB * KBS;                       // 1024-byte fragments per stage: activations
-    constexpr int WFR = W4 ? TNB * KBS / 2 : TNB * KBS;  //                               weights
-    constexpr int WKB = W4 ? KBS / 2 : KBS;              // weight fragments per row-block per stage
+    constexpr int WFR = TNB * KBS;                       //                               weights
     constexpr int XOFF = 0, WOFF = XFR * 1024;
     constexpr int STAGE_BYTES = (XFR + WFR) * 1024;
     // Fragment f of a stage is loaded by wavefront f % NW.  When the count does not divide evenly the first
     // FR % NW wavefronts issue one load more per stage than the others (LPW_HI / LPW_LO loads).
     constexpr int FR = XFR + WFR;
-    constexpr bool SCALE_DMA = W4;                       // group scales travel with the stage, through LDS
-    constexpr int LPW_HI = (FR + NW - 1) / NW + (SCALE_DMA ? 1 : 0);
-    constexpr int LPW_LO = FR / NW + (SCALE_DMA ? 1 : 0);
+    constexpr int LPW_HI = (FR + NW - 1) / NW, LPW_LO = FR / NW;
     constexpr int NHI = FR % NW;                         // wavefronts 0 .. NHI-1 issue LPW_HI loads
-    static_assert(!W4 || (KBS == 4 && PP), "W4A8: one stage is one scale group (128 k); ping-pong loop only");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     // behind the stage buffers: the tile's token scales, channel scales and bias as fp32, fetched once at
@@ -148,8 +85,6 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
     float *side_sx = reinterpret_cast<float *>(smem + STAGES * STAGE_BYTES);
     float *side_sw = side_sx + SXI * NW * 64;
     float *side_b = side_sw + SWI * NW * 64;
-    // int4 ping-pong: per stage and wavefront a 256-byte slot with the fp16 group scales of its WN*32 channels
-    char *scale_slots = reinterpret_cast<char *>(side_b + SWI * NW * 64);
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -167,7 +102,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
     short r_b[SWI];   // converted when it is written to LDS: a conversion here would wait for the load
     if (EPI == EPI_F16) {
         const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.sx, (unsigned)p.M * 4u);
-        const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.sw, (!W4 && p.sw) ? (unsigned)p.N * 4u : 0u);
+        const __amdgpu_buffer_rsrc_t rw = make_rsrc(p.sw, p.sw ? (unsigned)p.N * 4u : 0u);
         const __amdgpu_buffer_rsrc_t rb = make_rsrc(p.bias, p.bias ? (unsigned)p.N * 2u : 0u);
 #pragma unroll
         for (int it = 0; it < SXI; ++it)
@@ -184,7 +119,6 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
     // split-K: this workgroup multiplies stages [stage0, stage0 + nstages) only (never an empty range)
     const int stage0 = blockIdx.y * p.stages_per_split;
     const int nstages = min(p.stages_per_split, KB / KBS - stage0);
-    const unsigned s_bytes = W4 ? (unsigned)(p.K / 128) * p.Npad * 2u : 0u;
     const unsigned lane16 = lane * 16;
 
     // Fragment f of a stage lives at LDS offset f*1024 (activation fragments first) and, in global memory, at
@@ -208,20 +142,14 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, LDS_PTR(buf + f * 1024), 16, lane16 + off, 0, 0, 0);
             } else {
                 const int g = f - XFR;
-                const int nb = g / WKB, kb = g % WKB;
-                const unsigned off = ((unsigned)(tn * TNB + nb) * (KB / (W4 ? 2 : 1)) + (stage0 + s) * WKB + kb) * 1024u;
+                const int nb = g / KBS, kb = g % KBS;
+                const unsigned off = ((unsigned)(tn * TNB + nb) * KB + (stage0 + s) * KBS + kb) * 1024u;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, LDS_PTR(buf + f * 1024), 16, lane16 + off, 0, 0, 0);
             }
         };
 #pragma unroll
         for (int i = 0; i < FR / NW; ++i) load_fragment(i);
         if (NHI != 0 && wave < NHI) load_fragment(FR / NW);
-        if (SCALE_DMA) {   // stage s = scale group s: 4 bytes per lane, the first WN*16 lanes carry the wavefront's channels
-            const __amdgpu_buffer_rsrc_t sr = make_rsrc(p.wscales, live ? s_bytes : 0u);
-            const unsigned off = ((unsigned)(stage0 + s) * p.Npad + (tn * TNB + wn * WN) * 32) * 2u;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(sr, LDS_PTR(scale_slots + ((s % STAGES) * NW + wave) * 256), 4,
-                                                     lane * 4 + off, 0, 0, 0);
-        }
     };
 
     // wait until all but this wavefront's loads of the newest STAGES-2 stages have landed
@@ -259,21 +187,6 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
     auto ch_of = [&](int q) { return MI16 ? 16 * (q >> 1) + 4 * (lane >> 4) : 8 * q + 4 * (lane >> 5); };
     auto tok_of = [&](int q) { return MI16 ? 16 * (q & 1) + (lane & 15) : (lane & 31); };
 
-    // W4A8 only: fp32 accumulators over groups (EPI_F16) or integer totals (EPI_ACC)
-    float accf[W4 ? WN : 1][W4 ? WM : 1][16];
-    int tot[(W4 && EPI == EPI_ACC) ? WN : 1][(W4 && EPI == EPI_ACC) ? WM : 1][16];
-    if (W4) {
-#pragma unroll
-        for (int i = 0; i < WN; ++i)
-#pragma unroll
-            for (int j = 0; j < WM; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    accf[i][j][r] = 0.0f;
-                    if (EPI == EPI_ACC) tot[i][j][r] = 0;
-                }
-    }
-
     // prologue: STAGES-1 stages in flight
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s) issue_stage(s);
@@ -289,10 +202,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
         }
     }
 
-    const int n_lane0 = (tn * TNB + wn * WN) * 32 + 4 * (lane >> 5);   // + bi*32 + 8*q + (r%4)
-    const int m_lane0 = (tm * TMB + wm * WM) * 32 + (lane & 31);       // + bj*32
-
-    if constexpr (!W4 && PP) {
+    if constexpr (PP) {
         // Ping-pong.  The 8 wavefronts form two groups, one wavefront of each per SIMD (w and w + 4).  A
         // wavefront alternates between a memory phase (read the 2*(WN+WM) fragments of one 64-k stage from
         // LDS, issue its share of the global->LDS loads STAGES-1 stages ahead, wait for its loads of the
@@ -352,7 +262,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
         }
         if (!late) __builtin_amdgcn_s_barrier();
     }
-    if (!W4 && !PP) {
+    if (!PP) {
         // Rotated pipeline.  Fragments of the next k-block are read from LDS while the matrix
         // instructions of the current one run; the stage hand-over (wait for the next stage's loads,
         // barrier, refill of the buffer just freed, first fragment read of the next stage) sits in
@@ -400,103 +310,6 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
             // matrix instructions without a conservative wait at the loop header
             __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
         }
-    }
-    if constexpr (W4 && PP) {
-        // Ping-pong for int4 weights (same two phase-shifted groups as above; a stage is one scale group of
-        // 128 k).  Measured cost model of a gfx950 SIMD for this mix: cycles ~ 12 per matrix instruction + 4 per
-        // vector-ALU instruction + ~17 per LDS read, nearly additive whichever wavefront issues them, so what
-        // counts is the instruction count (176 vector ops per 16 matrix instructions: 128 fold, 48 unpack); an
-        // interleaved single-role loop with the same counts ran no faster than this split.  Memory phase: read the stage's fragments (nibbles stay packed), fold the PREVIOUS group's
-        // int32 partial into the fp32 sums (accf += float(acc) * scale -- as many vector-ALU cycles as the
-        // stage has matrix cycles, now running under the other group's matrix phase), issue loads, wait.
-        // Compute phase: shift/mask unpack + matrix instructions, the first of each block with C = 0.
-        static_assert(KBS == 4 && NW == 8, "ping-pong: one 128-k group per stage, 8 wavefronts");
-        const bool late = wave >= NW / 2;
-        v4i wp[KBS / 2][WN], xf[KBS][WM];
-        h4 sg[WN][4];
-#pragma unroll
-        for (int i = 0; i < WN; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) sg[i][q] = h4{0, 0, 0, 0};
-        auto fold_all = [&](int g) {                 // group g's partial (g < 0: nothing yet, acc = 0)
-#pragma unroll
-            for (int i = 0; i < WN; ++i)
-#pragma unroll
-                for (int j = 0; j < WM; ++j)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        if (EPI != EPI_ACC) {
-                            accf[i][j][r] = __builtin_fmaf((float)acc[i][j][r], (float)sg[i][r / 4][r % 4], accf[i][j][r]);
-                        } else {
-                            tot[i][j][r] += acc[i][j][r];
-                            if (p.partials && g >= 0) {
-                                const int m = m_lane0 + j * 32, n = n_lane0 + i * 32 + 8 * (r / 4) + (r % 4);
-                                if (m >= p.row0 && m < p.row0 + p.nrows && m < p.M && n < p.N)
-                                    p.partials[((size_t)(m - p.row0) * nstages + g) * p.N + n] = acc[i][j][r] >> 4;
-                            }
-                        }
-                    }
-        };
-        const v16i zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-        wait_stage();        // stage 0 has landed (this wavefront's part)
-        __builtin_amdgcn_s_barrier();            // ... everyone's
-        if (late) __builtin_amdgcn_s_barrier();  // phase shift
-        for (int it = 0; it < nstages; ++it) {
-            // ---- memory phase
-            const char *buf = smem + (it % STAGES) * STAGE_BYTES;
-            if (it > 0) {   // scales of the group whose partial sits in acc (their slot is refilled below)
-                const char *slot = scale_slots + (((it - 1) % STAGES) * NW + wave) * 256;
-#pragma unroll
-                for (int i = 0; i < WN; ++i)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        sg[i][q] = *reinterpret_cast<const h4 *>(slot + (i * 32 + 8 * q + 4 * (lane >> 5)) * 2);
-            }
-#pragma unroll
-            for (int kp = 0; kp < KBS / 2; ++kp)
-#pragma unroll
-                for (int i = 0; i < WN; ++i)
-                    wp[kp][i] = *reinterpret_cast<const v4i *>(buf + WOFF + ((wn * WN + i) * WKB + kp) * 1024 + lane * 16);
-#pragma unroll
-            for (int kb = 0; kb < KBS; ++kb)
-#pragma unroll
-                for (int j = 0; j < WM; ++j)
-                    xf[kb][j] = *reinterpret_cast<const v4i *>(buf + XOFF + ((wm * WM + j) * KBS + kb) * 1024 + lane * 16);
-            issue_stage(it + STAGES - 1);        // into the buffer of stage it-1: both groups are done with it
-            fold_all(it - 1);
-            __builtin_amdgcn_sched_barrier(0);   // the fold stays in front of the wait: it covers the loads' latency
-            wait_stage();    // own loads of stage it+1 have landed
-            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): fragments are in registers, the buffer may be reused
-            __builtin_amdgcn_s_barrier();
-            // ---- compute phase
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int kb = 0; kb < KBS; ++kb)
-#pragma unroll
-                for (int i = 0; i < WN; ++i) {
-                    const unsigned w0 = (unsigned)wp[kb / 2][i][2 * (kb % 2)], w1 = (unsigned)wp[kb / 2][i][2 * (kb % 2) + 1];
-                    v4i wf;
-                    wf[0] = (int)((w0 << 4) & 0xF0F0F0F0u);
-                    wf[1] = (int)(w0 & 0xF0F0F0F0u);
-                    wf[2] = (int)((w1 << 4) & 0xF0F0F0F0u);
-                    wf[3] = (int)(w1 & 0xF0F0F0F0u);
-#pragma unroll
-                    for (int j = 0; j < WM; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf, xf[kb][j], kb == 0 ? zero16 : acc[i][j], 0, 0, 0);
-                }
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_barrier();
-        }
-        if (!late) __builtin_amdgcn_s_barrier();
-        {
-            const char *slot = scale_slots + (((nstages - 1) % STAGES) * NW + wave) * 256;
-#pragma unroll
-            for (int i = 0; i < WN; ++i)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    sg[i][q] = *reinterpret_cast<const h4 *>(slot + (i * 32 + 8 * q + 4 * (lane >> 5)) * 2);
-        }
-        fold_all(nstages - 1);
     }
     wait_vmcnt<0>();   // drain the dead tail loads before the LDS is released
 
@@ -555,7 +368,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
                     v4i v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        v[e] = W4 ? __float_as_int(accf[i][j][4 * q + e]) : acc[i][j][4 * q + e];
+                        v[e] = acc[i][j][4 * q + e];
                     *reinterpret_cast<v4i *>(dst + ((i * WM + j) * 4 + q) * 1024 + lane * 16) = v;
                 }
         return;
@@ -573,8 +386,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
                     for (int e = 0; e < 4; ++e) {
                         const int n = (tn * TNB + wn * WN + i) * 32 + ch_of(q) + e;
                         if (m < p.M && n < p.N) {
-                            if constexpr (W4) p.acc[(size_t)m * p.ldacc + n] = tot[i][j][4 * q + e] >> 4;
-                            else p.acc[(size_t)m * p.ldacc + n] = acc_get(i, j, q, e);
+                            p.acc[(size_t)m * p.ldacc + n] = acc_get(i, j, q, e);
                         }
                     }
                 }
@@ -620,19 +432,6 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
             for (int i = 0; i < WN; ++i) read_channel_operands(i, i);
         }
     }
-    // int4 kernel (32x32x32 accumulators: one token per token block, four channel quads per channel block; no channel
-    // scales): the same, token scales and bias only
-    float sx4_r[W4 ? WM : 1];
-    float4 b4_r[W4 ? WN : 1][4];
-    if constexpr (W4) {
-#pragma unroll
-        for (int j = 0; j < WM; ++j) sx4_r[j] = side_sx[(wm * WM + j) * 32 + (lane & 31)] * 0.0625f;
-#pragma unroll
-        for (int i = 0; i < WN; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                b4_r[i][q] = *reinterpret_cast<const float4 *>(side_b + (wn * WN + i) * 32 + 8 * q + 4 * (lane >> 5));
-    }
 #pragma unroll
     for (int j = 0; j < WM; ++j) {
         if (!my_block(j)) continue;                        // wave-uniform
@@ -645,11 +444,9 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
                 float4 swq, bq;
                 if constexpr (MI16) {
                     sxm = sx_r[j][q & 1], swq = sw_r[ALL_CH ? i : 0][q >> 1], bq = b_r[ALL_CH ? i : 0][q >> 1];
-                } else if constexpr (W4) {
-                    sxm = sx4_r[j], swq = float4{0.0f, 0.0f, 0.0f, 0.0f}, bq = b4_r[i][q];
                 } else {
                     const int nl = (wn * WN + i) * 32 + ch_of(q);   // channel inside the tile
-                    sxm = side_sx[(wm * WM + j) * 32 + tok_of(q)] * (W4 ? 0.0625f : 1.0f);
+                    sxm = side_sx[(wm * WM + j) * 32 + tok_of(q)];
                     swq = *reinterpret_cast<const float4 *>(side_sw + nl);
                     bq = *reinterpret_cast<const float4 *>(side_b + nl);
                 }
@@ -657,9 +454,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
                 h4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    float v;
-                    if constexpr (W4) v = __builtin_fmaf(accf[i][j][4 * q + e], sxm, b4[e]);
-                    else v = __builtin_fmaf((float)acc_get(i, j, q, e) * sxm, sw4[e], b4[e]);
+                    float v = __builtin_fmaf((float)acc_get(i, j, q, e) * sxm, sw4[e], b4[e]);
                     // the sum is rounded to fp32, then to fp16, in every kernel variant: left alone, the compiler fuses
                     // some of these pairs into one instruction with a single rounding, and which ones differs from
                     // kernel to kernel (results one fp16 ulp apart between tile shapes)
@@ -695,8 +490,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *WK * 64, OCC) void gemm_prefill_k
     }
 }
 
-// Split-K, second kernel: adds the partial sums of the splits in a fixed order (int32: exact; int4 path: fp32,
-// split 0 first), then the same dequantization as the fused epilogue.  One lane per 4 consecutive channels of
+// Split-K, second kernel: adds the partial sums of the splits (int32: exact), then the same dequantization as the fused epilogue.  One lane per 4 consecutive channels of
 // one token, in the order the first kernel stored them (32-bit index arithmetic only: this kernel is short).
 struct FinishParams {
     const void *part;
@@ -705,13 +499,13 @@ struct FinishParams {
     const __half *bias;
     __half *y;
     int64_t ldy;
-    int32_t *acc;            // test hook (int8 weights): raw sums instead of y
+    int32_t *acc;            // test hook: raw sums instead of y
     int64_t ldacc;
     int M, N;
     int tiles_m, tiles_n, group_m, splits;
 };
 
-template <int WAVES_M, int WAVES_N, int WM, int WN, bool W4>
+template <int WAVES_M, int WAVES_N, int WM, int WN>
 __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams f)
 {
     // one workgroup per (tile, wavefront of the first kernel): its 4 wavefronts take the 4 quads of every block.
@@ -726,11 +520,10 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams f)
     const size_t split_stride = (size_t)ntiles * NW * BLOCKS * 4096;
     const char *src0 = static_cast<const char *>(f.part) + (size_t)blockIdx.x * BLOCKS * 4096 + q * 1024 + lane * 16;
     int si[BLOCKS][4];
-    float sf[BLOCKS][4];
 #pragma unroll
     for (int b = 0; b < BLOCKS; ++b)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) si[b][e] = 0, sf[b][e] = 0.0f;
+        for (int e = 0; e < 4; ++e) si[b][e] = 0;
     for (int s = 0; s < f.splits; ++s) {
         v4i v[BLOCKS];
 #pragma unroll
@@ -738,10 +531,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams f)
 #pragma unroll
         for (int b = 0; b < BLOCKS; ++b)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (W4) sf[b][e] += __int_as_float(v[b][e]);
-                else si[b][e] += v[b][e];
-            }
+            for (int e = 0; e < 4; ++e) si[b][e] += v[b][e];
     }
 #pragma unroll
     for (int i = 0; i < WN; ++i) {
@@ -751,7 +541,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams f)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int n = n0 + e < f.N ? n0 + e : n0;
-            sw4[e] = (!W4 && f.sw) ? f.sw[n] : 0.0f;
+            sw4[e] = f.sw ? f.sw[n] : 0.0f;
             b4[e] = f.bias ? __half2float(f.bias[n]) : 0.0f;
         }
 #pragma unroll
@@ -763,11 +553,11 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams f)
                 for (int e = 0; e < 4 && n0 + e < f.N; ++e) f.acc[(size_t)m * f.ldacc + n0 + e] = si[b][e];
                 continue;
             }
-            const float sxm = f.sx[m] * (W4 ? 0.0625f : 1.0f);
+            const float sxm = f.sx[m];
             h4 o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float v = W4 ? __builtin_fmaf(sf[b][e], sxm, b4[e]) : __builtin_fmaf((float)si[b][e] * sxm, sw4[e], b4[e]);
+                float v = __builtin_fmaf((float)si[b][e] * sxm, sw4[e], b4[e]);
                 asm("" : "+v"(v));   // rounded to fp32, then to fp16, as in the fused epilogue
                 o[e] = (_Float16)v;
             }
@@ -781,20 +571,19 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(FinishParams f)
     }
 }
 
-template <int WAVES_M, int WAVES_N, int WM, int WN, int KBS, int STAGES, bool W4, int EPI, int OCC = 1, bool PP = false,
+template <int WAVES_M, int WAVES_N, int WM, int WN, int KBS, int STAGES, int EPI, int OCC = 1, bool PP = false,
           int WK = 1, bool MI16 = false>
 int launch_one(const GemmArgs &a, hipStream_t st, int splits = 1)
 {
     constexpr int TM = WAVES_M * WM * 32, TN = WAVES_N * WN * 32;
     constexpr int XFR = WAVES_M * WM * KBS;
-    constexpr int WFR = W4 ? WAVES_N * WN * KBS / 2 : WAVES_N * WN * KBS;
+    constexpr int WFR = WAVES_N * WN * KBS;
     constexpr int THREADS = WAVES_M * WAVES_N * WK * 64;
     constexpr int LDS = (XFR + WFR) * 1024 * STAGES +
-                        ((TM + THREADS - 1) / THREADS + 2 * ((TN + THREADS - 1) / THREADS)) * THREADS * 4 +   // + epilogue side area (padded per thread)
-                        (W4 ? STAGES * WAVES_M * WAVES_N * WK * 256 : 0);  // + int4 group-scale slots
+                        ((TM + THREADS - 1) / THREADS + 2 * ((TN + THREADS - 1) / THREADS)) * THREADS * 4;   // + epilogue side area (padded per thread)
     static_assert(LDS <= 160 * 1024, "LDS budget");
     static_assert((STAGES - 2) * ((XFR + WFR) / (WAVES_M * WAVES_N * WK) + 1) <= 63, "vmcnt range");
-    auto kern = gemm_prefill_kernel<WAVES_M, WAVES_N, WM, WN, KBS, STAGES, W4, EPI, OCC, PP, WK, MI16>;
+    auto kern = gemm_prefill_kernel<WAVES_M, WAVES_N, WM, WN, KBS, STAGES, EPI, OCC, PP, WK, MI16>;
     // once per kernel and process; the initialisation of a function-local static is thread-safe
     static const hipError_t attr_status = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                               hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
@@ -809,20 +598,14 @@ int launch_one(const GemmArgs &a, hipStream_t st, int splits = 1)
     p.ldy = a.ldy;
     p.acc = a.acc;
     p.ldacc = a.ldacc ? a.ldacc : a.N;
-    p.partials = a.partials;
-    p.row0 = a.row0;
-    p.nrows = a.nrows;
     p.M = a.M;
     p.N = a.N;
     p.K = a.K;
-    p.Npad = round_up(a.N, TILE_ROWS);
     p.tiles_m = ceil_div(a.M, TM);
     p.tiles_n = ceil_div(a.N, TN);
     p.group_m = strip_height(p.tiles_m, p.tiles_n, TM, TN, OCC);
     p.x_bytes = (unsigned)act_kernel_bytes(a.M, a.K);
-    p.w_bytes = (unsigned)(W4 ? w4_codes_bytes(a.N, a.K) : w8_kernel_bytes(a.N, a.K));
-    p.wscales = W4 ? reinterpret_cast<const __half *>(static_cast<const char *>(a.wq) + w4_scales_offset(a.N, a.K))
-                   : nullptr;
+    p.w_bytes = (unsigned)w8_kernel_bytes(a.N, a.K);
     const int grid = p.tiles_m * p.tiles_n;
     const int nstages = a.K / (32 * KBS);
     p.stages_per_split = ceil_div(nstages, splits);
@@ -846,7 +629,7 @@ int launch_one(const GemmArgs &a, hipStream_t st, int splits = 1)
     f.tiles_n = p.tiles_n;
     f.group_m = p.group_m;
     f.splits = splits;
-    hipLaunchKernelGGL((splitk_finish_kernel<WAVES_M, WAVES_N, WM, WN, W4>), dim3(grid * WAVES_M * WAVES_N), dim3(256), 0, st,
+    hipLaunchKernelGGL((splitk_finish_kernel<WAVES_M, WAVES_N, WM, WN>), dim3(grid * WAVES_M * WAVES_N), dim3(256), 0, st,
                        f);
     return check_hip(hipGetLastError(), "splitk_finish launch");
 }
@@ -885,16 +668,6 @@ struct Choice {
     int variant, splits;
     double us;
 };
-
-// W4A8 has one tile shape: 128 tokens x 256 channels (equal bytes of both operands per stage), 8 wavefronts of
-// 64x64 in two ping-pong groups, 4 stages of one 128-k scale group each; K is split when the tiles are few.
-inline Choice choose_w4(const GemmArgs &a, size_t scratch, bool dump_partials)
-{
-    const long tiles = (long)ceil_div(a.M, 128) * ceil_div(a.N, 256);
-    const SplitModel model = {7.0, 7.0, 0.0, 4.0, true};
-    const SplitPlan plan = plan_split(tiles, 128, 256, a.K, 128, model, tiles < 192 && !dump_partials ? scratch : 0);
-    return {0, plan.splits, plan.us};
-}
 
 // W8A8.  Estimated time of a tile configuration:
 //   2.4 us launch + fp16 output at 6.9 TB/s + passes x (o + tile operations / r),
@@ -1019,31 +792,19 @@ inline GemmArgs column_range(const GemmArgs &a, int n0, int n)
 }
 
 // variant 0 = automatic choice; other values pick one of the configurations below (tests and tuning)
-template <bool W4, int EPI>
+template <int EPI>
 int dispatch(const GemmArgs &a, int variant, hipStream_t st)
 {
     // split-K scratch: whatever the caller's workspace offers behind the quantized activations
     const size_t scratch = a.ws ? a.ws_bytes : 0;
     const bool dump_partials = a.partials != nullptr;
-    if (W4) {
-        int splits = 1;
-        if (variant >= 202 && variant <= 232) splits = variant - 200;
-        else if (variant == 0 || variant == 2) splits = choose_w4(a, scratch, dump_partials).splits;
-        if (splits > 1 && EPI == EPI_F16 && !dump_partials) {
-            const long tiles = (long)ceil_div(a.M, 128) * ceil_div(a.N, 256);
-            if ((size_t)splits * tiles * 128 * 256 * 4 > scratch)
-                return fail(QL_ERR_WORKSPACE, "split-K needs %zu bytes of workspace", (size_t)splits * tiles * 128 * 256 * 4);
-            return launch_one<2, 4, 2, 2, 4, 4, true, EPI_PART, 1, true>(a, st, splits);
-        }
-        return launch_one<2, 4, 2, 2, 4, 4, true, EPI, 1, true>(a, st);
-    }
     int splits = 1;
     if (variant == 0 || variant == 2) {   // 2: the automatic choice without the channel split
         const ColumnSplit cs = variant == 0 ? choose_w8_columns(a, scratch, dump_partials)
                                             : ColumnSplit{a.N, choose_w8(a, scratch, dump_partials), {0, 1, 0.0}, 0.0};
         if (cs.n1 < a.N) {
-            QL_TRY((dispatch<false, EPI>(column_range(a, 0, cs.n1), cs.first.variant, st)));
-            return dispatch<false, EPI>(column_range(a, cs.n1, a.N - cs.n1), cs.rest.variant, st);
+            QL_TRY((dispatch<EPI>(column_range(a, 0, cs.n1), cs.first.variant, st)));
+            return dispatch<EPI>(column_range(a, cs.n1, a.N - cs.n1), cs.rest.variant, st);
         }
         variant = cs.first.variant, splits = cs.first.splits;
     } else if (variant >= 202 && variant <= 232) {
@@ -1055,37 +816,37 @@ int dispatch(const GemmArgs &a, int variant, hipStream_t st)
         const int T = variant == 200 ? 128 : 256;
         const size_t need = (size_t)splits * ceil_div(a.M, T) * ceil_div(a.N, T) * T * T * 4;
         if (need > scratch) return fail(QL_ERR_WORKSPACE, "split-K needs %zu bytes of workspace", need);
-        if (variant == 200) return launch_one<4, 2, 1, 2, 2, 4, false, EPI_PART>(a, st, splits);
-        return launch_one<2, 4, 4, 2, 2, 4, false, EPI_PART, 1, true>(a, st, splits);
+        if (variant == 200) return launch_one<4, 2, 1, 2, 2, 4, EPI_PART>(a, st, splits);
+        return launch_one<2, 4, 4, 2, 2, 4, EPI_PART, 1, true>(a, st, splits);
     }
     if (variant == 19 && a.K % 128) variant = 13;   // 128-k stages need K % 128 == 0
     if (variant == 39 && a.K % 128) variant = 13;
     switch (variant) {
     // 26, 43, 35, 37, 39: the configurations 6, 23, 15, 17, 19 on the 16x16x64 matrix instruction
-    case 26: return launch_one<2, 4, 4, 2, 2, 4, false, EPI, 1, true, 1, true>(a, st);
-    case 43: return launch_one<2, 4, 4, 3, 2, 3, false, EPI, 1, true, 1, true>(a, st);
-    case 35: return launch_one<4, 2, 2, 3, 2, 4, false, EPI, 1, true, 1, true>(a, st);
-    case 37: return launch_one<2, 4, 2, 2, 2, 3, false, EPI, 2, true, 1, true>(a, st);
-    case 39: return launch_one<2, 2, 2, 2, 4, 4, false, EPI, 1, true, 2, true>(a, st);
+    case 26: return launch_one<2, 4, 4, 2, 2, 4, EPI, 1, true, 1, true>(a, st);
+    case 43: return launch_one<2, 4, 4, 3, 2, 3, EPI, 1, true, 1, true>(a, st);
+    case 35: return launch_one<4, 2, 2, 3, 2, 4, EPI, 1, true, 1, true>(a, st);
+    case 37: return launch_one<2, 4, 2, 2, 2, 3, EPI, 2, true, 1, true>(a, st);
+    case 39: return launch_one<2, 2, 2, 2, 4, 4, EPI, 1, true, 2, true>(a, st);
     case 6:   // 256x256, 8 wavefronts of 128 tokens x 64 channels in two ping-pong groups (one computes while the other fetches), 64-k stages
-        return launch_one<2, 4, 4, 2, 2, 4, false, EPI, 1, true>(a, st);
+        return launch_one<2, 4, 4, 2, 2, 4, EPI, 1, true>(a, st);
     case 23:  // 256 tokens x 384 channels, 8 wavefronts of 128x96 in two ping-pong groups, 3 stages
-        return launch_one<2, 4, 4, 3, 2, 3, false, EPI, 1, true>(a, st);
+        return launch_one<2, 4, 4, 3, 2, 3, EPI, 1, true>(a, st);
     case 15:  // 256 tokens x 192 channels, 8 wavefronts of 64x96 in two ping-pong groups
-        return launch_one<4, 2, 2, 3, 2, 4, false, EPI, 1, true>(a, st);
+        return launch_one<4, 2, 2, 3, 2, 4, EPI, 1, true>(a, st);
     case 17:  // 128 tokens x 256 channels, 8 wavefronts of 64x64, ping-pong, 3 stages: two workgroups per CU
-        return launch_one<2, 4, 2, 2, 2, 3, false, EPI, 2, true>(a, st);
+        return launch_one<2, 4, 2, 2, 2, 3, EPI, 2, true>(a, st);
     case 19:  // 128x128, two ping-pong groups of 4 wavefronts (64x64 each) that split the k-blocks of every 128-k stage;
               // 4 stages (96 KB in flight per workgroup: 3-5 % faster than 3 when the weights come from HBM)
-        return launch_one<2, 2, 2, 2, 4, 4, false, EPI, 1, true, 2>(a, st);
+        return launch_one<2, 2, 2, 2, 4, 4, EPI, 1, true, 2>(a, st);
     case 13:  // 128x128, 8 wavefronts of 32 tokens x 64 channels (two per SIMD with one workgroup per CU), rotated single-phase loop
-        return launch_one<4, 2, 1, 2, 2, 4, false, EPI>(a, st);
+        return launch_one<4, 2, 1, 2, 2, 4, EPI>(a, st);
     case 4:   // 128x128, 4 wavefronts of 64x64 (two workgroups per CU)
-        return launch_one<2, 2, 2, 2, 2, 4, false, EPI>(a, st);
+        return launch_one<2, 2, 2, 2, 2, 4, EPI>(a, st);
     case 11:  // 128x128, 4 wavefronts of 64x64, 3 stages of 64 k: three workgroups per CU
-        return launch_one<2, 2, 2, 2, 2, 3, false, EPI, 3>(a, st);
+        return launch_one<2, 2, 2, 2, 2, 3, EPI, 3>(a, st);
     case 20:  // 64 tokens x 64 channels, 4 wavefronts of 32x32, up to four workgroups per CU: few-token shapes
-        return launch_one<2, 2, 1, 1, 2, 4, false, EPI, 4>(a, st);
+        return launch_one<2, 2, 1, 1, 2, 4, EPI, 4>(a, st);
     default:
         return fail(QL_ERR_UNSUPPORTED, "unknown prefill kernel variant %d", variant);
     }
@@ -1096,9 +857,7 @@ int dispatch(const GemmArgs &a, int variant, hipStream_t st)
 double prefill_estimate_us(const GemmArgs &a)
 {
     const size_t scratch = a.ws ? a.ws_bytes : 0;
-    // int4: the plan's times are ~15 % above the measured ones with the weights coming from HBM (16 layer shapes x 9
-    // token counts); they only rank split counts there, here they meet another kernel's estimate
-    return a.bits == 4 ? 0.85 * choose_w4(a, scratch, a.partials != nullptr).us : choose_w8_columns(a, scratch, a.partials != nullptr).us;
+    return a.bits == 4 ? prefill_w4_estimate_us(a) : choose_w8_columns(a, scratch, a.partials != nullptr).us;
 }
 
 void prefill_plan(const GemmArgs &a, int *variant, int *tile_tokens, int *tile_channels, int *splits, int *rest_channels,
@@ -1107,9 +866,7 @@ void prefill_plan(const GemmArgs &a, int *variant, int *tile_tokens, int *tile_c
     const size_t scratch = a.ws ? a.ws_bytes : 0;
     *rest_channels = 0, *rest_variant = 0;
     if (a.bits == 4) {
-        *splits = choose_w4(a, scratch, a.partials != nullptr).splits;
-        *variant = *splits > 1 ? 200 + *splits : 0;
-        *tile_tokens = 128, *tile_channels = 256;
+        prefill_w4_plan(a, variant, tile_tokens, tile_channels, splits);
         return;
     }
     const ColumnSplit cs = choose_w8_columns(a, scratch, a.partials != nullptr);
@@ -1134,10 +891,8 @@ void prefill_plan(const GemmArgs &a, int *variant, int *tile_tokens, int *tile_c
 int launch_gemm_prefill(const GemmArgs &a, int variant, hipStream_t st)
 {
     if (a.M == 0) return QL_OK;
-    const bool w4 = a.bits == 4;
-    const bool dump = a.acc != nullptr;
-    if (w4) return dump ? dispatch<true, EPI_ACC>(a, variant, st) : dispatch<true, EPI_F16>(a, variant, st);
-    return dump ? dispatch<false, EPI_ACC>(a, variant, st) : dispatch<false, EPI_F16>(a, variant, st);
+    if (a.bits == 4) return launch_gemm_prefill_w4(a, variant, st);
+    return a.acc ? dispatch<EPI_ACC>(a, variant, st) : dispatch<EPI_F16>(a, variant, st);
 }
 
 }  // namespace ql

@@ -1,0 +1,59 @@
+"""The int4 prefill kernel's tile shapes (256x256, 192x256, 128x256, 128x128, 256x256 with 128x256 tiles for the last
+channels, split-K) at edges of tiles and stages: against the oracle, and bit for bit against each other where K is not
+split (every shape folds the groups in the same order)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2512_23367_amd import binding as ql
+from paper_2512_23367_amd import synth
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-3      # the parity bar: max|y - ref| / max|ref|; the fp16 rounding alone is up to 4.9e-4
+UNSPLIT = [26, 35, 37, 13, 43]
+
+
+@pytest.fixture(scope="module")
+def G():
+    import gpu_util
+    return gpu_util
+
+
+# tokens: one, around 16 / 32 / 192 / 256; channels: around 32 / 256 / 768 (43: two regions); K: 1, 2, 3, 4 and more stages
+@pytest.mark.parametrize("M,K,N", [(1, 128, 32), (33, 256, 31), (191, 384, 257), (193, 512, 600), (257, 640, 769), (300, 1152, 1000),
+                                   (513, 128, 520), (64, 4096, 264)])
+@pytest.mark.parametrize("bias", [False, True])
+def test_shapes_agree_with_the_oracle(G, M, K, N, bias):
+    x, w = synth.activations(M, K, 0, "single"), synth.weights(N, K, 0, "single")
+    b = synth.bias(N, 0, "single") if bias else None
+    g = G.gpu_quant_weight(w, 4, 128)
+    ref = oracle.linear_w4a8(x, g["canon"], g["scales"], 128, b)["y64"]
+    outs = {}
+    try:
+        for v in UNSPLIT + [0, 2, 202, 203]:
+            if v in (202, 203) and K < 1024:
+                continue                                   # (at least one stage per split)
+            ql.ql_set_kernel_variant(v)
+            outs[v] = G.gpu_linear(x, g, b, extra_ws=64 << 20)
+    finally:
+        ql.ql_set_kernel_variant(0)
+    for v, y in outs.items():
+        assert G.norm_err(y, ref) <= TOL, v
+        if v in UNSPLIT:
+            assert (y.view(np.uint16) == outs[26].view(np.uint16)).all(), v
+
+
+def test_the_choice_covers_the_shapes():
+    """Host only in effect (no launch): each form is the automatic choice somewhere, and the two-region form needs no
+    second launch."""
+    def variant(M, N, K):
+        p = ql.ql_plan_gemm(M, N, K, 4, 128, 64 << 20)
+        assert p.rest_channels == 0
+        return p.variant
+
+    assert variant(4096, 12288, 4096) == 26       # three whole passes of 256x256
+    assert variant(3001, 4096, 4096) == 35        # 256 tiles of 192x256: one pass
+    assert variant(2048, 4096, 4096) == 37        # 256 tiles of 128x256
+    assert variant(1100, 3584, 4096) == 13        # 252 tiles of 128x128, one per CU
+    assert variant(4096, 22016, 4096) == 43       # five passes of 256x256, the last 1536 channels in 128x256
+    assert 202 <= variant(200, 4096, 16384) <= 232 or variant(200, 4096, 16384) > 100
