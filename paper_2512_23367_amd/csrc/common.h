@@ -138,6 +138,6 @@ double decode_estimate_us(const GemmArgs &a);
 void prefill_plan(const GemmArgs &a, int *variant, int *tile_tokens, int *tile_channels, int *splits, int *rest_channels,
                   int *rest_variant);
 void decode_plan(const GemmArgs &a, int *token_block, int *channel_groups);
-bool decode_fuses_quant(int M, int K, int variant);
+bool decode_fuses_quant(int M, int N, int K, int bits, int variant);
 
 }  // namespace ql

@@ -8,8 +8,8 @@
 //     per wavefront, straight into the 16x16x64 int8 matrix instruction (int4: after a shift/mask
 //     unpack); nothing is reused, so nothing is staged in LDS;
 //   * the quantized tokens (of the workgroup's block) are re-read from L2 in the same tile order, or staged in LDS when
-//     they are few; for up to four tokens the linear-layer entry points skip the separate quantization
-//     kernel and every workgroup quantizes the fp16 tokens itself on the way into LDS (paper Eq. 1-2,
+//     they are few; for few tokens (up to 16, see fused_slots) the linear-layer entry points skip the separate
+//     quantization kernel and every workgroup quantizes the fp16 tokens itself on the way into LDS (paper Eq. 1-2,
 //     same arithmetic as the stand-alone quantizer), while its first weight fragments are in flight.
 #include "common.h"
 #include "quant_math.h"
@@ -57,12 +57,8 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *p, unsigned bytes
 // XL: the (few) quantized tokens are staged once per workgroup in LDS, [k-tile half][token] with one extra
 // all-zero token row that the lanes of absent tokens read; the ring then holds weights only.
 // FQ > 0: the tokens arrive as fp16 and are quantized here (XL staging with the quantizer in front of it); a lane
-// keeps FQ (= 2) pieces of 16 k in registers.
-// Measured: up to 4 tokens and K <= 4096 (8192 for two, 12288 for one) the fused form wins 0.7-2.4 us per
-// linear; at 8 tokens, or with twice the pieces per lane, every workgroup re-quantizing all tokens costs more
-// than the separate launch.
-constexpr int FQ_MAX_M = 4;
-constexpr size_t FQ_MAX_LDS = 24576;   // staged tokens (M + 1) * K bytes: four workgroups per CU still fit
+// keeps FQ (2 or 4) pieces of 16 k in registers.  Which calls take it: fused_slots.
+constexpr int FQ_MAX_M = 16;
 // OVL (fused quantizer only): the first ring of weights is loaded without conditions, see the int8 loop.
 template <bool W4, int MH, int C, int EPI, int WAVES, bool XL, int FQ, bool OVL>
 __global__ __launch_bounds__(WAVES * 64) void gemm_decode_kernel(DecodeParams p)
@@ -193,7 +189,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_kernel(DecodeParams p)
     // that FQ slots cover the wavefront's pieces.
     constexpr int FQ_SLOTS = FQ > 0 ? FQ : 1;
     Half16 keep[FQ_SLOTS];
-    const int fq_lg = p.M <= 1 ? 0 : p.M <= 2 ? 1 : 2;   // log2(Mp)
+    const int fq_lg = p.M <= 1 ? 0 : p.M <= 2 ? 1 : p.M <= 4 ? 2 : p.M <= 8 ? 3 : 4;   // log2(Mp)
     const int fq_m = lane & ((1 << fq_lg) - 1);        // this lane's token (absent when >= M)
     const int fq_ppr = 64 >> fq_lg;                     // pieces per slot
     auto load_tokens = [&](int th0, int th1) {
@@ -705,7 +701,9 @@ inline void auto_shape(int M, int N, int K, bool w4, int force_block, int &block
             if (w4 && (size_t)cand * (K / 128) * 32 > 16384) break;      // int4: staged scales
             const int wgs = ceil_div(groups, cand);
             const double rounds = wgs <= 512 ? (double)ceil_div(wgs, 256) : wgs / 256.0 + 1.0;
-            const double cost = rounds * (cand + tokens);
+            // (int8 and long rows: four groups leave the register ring two fragments deep and one workgroup per CU pulls too
+            // few bytes at a time -- 4096 x 14336, one token: 12.3 us with two groups per workgroup, 15.7 with four)
+            const double cost = rounds * (cand + tokens) * (!w4 && cand == 4 && K >= 4096 ? 1.12 : 1.0);
             if (cost < best * 0.999) best = cost, c = cand;
         }
     } else if (M <= 32) {
@@ -721,6 +719,33 @@ inline void auto_shape(int M, int N, int K, bool w4, int force_block, int &block
     }
 }
 
+constexpr size_t XL_MAX_LDS = 24576;   // staged tokens (M + 1) * K bytes: four workgroups per CU still fit
+
+inline bool sixteen_wavefronts(int N, int c) { return c == 1 && round_up(N, TILE_ROWS) / 16 <= 256; }
+
+inline int fused_pieces(int M, int K, int waves)   // pieces of 16 k x (rounded) tokens that a wavefront holds
+{
+    const int mp = M <= 1 ? 1 : M <= 2 ? 2 : M <= 4 ? 4 : M <= 8 ? 8 : 16;
+    return ceil_div(ceil_div(K, 128), waves) * 8 * mp;
+}
+
+// Fused quantizer: pieces of 16 k a lane keeps (2 or 4), 0 = the quantizer is a launch of its own.  A wavefront (of 8) keeps
+// its k-range in registers: 64 lanes x slots pieces, tokens rounded up to a power of two (int4 splits whole 128-k groups,
+// int8 64-k chunks: bound both); the codes of all tokens are staged in LDS.  Every workgroup quantizes all tokens, while
+// its first weights are on their way, with the channel groups per workgroup that the decode kernels take anyway (a rule
+// of its own for int8, at most two groups, was 20 % slower on small layers).  Measured against the separate launch (us,
+// weights from HBM; int8 / int4; K x N): one token of 4096 x 4096 5.6 / 4.7 against 8.0 / 7.3; with four pieces 8 tokens of
+// 4096 x 12288 12.1 / 9.7 against 12.8 / 10.3, of 1536 x 4608 5.1 / 4.8 against 6.0 / 6.8, of 4096 x 4096 7.8 / 7.5 against
+// 8.2 / 7.5, 5 tokens of 4096 x 22016 17.6 / 12.6 against 19.3 / 14.3 (8 tokens: equal).
+inline int fused_slots(int M, int K)
+{
+    if (M < 1 || M > FQ_MAX_M) return 0;
+    const int pieces = fused_pieces(M, K, 8);
+    const size_t lds = (size_t)(M + 1) * K;
+    if (pieces <= 128 && lds <= XL_MAX_LDS) return 2;
+    return pieces <= 256 && lds <= 40960 ? 4 : 0;
+}
+
 template <bool W4, int EPI>
 int by_m(const GemmArgs &a, int variant, hipStream_t st)
 {
@@ -733,36 +758,33 @@ int by_m(const GemmArgs &a, int variant, hipStream_t st)
     if (variant == 104 && (!W4 || (size_t)4 * (a.K / 128) * 32 <= 16384)) c = 4;
     if ((variant == 106 || variant == 108) && !W4 && a.M > 32 && block == 64) c = variant - 100;
     // 16 wavefronts (K split 16 ways) when there is at most one workgroup per CU: twice the bytes in flight
-    const bool wide = c == 1 && (groups <= 256 || variant == 111) && variant != 101 && a.M <= 32;
+    const bool wide = c == 1 && (sixteen_wavefronts(a.N, c) || variant == 111) && variant != 101 && a.M <= 32;
     // few tokens can be staged in LDS (ring slots then hold weights only).  Measured: it pays for int4 weights
     // with 8 wavefronts (gate+up at up to 5 tokens 13.5 -> 11.4 us: the short int4 ring no longer shares its
     // registers with token fragments), makes no difference for int8 weights, and costs 0.7-1.1 us with 16
     // wavefronts -- so it is used there, and as the vehicle of the fused quantization below.
-    const bool fits = (size_t)(a.M + 1) * a.K <= FQ_MAX_LDS && a.M <= 16 && variant != 121;   // keeps 4 workgroups per CU
-    if (a.x && !W4 && variant == 100) {
-        // fused quantization, int8 weights: measured faster with at most 32 channels per workgroup (QKV, one token:
-        // 10.4 us against 11.6 with 48) -- every workgroup quantizes all tokens before its first multiply
-        c = 2;
-        while (c > 1 && ceil_div(groups, c) < 320) c /= 2;
-    }
-    if (a.x) {   // fp16 tokens: quantize in the prologue (the caller checked decode_fuses_quant); always 8 wavefronts
-        if (EPI != EPI_F16 || !fits || a.M > FQ_MAX_M) return fail(QL_ERR_UNSUPPORTED, "fused quantization: unsupported shape");
-        // 16-k pieces of a wavefront's k-range x tokens (rounded up to a power of two) <= 64 lanes x 2 slots
-        const int pieces = W4 ? 8 * ceil_div(a.K / 128, 8) : 4 * ceil_div(a.K / 64, 8);
-        const int mp = a.M <= 1 ? 1 : a.M <= 2 ? 2 : 4;
-        if (pieces * mp > 128) return fail(QL_ERR_UNSUPPORTED, "fused quantization: unsupported shape");
+    const bool fits = (size_t)(a.M + 1) * a.K <= XL_MAX_LDS && a.M <= 16 && variant != 121;
+    if (a.x) {   // fp16 tokens: quantize in the prologue (the caller checked decode_fuses_quant)
+        const int slots = fused_slots(a.M, a.K);
+        if (EPI != EPI_F16 || !slots || variant == 121) return fail(QL_ERR_UNSUPPORTED, "fused quantization: unsupported shape");
         if constexpr (EPI == EPI_F16) {
             // at most one workgroup per CU: the quantizer overlaps the first ring of weights (OVL)
-            if (ceil_div(round_up(a.N, TILE_ROWS) / 16, c) <= 256) {
-                if (c == 1) return launch_one<W4, 1, 1, EPI, 8, true, 2, true>(a, st);
-                if (c == 2) return launch_one<W4, 1, 2, EPI, 8, true, 2, true>(a, st);
-                if (c == 3) return launch_one<W4, 1, 3, EPI, 8, true, 2, true>(a, st);
-                return launch_one<W4, 1, 4, EPI, 8, true, 2, true>(a, st);
+            const bool single = ceil_div(groups, c) <= 256;
+#define QL_FUSED(C)                                                                                                       \
+    return single ? (slots == 2 ? launch_one<W4, 1, C, EPI, 8, true, 2, true>(a, st) : launch_one<W4, 1, C, EPI, 8, true, 4, true>(a, st)) \
+                  : (slots == 2 ? launch_one<W4, 1, C, EPI, 8, true, 2>(a, st) : launch_one<W4, 1, C, EPI, 8, true, 4>(a, st))
+            // 8 wavefronts; with four pieces per lane and int4 weights as many as the two-kernel path takes (16: `wide`), so that
+            // the fp32 sums over the wavefronts' k-ranges are the same bits either way
+            if constexpr (W4) {
+                if (wide && slots == 4)
+                    return fused_pieces(a.M, a.K, 16) <= 128 ? launch_one<W4, 1, 1, EPI, 16, true, 2, true>(a, st)
+                                                             : launch_one<W4, 1, 1, EPI, 16, true, 4, true>(a, st);
             }
-            if (c == 1) return launch_one<W4, 1, 1, EPI, 8, true, 2>(a, st);
-            if (c == 2) return launch_one<W4, 1, 2, EPI, 8, true, 2>(a, st);
-            if (c == 3) return launch_one<W4, 1, 3, EPI, 8, true, 2>(a, st);
-            return launch_one<W4, 1, 4, EPI, 8, true, 2>(a, st);
+            if (c == 1) QL_FUSED(1);
+            if (c == 2) QL_FUSED(2);
+            if (c == 3) QL_FUSED(3);
+            QL_FUSED(4);
+#undef QL_FUSED
         }
     }
     const bool xl = fits && ((W4 && !wide) || variant == 111 || (variant >= 101 && variant <= 104));
@@ -799,17 +821,17 @@ int by_m(const GemmArgs &a, int variant, hipStream_t st)
 
 }  // namespace
 
-// The linear-layer entry points hand fp16 tokens straight to the decode GEMM when this holds (the same
-// condition that stages the tokens in LDS, and few enough tokens that every workgroup re-reading and
-// re-quantizing all of them costs less than a kernel launch).
-bool decode_fuses_quant(int M, int K, int variant)
+// The linear-layer entry points hand fp16 tokens straight to the decode GEMM when this holds.
+bool decode_fuses_quant(int M, int N, int K, int bits, int variant)
 {
-    // a wavefront (of at least 8) keeps its k-range in registers: at most 2 x 64 pieces of 16 k, tokens rounded up
-    // to a power of two (int4 splits whole 128-k groups, int8 64-k chunks: bound both)
-    const int pieces = ceil_div(ceil_div(K, 128), 8) * 8;
-    const int mp = M <= 1 ? 1 : M <= 2 ? 2 : 4;
-    return M >= 1 && M <= FQ_MAX_M && (size_t)(M + 1) * K <= FQ_MAX_LDS && pieces * mp <= 128 && variant != 121 &&
-           variant != 130;
+    const int slots = fused_slots(M, K);
+    if (!slots || variant == 121 || variant == 130) return false;
+    if (bits == 4 && slots == 4 && M > 8) {   // int4 on 16 wavefronts, 9 to 16 tokens: 6.9 us fused, 6.3 not (2048 x 2048)
+        int block, c;
+        auto_shape(M, N, K, true, 0, block, c);
+        return !sixteen_wavefronts(N, c);
+    }
+    return true;
 }
 
 double decode_estimate_us(const GemmArgs &a)
