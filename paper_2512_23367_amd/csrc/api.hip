@@ -95,6 +95,24 @@ int check_out(const void *y, int64_t ldy, int N)
     return QL_OK;
 }
 
+bool bytes_overlap(const void *p, size_t np, const void *q, size_t nq)
+{
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return a < b + nq && b < a + np;
+}
+
+// Whether rows of x and y share bytes.  The GEMM that quantizes its own tokens writes y while other workgroups still read
+// x; with the quantizer as a launch of its own all of x has been read before the first byte of y is written.
+bool rows_overlap(const void *x, int64_t ldx, int K, const void *y, int64_t ldy, int N, int M)
+{
+    const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), y0 = reinterpret_cast<uintptr_t>(y);
+    const uintptr_t x1 = x0 + 2 * ((uintptr_t)(M - 1) * ldx + K), y1 = y0 + 2 * ((uintptr_t)(M - 1) * ldy + N);
+    if (x1 <= y0 || y1 <= x0) return false;
+    if (ldx != ldy) return true;
+    const uintptr_t ld = 2 * (uintptr_t)ldx, shift = y0 >= x0 ? (y0 - x0) % ld : (ld - (x0 - y0) % ld) % ld;
+    return shift < 2 * (uintptr_t)K || shift + 2 * (uintptr_t)N > ld;   // false: two column ranges of one buffer
+}
+
 // automatic choice between the two kernel families
 bool decode_family(const GemmArgs &a)
 {
@@ -170,7 +188,8 @@ int linear_common(const void *x, int64_t ldx, int M, int K, const void *wq, cons
     if (!aligned(wq, 256) || (sw && !aligned(sw, 16)) || (bias && !aligned(bias, 16)))
         return fail(QL_ERR_ALIGN, "wq needs 256-byte, sw/bias 16-byte alignment");
     QL_TRY(check_out(y, ldy, N));
-    if (M <= DECODE_MAX_M && (g_variant == 0 || (g_variant >= 100 && g_variant < 200)) && decode_fuses_quant(M, N, K, bits, g_variant)) {
+    if (M <= DECODE_MAX_M && (g_variant == 0 || (g_variant >= 100 && g_variant < 200)) && decode_fuses_quant(M, N, K, bits, g_variant) &&
+        !rows_overlap(x, ldx, K, y, ldy, N, M)) {
         // few tokens: the decode GEMM quantizes them itself, one launch instead of two
         GemmArgs a = {};
         a.x = static_cast<const __half *>(x);
@@ -526,6 +545,16 @@ int ql_quant_weight_transformed(const void *w, int N, int K, int bits, int group
         (wq_kernel && !aligned(wq_kernel, 256)))
         return fail(QL_ERR_ALIGN, "w/w32/smooth/wq_canonical/scales need 16-byte, wq_kernel 256-byte alignment");
     hipStream_t st = static_cast<hipStream_t>(stream);
+    // results may take the place of the fp16 weights (or of the scale vector): all of these are then read before any is written
+    const size_t nk = (size_t)N * K;
+    auto over_inputs = [&](const void *p, size_t bytes) {
+        return p && (bytes_overlap(p, bytes, w, nk * 2) || (smooth && bytes_overlap(p, bytes, smooth, (size_t)K * 4)));
+    };
+    const bool in_place = over_inputs(wq_canonical, bits == 8 ? nk : nk / 2) || over_inputs(scales, bits == 8 ? (size_t)N * 4 : nk / 64) ||
+                          over_inputs(wq_kernel, bits == 8 ? w8_kernel_bytes(N, K) : w4_kernel_bytes(N, K, group));
+    if (in_place)
+        return launch_weight_transform_then_quant(static_cast<const __half *>(w), N, K, bits, group, smooth, hadamard_block, w32,
+                                                  wq_canonical, scales, wq_kernel, st);
     return launch_weight_transform_quant(static_cast<const __half *>(w), N, K, bits, group, smooth, hadamard_block, w32, wq_canonical,
                                          scales, wq_kernel, st);
 }

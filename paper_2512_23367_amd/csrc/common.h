@@ -99,6 +99,8 @@ int launch_act_quant_transform(const __half *x, int64_t ldx, int M, int K, const
                                int8_t *xq_rm, int8_t *xq_kl, float *sx, hipStream_t st);
 int launch_weight_transform_quant(const __half *w, int N, int K, int bits, int group, const float *smooth, int hblock, float *w32,
                                   void *canon, void *scales, void *kl, hipStream_t st);
+int launch_weight_transform_then_quant(const __half *w, int N, int K, int bits, int group, const float *smooth, int hblock, float *w32,
+                                       void *canon, void *scales, void *kl, hipStream_t st);
 int launch_channel_absmax(const __half *x, int64_t ldx, int M, int K, float *xmax, hipStream_t st);
 int launch_smooth_scales(const float *xmax, const __half *w, int N, int K, float alpha, float *s, float *inv_s,
                          hipStream_t st);

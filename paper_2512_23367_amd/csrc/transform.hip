@@ -312,7 +312,8 @@ __device__ inline int weight_code(float w, float s, float limit)   // the quanti
 // Offline: S W and / or H^T W of one weight row (output channel) per workgroup, its fp32 values stored (w32) and quantized
 // from the registers in the same pass (bound by HBM: 2 bytes in, 4 + 2 x codes out per weight; as two kernels the
 // fp32 values were read back: 145 us for 4096 x 11008, int4, against 87 in one).  Rows N .. 32-row padding: zero codes.
-template <int LB, int BITS>
+// STORED: quantizes what an earlier launch left in w32 (only where the results take the place of the inputs).
+template <int LB, int BITS, bool STORED = false>
 __global__ __launch_bounds__(MAX_WAVES * 64) void weight_transform_quant_kernel(const __half *__restrict__ w, int N, int Npad, int K,
                                                                                  const float *__restrict__ smooth, float norm,
                                                                                  float *__restrict__ w32, uint8_t *__restrict__ canon,
@@ -327,10 +328,21 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void weight_transform_quant_kernel(
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
     const int l = logical_lane(lane), c0 = wave * NIT * 64 + l, G = K / 128;
     float v[NIT][16];
-    load_row<NIT>(w + (size_t)(real ? n : 0) * K, real, K, smooth, c0, v);
-    hadamard_wave<LB>(v, l, norm);
+    if constexpr (STORED) {
+        static_assert(LB == 0, "already transformed");
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) unswap_values<LB>(v[it]);
+        for (int it = 0; it < NIT; ++it) {
+            const int c = c0 + it * 64;
+            const bool there = real && c < K / 16;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[it][i] = there ? w32[(size_t)n * K + (size_t)c * 16 + i] : 0.0f;
+        }
+    } else {
+        load_row<NIT>(w + (size_t)(real ? n : 0) * K, real, K, smooth, c0, v);
+        hadamard_wave<LB>(v, l, norm);
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) unswap_values<LB>(v[it]);
+    }
     float amax[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
@@ -338,7 +350,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void weight_transform_quant_kernel(
         amax[it] = 0.0f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) amax[it] = fmaxf(amax[it], fabsf(v[it][i]));
-        if (real && c < K / 16) {
+        if (!STORED && real && c < K / 16) {
 #pragma unroll
             for (int i = 0; i < 16; i += 4)
                 *reinterpret_cast<float4 *>(w32 + (size_t)n * K + (size_t)c * 16 + i) = make_float4(v[it][i], v[it][i + 1], v[it][i + 2], v[it][i + 3]);
@@ -560,6 +572,21 @@ int launch_weight_transform_quant(const __half *w, int N, int K, int bits, int g
                                static_cast<uint8_t *>(canon), scales, blob, kls, klsd);
         return check_hip(hipGetLastError(), "weight_transform_quant launch");
     });
+}
+
+int launch_weight_transform_then_quant(const __half *w, int N, int K, int bits, int group, const float *smooth, int hblock, float *w32,
+                                       void *canon, void *scales, void *kl, hipStream_t st)
+{
+    QL_TRY(launch_weight_transform_quant(w, N, K, 8, 0, smooth, hblock, w32, nullptr, nullptr, nullptr, st));   // fills w32
+    const int Npad = round_up(N, TILE_ROWS), rows = kl ? Npad : N;
+    uint8_t *blob = static_cast<uint8_t *>(kl);
+    __half *kls = (kl && bits == 4) ? reinterpret_cast<__half *>(blob + w4_scales_offset(N, K)) : nullptr;
+    __half *klsd = (kl && bits == 4) ? reinterpret_cast<__half *>(blob + w4_scales_dec_offset(N, K, group)) : nullptr;
+    const dim3 grid(workgroups_for(rows, 32)), block(ceil_div(K / 16, 64 * hadamard_chunks(0)) * 64);
+    auto kern = bits == 8 ? weight_transform_quant_kernel<0, 8, true> : weight_transform_quant_kernel<0, 4, true>;
+    hipLaunchKernelGGL(kern, grid, block, 0, st, nullptr, N, rows, K, nullptr, 1.0f, w32, static_cast<uint8_t *>(canon), scales, blob,
+                       kls, klsd);
+    return check_hip(hipGetLastError(), "weight_transform_quant launch (stored)");
 }
 
 int launch_channel_absmax(const __half *x, int64_t ldx, int M, int K, float *xmax, hipStream_t st)
