@@ -35,8 +35,10 @@ __device__ inline int logical_lane(int p) { return p ^ ((p & 4) ? 3 : 0); }
 // of its result.  Every value of a lane then carries the same sign, -1 to the number of such stages in which the lane was
 // the upper one; partners agree in it (they differ in the stage's own bit only), and the final multiply takes it out.
 // Written as one block of multiply-adds whose first operand is permuted (the compiler keeps the permutation a move of its
-// own, with wait states in front of each); the leading s_nop covers the two wait states between the last write of a
-// register and its permuted read.  Every lane of the wavefront is active here and every source lane exists.
+// own, with wait states in front of each).  gfx950 needs two wait states between a vector write of a register and its
+// permuted read or lane-register swap: the leading s_nop covers them for the first multiply-add, the last one for whatever
+// follows -- the compiler counts them for its own instructions but does not see writes inside the block.  Every lane of
+// the wavefront is active here and every source lane exists.
 #define QL_FMAC_DPP(i, ctrl) "v_fmac_f32_dpp %" #i ", %" #i ", %16 " ctrl " row_mask:0xf bank_mask:0xf\n\t"
 #define QL_LANE_STAGE(name, ctrl)                                                                                                     \
     __device__ inline void name(float (&v)[16], float s)                                                                              \
@@ -44,7 +46,7 @@ __device__ inline int logical_lane(int p) { return p ^ ((p & 4) ? 3 : 0); }
         asm("s_nop 1\n\t" QL_FMAC_DPP(0, ctrl) QL_FMAC_DPP(1, ctrl) QL_FMAC_DPP(2, ctrl) QL_FMAC_DPP(3, ctrl) QL_FMAC_DPP(4, ctrl)      \
                 QL_FMAC_DPP(5, ctrl) QL_FMAC_DPP(6, ctrl) QL_FMAC_DPP(7, ctrl) QL_FMAC_DPP(8, ctrl) QL_FMAC_DPP(9, ctrl)               \
                     QL_FMAC_DPP(10, ctrl) QL_FMAC_DPP(11, ctrl) QL_FMAC_DPP(12, ctrl) QL_FMAC_DPP(13, ctrl) QL_FMAC_DPP(14, ctrl)       \
-                        QL_FMAC_DPP(15, ctrl)                                                                                         \
+                        QL_FMAC_DPP(15, ctrl) "s_nop 1"                                                                               \
             : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]), "+v"(v[8]), "+v"(v[9]),  \
               "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15])                                            \
             : "v"(s));                                                                                                                \
