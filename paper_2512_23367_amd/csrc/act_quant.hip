@@ -29,13 +29,19 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));
 // single fp32 operations).
 //
 // What bounds it: HBM (3 B per element, SwiGLU 5) for many tokens, one memory round trip for few.  One workgroup per
-// token, one chunk of 16 consecutive elements per lane (K / 1024 wavefronts, rounded up, share the token): few registers,
-// so a CU holds many tokens whose loads and arithmetic cover each other.  Range-checked buffer loads: a lane behind the
-// row's end reads zeros, without a branch.  With the row spread over at most 8 wavefronts of several chunks, loaded under
-// conditions, SwiGLU of 4096 x 11008 took 84 us (2.7 TB/s) against 64 us (3.5 TB/s), of 32 x 11008 7.6 against 5.5 us.
+// token, NC chunks of 16 consecutive elements per lane (1 up to K = 16384: K / 1024 wavefronts, rounded up, share the token):
+// few registers, so a CU holds many tokens whose loads and arithmetic cover each other.  Range-checked buffer loads: a lane
+// behind the row's end reads zeros, without a branch.  With the row spread over at most 8 wavefronts of several chunks, loaded
+// under conditions, SwiGLU of 4096 x 11008 took 84 us (2.7 TB/s) against 64 us (3.5 TB/s), of 32 x 11008 7.6 against 5.5 us.
 // (Workgroups that stay and keep several tokens in flight in an LDS ring were slower: 69 us.)
+// Longer rows (the down projections of 70B-class layers: 28672) keep 2, 4 or 8 chunks per lane in as many wavefronts as they
+// need.  The fp32 values stay in registers between maximum and codes (SwiGLU: its ~45 operations per element are done once);
+// with 8 chunks there is room for the fp16 values only, and RMSNorm forms its products again.  K = 28672, plain / RMSNorm /
+// SwiGLU, against rows read twice (three times) by 8 wavefronts: 32 tokens 4.6 / 6.7 / 11.3 us, before 5.3 / 7.6 / 15.3;
+// 4096 tokens 75 / 105 / 145, before 161 / 181 / 229.
 constexpr int MAX_WAVES = 16;
-constexpr int ROW_MAX_K = MAX_WAVES * 64 * CHUNK;   // 16384; longer rows: act_quant_long_kernel
+constexpr int ROW_CHUNKS = MAX_WAVES * 64;                      // chunks of a row held one per lane
+constexpr int ROW4_MAX_K = 4 * ROW_CHUNKS * CHUNK;              // 65536: longer SmoothQuant and SwiGLU rows are read twice
 
 __device__ inline void widen(const Half16 &h, float (&f)[16])
 {
@@ -63,54 +69,70 @@ __device__ inline Half16 load_chunk(__amdgpu_buffer_rsrc_t rs, unsigned off)
     return chunk_of(lo, hi);
 }
 
-template <int MODE>
+// Workgroup ids go to the 8 XCDs in turn.  Every XCD takes one contiguous range of tokens (whole groups of 8: the tokens that
+// share 128-byte lines of the tile order), so that what it writes at a time is a window of a few dozen tokens that its L2
+// holds until the lines are whole.  M: nothing to do.
+__device__ inline int token_of_workgroup(int M)
+{
+    const int groups = (M + 7) / 8, xcd = blockIdx.x % 8, in_xcd = blockIdx.x / 8;
+    if (in_xcd >= 8 * (groups / 8 + (xcd < groups % 8 ? 1 : 0))) return M;
+    return 8 * (xcd * (groups / 8) + (xcd < groups % 8 ? xcd : groups % 8)) + in_xcd;
+}
+
+template <int MODE, int NC>
 __global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_kernel(const __half *__restrict__ x, int64_t ldx, int M, int K,
                                                                     const float *__restrict__ inv_smooth,
                                                                     const __half *__restrict__ gamma, float eps,
                                                                     int8_t *__restrict__ xq_rm, int8_t *__restrict__ xq_kl,
                                                                     float *__restrict__ sx)
 {
+    static_assert(NC <= 4 || MODE == 0 || MODE == 2, "SmoothQuant, SwiGLU: the fp32 values of a row stay in registers");
+    constexpr bool KEEP = MODE != 0 && NC <= 4;      // the values to quantize stay in registers as fp32
     __shared__ unsigned red[MAX_WAVES];
     __shared__ double red_ss[MODE == 2 ? MAX_WAVES : 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-    // Workgroup ids go to the 8 XCDs in turn.  Every XCD takes one contiguous range of tokens (whole groups of 8: the tokens
-    // that share 128-byte lines of the tile order), so that what it writes at a time is a window of a few dozen tokens
-    // that its L2 holds until the lines are whole.
-    const int groups = (M + 7) / 8, xcd = blockIdx.x % 8, in_xcd = blockIdx.x / 8;
-    const int m = 8 * (xcd * (groups / 8) + (xcd < groups % 8 ? xcd : groups % 8)) + in_xcd;
-    if (in_xcd >= 8 * (groups / 8 + (xcd < groups % 8 ? 1 : 0)) || m >= M) return;
+    const int m = token_of_workgroup(M);
+    if (m >= M) return;
 
-    const int c = threadIdx.x;                       // this lane's chunk of the row
-    const bool have = c < K / CHUNK;
+    // this lane's chunks of the row: threadIdx.x, threadIdx.x + blockDim.x, ...
+    auto chunk = [&](int it) { return (int)threadIdx.x + it * (int)blockDim.x; };
+    auto have = [&](int it) { return chunk(it) < K / CHUNK; };
+    auto at = [&](int it, unsigned bytes) { return have(it) ? (unsigned)chunk(it) * bytes : ABSENT; };
     const __amdgpu_buffer_rsrc_t rs = buffer_of(x + (size_t)m * ldx, (MODE == 3 ? 4u : 2u) * (unsigned)K);
-    const Half16 v = load_chunk(rs, have ? (unsigned)c * 32u : ABSENT);
-    Half16 u, gm;
-    if constexpr (MODE == 3) u = load_chunk(rs, have ? (unsigned)c * 32u + 2u * (unsigned)K : ABSENT);
-    if constexpr (MODE == 2) gm = load_chunk(buffer_of(gamma, (size_t)K * sizeof(__half)), have ? (unsigned)c * 32u : ABSENT);
-    // the values to quantize: fp16 bits as loaded, or fp32 after the mode's arithmetic (absent chunks are zeros, which
-    // change neither a maximum nor a sum of squares)
-    float f[16];
-    if constexpr (MODE != 0) widen(v, f);
-    if constexpr (MODE == 1) {
-        const __amdgpu_buffer_rsrc_t ri = buffer_of(inv_smooth, (size_t)K * sizeof(float));
-        v4u sm[4];
+    const __amdgpu_buffer_rsrc_t rv = MODE == 1 ? buffer_of(inv_smooth, (size_t)K * sizeof(float))
+                                                : buffer_of(gamma, MODE == 2 ? (size_t)K * sizeof(__half) : 0);
+    Half16 v[NC];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            sm[q] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(ri, have ? (unsigned)c * 64u + q * 16u : ABSENT, 0, 0));
-#pragma unroll
-        for (int e = 0; e < 16; ++e) f[e] *= __uint_as_float(sm[e / 4][e % 4]);
-    }
+    for (int it = 0; it < NC; ++it) v[it] = load_chunk(rs, at(it, 32u));
+    Half16 u[MODE == 3 ? NC : 1], gm[MODE == 2 && KEEP ? NC : 1];
     if constexpr (MODE == 3) {
-        float up[16];
-        widen(u, up);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) f[e] = swiglu_f32(f[e], up[e]);
+        for (int it = 0; it < NC; ++it) u[it] = load_chunk(rs, have(it) ? (unsigned)chunk(it) * 32u + 2u * (unsigned)K : ABSENT);
     }
+    if constexpr (MODE == 2 && KEEP) {
+#pragma unroll
+        for (int it = 0; it < NC; ++it) gm[it] = load_chunk(rv, at(it, 32u));
+    }
+    // RMSNorm, 8 chunks: the widened values of one pass must not stay for the next (the registers do not hold them)
+    auto fp16_only = [&]() {
+        if constexpr (MODE == 2 && !KEEP) {
+#pragma unroll
+            for (int it = 0; it < NC; ++it)
+                asm volatile("" : "+v"(v[it].lo.x), "+v"(v[it].lo.y), "+v"(v[it].lo.z), "+v"(v[it].lo.w), "+v"(v[it].hi.x), "+v"(v[it].hi.y),
+                             "+v"(v[it].hi.z), "+v"(v[it].hi.w)::"memory");
+        }
+    };
+    float rnorm = 0.0f;
     if constexpr (MODE == 2) {
-        // sum of squares first (the maximum needs the normalised values); squares of fp16 values are exact
+        // sum of squares first (the maximum needs the normalised values); squares of fp16 values are exact, absent chunks zeros
         double ss = 0.0;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) ss = __builtin_fma((double)f[e], (double)f[e], ss);
+        for (int it = 0; it < NC; ++it) {
+            float f[16];
+            widen(v[it], f);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) ss = __builtin_fma((double)f[e], (double)f[e], ss);
+        }
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
         if (lane == 0) red_ss[wave] = ss;
@@ -118,19 +140,49 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_kernel(const __half 
         double tot = 0.0;
         for (int w = 0; w < nwaves; ++w) tot += red_ss[w];
         const float mean = (float)tot / (float)K;
-        const float rnorm = 1.0f / sqrtf(mean + eps);
-        float g[16];
-        widen(gm, g);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) f[e] = (f[e] * rnorm) * g[e];
+        rnorm = 1.0f / sqrtf(mean + eps);
+        fp16_only();
     }
+    // the values to quantize: fp16 bits as loaded, or fp32 after the mode's arithmetic (absent chunks are zeros, which
+    // change no maximum)
+    auto values = [&](int it, float (&f)[16]) {
+        widen(v[it], f);
+        if constexpr (MODE == 1) {
+            v4u sm[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                sm[q] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rv, have(it) ? (unsigned)chunk(it) * 64u + q * 16u : ABSENT, 0, 0));
+#pragma unroll
+            for (int e = 0; e < 16; ++e) f[e] *= __uint_as_float(sm[e / 4][e % 4]);
+        }
+        if constexpr (MODE == 2) {
+            float g[16];
+            widen(KEEP ? gm[KEEP ? it : 0] : load_chunk(rv, at(it, 32u)), g);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) f[e] = (f[e] * rnorm) * g[e];
+        }
+        if constexpr (MODE == 3) {
+            float up[16];
+            widen(u[it], up);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) f[e] = swiglu_f32(f[e], up[e]);
+        }
+    };
+    float kept[KEEP ? NC : 1][16];
     unsigned mx = 0;
     if constexpr (MODE == 0) {
-        mx = abs_max_bits(v, 0);
+#pragma unroll
+        for (int it = 0; it < NC; ++it) mx = abs_max_bits(v[it], mx);
     } else {
         float mf = 0.0f;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) mf = __builtin_elementwise_maximum(mf, fabsf(f[e]));   // passes a NaN on
+        for (int it = 0; it < NC; ++it) {
+            float (&f)[16] = kept[KEEP ? it : 0];
+            values(it, f);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) mf = __builtin_elementwise_maximum(mf, fabsf(f[e]));   // passes a NaN on
+            if (!KEEP) __builtin_amdgcn_sched_barrier(0);   // (nor do the vectors of all chunks at once)
+        }
         mx = __float_as_uint(mf);   // non-negative floats order like their bit patterns
     }
 #pragma unroll
@@ -143,12 +195,25 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_kernel(const __half 
     if (MODE != 0) token_scales_f32(__uint_as_float(mx), scale, inv);
     else token_scales(mx, scale, inv);
     if (threadIdx.x == 0) sx[m] = scale;
-    if (!have) return;
-    uint4 q;
-    if constexpr (MODE == 0) q = quant_chunk(v, inv);
-    else q = quant_chunk_f32(f, inv);
-    if (xq_rm) *reinterpret_cast<uint4 *>(xq_rm + (size_t)m * K + (size_t)c * CHUNK) = q;
-    if (xq_kl) *reinterpret_cast<uint4 *>(xq_kl + tile_offset_i8(m, c * CHUNK, K)) = q;
+    fp16_only();
+#pragma unroll
+    for (int it = 0; it < NC; ++it) {
+        const int c = chunk(it);
+        if (!have(it)) break;                        // (the chunks of a lane ascend)
+        uint4 q;
+        if constexpr (MODE == 0) {
+            q = quant_chunk(v[it], inv);
+        } else if constexpr (KEEP) {
+            q = quant_chunk_f32(kept[it], inv);
+        } else {
+            float f[16];
+            values(it, f);
+            q = quant_chunk_f32(f, inv);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (xq_rm) *reinterpret_cast<uint4 *>(xq_rm + (size_t)m * K + (size_t)c * CHUNK) = q;
+        if (xq_kl) *reinterpret_cast<uint4 *>(xq_kl + tile_offset_i8(m, c * CHUNK, K)) = q;
+    }
 }
 
 // Many tokens, plain and SmoothQuant (MODE 0, 1): one workgroup per 8 tokens.  A wavefront covers 8 tokens x 8 chunks per
@@ -158,19 +223,20 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_kernel(const __half 
 // 10.9 us against 12.9 with a workgroup per token, 16384 x 1536 16.2 against 20.0; at 3001 x 4096 (10.2 / 10.1),
 // 1024 x 4096 (6.5 / 5.4) and below it is the other way round.
 // NIT: steps per wavefront kept in registers (up to K = 12288).
-constexpr int ROWS8 = 8, ROWS8_WAVES = 8, ROWS8_MIN_M = 3072, ROWS8_MAX_K = 12288;
+// RPB: 8 tokens per workgroup, or 1 (SmoothQuant rows of 65536 < K <= 98304: the fp16 values fit 8 wavefronts of 12 chunks).
+constexpr int ROWS8_WAVES = 8, ROWS8_MIN_M = 3072, ROWS8_MAX_K = 12288, ROW12_MAX_K = 12 * 64 * ROWS8_WAVES * CHUNK;
 
-template <int NIT, int MODE>
+template <int NIT, int MODE, int RPB = 8>
 __global__ __launch_bounds__(ROWS8_WAVES * 64) void act_quant_rows8_kernel(const __half *__restrict__ x, int64_t ldx, int M, int K,
                                                                             int per_wave, const float *__restrict__ inv_smooth,
                                                                             int8_t *__restrict__ xq_rm, int8_t *__restrict__ xq_kl,
                                                                             float *__restrict__ sx)
 {
-    __shared__ unsigned red[ROWS8][ROWS8_WAVES];
-    constexpr int CPS = 64 / ROWS8;                     // chunks per wavefront per step
+    __shared__ unsigned red[RPB][ROWS8_WAVES];
+    constexpr int CPS = 64 / RPB;                     // chunks per wavefront per step
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-    const int r = lane % ROWS8, cl = lane / ROWS8;
-    const int m = blockIdx.x * ROWS8 + r;
+    const int r = lane % RPB, cl = lane / RPB;
+    const int m = blockIdx.x * RPB + r;
     const bool valid = m < M;
     const int nchunks = K / CHUNK;
     const int s0 = wave * per_wave;
@@ -190,8 +256,8 @@ __global__ __launch_bounds__(ROWS8_WAVES * 64) void act_quant_rows8_kernel(const
         // chunk beyond the row, the wavefront's share or the last token reads zeros): with a conditional load per step the
         // compiler waits for each step's data before it issues the next step's loads.  The buffer is the workgroup's
         // 8 rows, so the 32-bit offsets hold for any M.
-        const int rows = M - (int)blockIdx.x * ROWS8 < ROWS8 ? M - (int)blockIdx.x * ROWS8 : ROWS8;
-        const __amdgpu_buffer_rsrc_t rs = buffer_of(x + (size_t)blockIdx.x * ROWS8 * ldx, ((size_t)(rows - 1) * ldx + K) * sizeof(__half));
+        const int rows = M - (int)blockIdx.x * RPB < RPB ? M - (int)blockIdx.x * RPB : RPB;
+        const __amdgpu_buffer_rsrc_t rs = buffer_of(x + (size_t)blockIdx.x * RPB * ldx, ((size_t)(rows - 1) * ldx + K) * sizeof(__half));
 #pragma unroll
         for (int i = 0; i < NIT; ++i) {
             const int c = (s0 + i) * CPS + cl;
@@ -217,7 +283,7 @@ __global__ __launch_bounds__(ROWS8_WAVES * 64) void act_quant_rows8_kernel(const
         }
     }
 #pragma unroll
-    for (int off = 32; off >= ROWS8; off >>= 1) mx = max(mx, (unsigned)__shfl_xor((int)mx, off, 64));
+    for (int off = 32; off >= RPB; off >>= 1) mx = max(mx, (unsigned)__shfl_xor((int)mx, off, 64));
     if (cl == 0) red[r][wave] = mx;
     __syncthreads();
     mx = 0;
@@ -244,51 +310,26 @@ __global__ __launch_bounds__(ROWS8_WAVES * 64) void act_quant_rows8_kernel(const
     }
 }
 
-// Rows too long for the kernel above (K > 16384; no layer of the usual models): one workgroup per token, the row is read
-// twice (three times with RMSNorm), the mode's arithmetic is repeated.
+// SwiGLU rows too long for registers (K > 65536): the row is read twice and the arithmetic done twice.
 constexpr int LONG_WAVES = 8;
 
-template <int MODE>
-__global__ __launch_bounds__(LONG_WAVES * 64) void act_quant_long_kernel(const __half *__restrict__ x, int64_t ldx, int K,
-                                                                         const float *__restrict__ inv_smooth,
-                                                                         const __half *__restrict__ gamma, float eps,
-                                                                         int8_t *__restrict__ xq_rm, int8_t *__restrict__ xq_kl,
-                                                                         float *__restrict__ sx)
+__global__ __launch_bounds__(LONG_WAVES * 64) void act_quant_swiglu_long_kernel(const __half *__restrict__ x, int64_t ldx, int M, int K,
+                                                                                int8_t *__restrict__ xq_rm, int8_t *__restrict__ xq_kl,
+                                                                                float *__restrict__ sx)
 {
     __shared__ unsigned red[LONG_WAVES];
-    __shared__ double red_ss[LONG_WAVES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m = blockIdx.x, nchunks = K / CHUNK;
+    // (up to 64 tokens: no XCD holds more than 8 of them either way, and 8 XCDs read faster than one: 8 x 98304 45 us against 49)
+    const int m = M <= 64 ? (int)blockIdx.x : token_of_workgroup(M), nchunks = K / CHUNK;
+    if (m >= M) return;
     const Half16 *row = reinterpret_cast<const Half16 *>(x + (size_t)m * ldx);
     const Half16 *row_up = reinterpret_cast<const Half16 *>(x + (size_t)m * ldx + K);
-    float rnorm = 0.0f;
-    if constexpr (MODE == 2) {
-        double ss = 0.0;
-        for (int c = threadIdx.x; c < nchunks; c += LONG_WAVES * 64) {
-            float f[16];
-            widen(row[c], f);
-#pragma unroll
-            for (int e = 0; e < 16; ++e) ss = __builtin_fma((double)f[e], (double)f[e], ss);
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
-        if (lane == 0) red_ss[wave] = ss;
-        __syncthreads();
-        double tot = 0.0;
-        for (int w = 0; w < LONG_WAVES; ++w) tot += red_ss[w];
-        rnorm = 1.0f / sqrtf((float)tot / (float)K + eps);
-    }
     auto values = [&](int c, float (&f)[16]) {
-        widen(row[c], f);
         float g[16];
-        if constexpr (MODE == 2) widen(reinterpret_cast<const Half16 *>(gamma)[c], g);
-        if constexpr (MODE == 3) widen(row_up[c], g);
+        widen(row[c], f);
+        widen(row_up[c], g);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            if (MODE == 1) f[e] *= inv_smooth[(size_t)c * CHUNK + e];
-            if (MODE == 2) f[e] = (f[e] * rnorm) * g[e];
-            if (MODE == 3) f[e] = swiglu_f32(f[e], g[e]);
-        }
+        for (int e = 0; e < 16; ++e) f[e] = swiglu_f32(f[e], g[e]);
     };
     unsigned mx = 0;
     for (int c = threadIdx.x; c < nchunks; c += LONG_WAVES * 64) {
@@ -304,7 +345,7 @@ __global__ __launch_bounds__(LONG_WAVES * 64) void act_quant_long_kernel(const _
     mx = 0;
     for (int w = 0; w < LONG_WAVES; ++w) mx = max(mx, red[w]);
     float scale, inv;
-    token_scales_f32(__uint_as_float(mx), scale, inv);   // widening to fp32 is exact: the same as the fp16 maximum's
+    token_scales_f32(__uint_as_float(mx), scale, inv);
     if (threadIdx.x == 0) sx[m] = scale;
     for (int c = threadIdx.x; c < nchunks; c += LONG_WAVES * 64) {
         float f[16];
@@ -314,6 +355,64 @@ __global__ __launch_bounds__(LONG_WAVES * 64) void act_quant_long_kernel(const _
         if (xq_kl) *reinterpret_cast<uint4 *>(xq_kl + tile_offset_i8(m, c * CHUNK, K)) = q;
     }
 }
+
+// SmoothQuant, long rows of many tokens (the factors, 4 bytes per element from L2, are shared by RPB = 8 tokens; lane = token %
+// 8 + 8 * chunk as above) and rows beyond the registers: read twice, the wavefronts take contiguous ranges of K.
+// 2048 x 40960 83 us against 95 with a workgroup per token, 4096 x 16448 67 against 72 (below 2048 tokens it is the
+// other way round: 1024 x 28672 45 against 32).  RPB = 1: at most 512 tokens of K > 98304.
+template <int RPB>
+__global__ __launch_bounds__(LONG_WAVES * 64) void act_quant_smooth_long_kernel(const __half *__restrict__ x, int64_t ldx, int M, int K,
+                                                                                const float *__restrict__ inv_smooth,
+                                                                                int8_t *__restrict__ xq_rm, int8_t *__restrict__ xq_kl,
+                                                                                float *__restrict__ sx)
+{
+    __shared__ unsigned red[RPB][LONG_WAVES];
+    constexpr int CPS = 64 / RPB;                        // chunks per wavefront per step
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane % RPB, cl = lane / RPB;
+    const int m = blockIdx.x * RPB + r, nchunks = K / CHUNK;
+    const bool valid = m < M;
+    const int steps = (nchunks + CPS - 1) / CPS, per_wave = (steps + LONG_WAVES - 1) / LONG_WAVES, s0 = wave * per_wave;
+    const Half16 *row = reinterpret_cast<const Half16 *>(x + (size_t)(valid ? m : 0) * ldx);
+    auto products = [&](int c, float (&f)[16]) {
+        widen(row[c], f);
+#pragma unroll
+        for (int i = 0; i < 16; i += 4) {
+            const float4 s4 = *reinterpret_cast<const float4 *>(inv_smooth + (size_t)c * CHUNK + i);
+            f[i] *= s4.x, f[i + 1] *= s4.y, f[i + 2] *= s4.z, f[i + 3] *= s4.w;
+        }
+    };
+    unsigned mx = 0;
+    for (int i = 0; i < per_wave; ++i) {
+        const int c = (s0 + i) * CPS + cl;
+        if (c < nchunks && valid) {
+            float f[16];
+            products(c, f);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) mx = max(mx, __float_as_uint(fabsf(f[e])));
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= RPB; off >>= 1) mx = max(mx, (unsigned)__shfl_xor((int)mx, off, 64));
+    if (cl == 0) red[r][wave] = mx;
+    __syncthreads();
+    mx = 0;
+    for (int w = 0; w < LONG_WAVES; ++w) mx = max(mx, red[r][w]);
+    float scale, inv;
+    token_scales_f32(__uint_as_float(mx), scale, inv);
+    if (wave == 0 && cl == 0 && valid) sx[m] = scale;
+    for (int i = 0; i < per_wave; ++i) {
+        const int c = (s0 + i) * CPS + cl;
+        if (c < nchunks && valid) {
+            float f[16];
+            products(c, f);
+            const uint4 q = quant_chunk_f32(f, inv);
+            if (xq_rm) *reinterpret_cast<uint4 *>(xq_rm + (size_t)m * K + (size_t)c * CHUNK) = q;
+            if (xq_kl) *reinterpret_cast<uint4 *>(xq_kl + tile_offset_i8(m, c * CHUNK, K)) = q;
+        }
+    }
+}
+
+constexpr int SMOOTH_LONG_MIN_M = 2048;
 
 // The other quantizer forms of the Preliminary section (not the hot path; one workgroup per token, the row is
 // read twice).  Eq. 1 as printed: code = rne(x / s) with the stored fp32 scale s (IEEE division), then Eq. 2's
@@ -422,9 +521,9 @@ template <int MODE>
 static void launch_rows8(const __half *x, int64_t ldx, int M, int K, const float *inv_smooth, int8_t *xq_rm, int8_t *xq_kl, float *sx,
                          hipStream_t st)
 {
-    const int steps = ceil_div(K / CHUNK, 64 / ROWS8);
+    const int steps = ceil_div(K / CHUNK, 64 / 8);
     const int nw = steps < ROWS8_WAVES ? steps : ROWS8_WAVES, per_wave = ceil_div(steps, nw);
-    const dim3 grid(ceil_div(M, ROWS8)), block(nw * 64);
+    const dim3 grid(ceil_div(M, 8)), block(nw * 64);
 #define QL_LAUNCH_ROWS8(NIT) \
     hipLaunchKernelGGL((act_quant_rows8_kernel<NIT, MODE>), grid, block, 0, st, x, ldx, M, K, per_wave, inv_smooth, xq_rm, xq_kl, sx)
     if (per_wave <= 1) QL_LAUNCH_ROWS8(1);
@@ -445,12 +544,38 @@ static int launch_aq(const __half *x, int64_t ldx, int M, int K, const float *in
             return check_hip(hipGetLastError(), "act_quant (8 tokens per workgroup) launch");
         }
     }
-    if (K > ROW_MAX_K)
-        hipLaunchKernelGGL((act_quant_long_kernel<MODE>), dim3(M), dim3(LONG_WAVES * 64), 0, st, x, ldx, K, inv_smooth, gamma, eps,
-                           xq_rm, xq_kl, sx);
-    else   // 8 equal ranges of whole groups of 8 tokens; what a range has too few ends at once
-        hipLaunchKernelGGL((act_quant_kernel<MODE>), dim3(64 * ceil_div(M, 64)), dim3(ceil_div(K / CHUNK, 64) * 64), 0, st, x, ldx, M, K,
-                           inv_smooth, gamma, eps, xq_rm, xq_kl, sx);
+    const dim3 grid(64 * ceil_div(M, 64));   // 8 equal ranges of whole groups of 8 tokens; what a range has too few ends at once
+    const int chunks = K / CHUNK;
+    if constexpr (MODE == 1) {
+        if (K > ROW4_MAX_K && K <= ROW12_MAX_K && M < SMOOTH_LONG_MIN_M) {
+            hipLaunchKernelGGL((act_quant_rows8_kernel<12, 1, 1>), dim3(M), dim3(ROWS8_WAVES * 64), 0, st, x, ldx, M, K,
+                               ceil_div(ceil_div(chunks, 64), ROWS8_WAVES), inv_smooth, xq_rm, xq_kl, sx);
+            return check_hip(hipGetLastError(), "act_quant (long rows) launch");
+        }
+        if (K > ROW12_MAX_K && M <= 512) {
+            hipLaunchKernelGGL(act_quant_smooth_long_kernel<1>, dim3(M), dim3(LONG_WAVES * 64), 0, st, x, ldx, M, K, inv_smooth, xq_rm, xq_kl, sx);
+            return check_hip(hipGetLastError(), "act_quant (long rows) launch");
+        }
+        if (K > ROW4_MAX_K || (chunks > ROW_CHUNKS && M >= SMOOTH_LONG_MIN_M)) {
+            hipLaunchKernelGGL(act_quant_smooth_long_kernel<8>, dim3(ceil_div(M, 8)), dim3(LONG_WAVES * 64), 0, st, x, ldx, M, K, inv_smooth,
+                               xq_rm, xq_kl, sx);
+            return check_hip(hipGetLastError(), "act_quant (long rows) launch");
+        }
+    }
+    if constexpr (MODE == 3) {
+        if (K > ROW4_MAX_K) {
+            hipLaunchKernelGGL(act_quant_swiglu_long_kernel, grid, dim3(LONG_WAVES * 64), 0, st, x, ldx, M, K, xq_rm, xq_kl, sx);
+            return check_hip(hipGetLastError(), "act_quant (long rows) launch");
+        }
+    }
+#define QL_LAUNCH_ROW(NC)                                                                                                       \
+    hipLaunchKernelGGL((act_quant_kernel<MODE, NC>), grid, dim3(ceil_div(ceil_div(chunks, NC), 64) * 64), 0, st, x, ldx, M, K, inv_smooth, \
+                       gamma, eps, xq_rm, xq_kl, sx)
+    if (chunks <= ROW_CHUNKS) QL_LAUNCH_ROW(1);
+    else if (chunks <= 2 * ROW_CHUNKS) QL_LAUNCH_ROW(2);
+    else if (chunks <= 4 * ROW_CHUNKS) QL_LAUNCH_ROW(4);
+    else if constexpr (MODE == 0 || MODE == 2) QL_LAUNCH_ROW(8);   // the last: K <= 131072
+#undef QL_LAUNCH_ROW
     return check_hip(hipGetLastError(), "act_quant launch");
 }
 

@@ -73,6 +73,7 @@ __device__ inline uint4 quant_chunk_f32(const float (&v)[16], float inv)
 #pragma unroll
         for (int i = 0; i < 4; ++i) q[i] = code_word(v[4 * i] * inv, v[4 * i + 1] * inv, v[4 * i + 2] * inv, v[4 * i + 3] * inv);
     } else {
+        asm volatile("");               // or the compiler computes both sides for every token and selects
         auto clamped = [&](float x) { return fminf(fmaxf(x * inv, -127.0f), 127.0f); };
 #pragma unroll
         for (int i = 0; i < 4; ++i) q[i] = code_word(clamped(v[4 * i]), clamped(v[4 * i + 1]), clamped(v[4 * i + 2]), clamped(v[4 * i + 3]));

@@ -1,5 +1,6 @@
-"""The activation quantizer's kernel forms (a workgroup per token up to K = 16384, 8 tokens per workgroup above 3072 tokens,
-rows read twice beyond K = 16384) at their edges: codes and scales bit for bit against the oracle, every mode."""
+"""The activation quantizer's kernel forms (a workgroup per token with 1, 2, 4 or 8 chunks per lane, 8 tokens per workgroup
+above 3072 tokens, rows read twice where registers do not hold them) at their edges: codes and scales bit for bit against
+the oracle, every mode."""
 import numpy as np
 import pytest
 import torch
@@ -51,6 +52,23 @@ def _run(G, mode, x, vec, K):
                                  (3075, 1088), (3081, 12288), (3073, 12352)])
 @pytest.mark.parametrize("mode", ["plain", "smooth", "rmsnorm", "swiglu"])
 def test_forms_bit_exact(G, mode, M, K):
+    _check_form(G, mode, M, K)
+
+
+# long rows: the last K of 1, 2 and 4 chunks per lane and the first beyond, the longest K there is; SmoothQuant also around
+# the token counts where its 8-token form begins (2048, 513) and the last K of its 12-chunk form
+@pytest.mark.parametrize("M,K", [(9, 16448), (65, 28672), (3, 32768), (9, 32832), (2, 65536), (9, 65600), (1, 131072)])
+@pytest.mark.parametrize("mode", ["plain", "smooth", "rmsnorm", "swiglu"])
+def test_long_rows_bit_exact(G, mode, M, K):
+    _check_form(G, mode, M, K)
+
+
+@pytest.mark.parametrize("M,K", [(2047, 16448), (2048, 16448), (2051, 20480), (1, 65600), (17, 98304), (17, 98368), (513, 98368)])
+def test_long_smooth_rows_bit_exact(G, M, K):
+    _check_form(G, "smooth", M, K)
+
+
+def _check_form(G, mode, M, K):
     rng = np.random.default_rng(M * 7 + K)
     x = rng.standard_normal((M, 2 * K if mode == "swiglu" else K)).astype(np.float32)
     x[:, rng.integers(0, x.shape[1], 4)] *= 20
