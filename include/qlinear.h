@@ -200,7 +200,8 @@ int ql_w4a8_gemm_acc_i32(const int8_t *xq_kernel, int M, int K, const void *w4_k
  *   groups of 16 channels per workgroup; 111 sixteen wavefronts; 121 tokens never staged in LDS; 122 / 123 token
  *   blocks of 32 / 64; 130 quantizer never fused into the decode GEMM.  int4 weights have five tile forms of their own:
  *   6, 26 = 256x256; 15, 35 = 192x256 (tokens x channels); 4, 11, 13, 19, 20, 39 = 128x128; 23, 43 = 256x256 with the last
- *   third of the channels in 128x256 tiles; 202..232 split-K on 128x128; every other tile value = 128x256.
+ *   third of the channels in 128x256 tiles; 202..232 split-K on 128x128; 302..332 split-K on 128x256 (unsplit where the
+ *   scratch does not hold the partial sums); every other tile value = 128x256.
  *   Unknown values -> QL_ERR_UNSUPPORTED. */
 int ql_set_kernel_variant(int variant);
 

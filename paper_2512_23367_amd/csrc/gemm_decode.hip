@@ -658,13 +658,14 @@ int launch_one(const GemmArgs &a, hipStream_t st)
 struct BlockedPlan {
     int block, c;
     double us;
+    double passes, wg_bytes;   // of the pick
 };
 
 inline BlockedPlan plan_blocked(int M, int N, int K, bool w4, int force_block = 0)
 {
     const int groups = round_up(N, TILE_ROWS) / 16;
     static const int cs[] = {1, 2, 3, 4, 6, 8};
-    BlockedPlan best = {64, 1, 1e30};
+    BlockedPlan best = {64, 1, 1e30, 0.0, 0.0};
     for (int block = 64; block >= 32; block /= 2) {
         if (force_block && block != force_block) continue;
         const int blocks = ceil_div(M, block);
@@ -673,8 +674,9 @@ inline BlockedPlan plan_blocked(int M, int N, int K, bool w4, int force_block = 
             if (c > 4 && (w4 || block == 32)) continue;   // int4: register budget; 32-token kernels: 6 or 8 measured no faster
             if (w4 && (size_t)c * (K / 128) * 32 > 16384) continue;            // int4: staged scales
             const double passes = (double)ceil_div(ceil_div(groups, c) * blocks, 256);
-            const double us = 1.0 + passes * (2.5 + K * ((w4 ? 8.0 : 16.0) * c + tokens) / (c <= 4 ? 50e3 : 40e3));
-            if (us < best.us) best = {block, c, us};
+            const double wg_bytes = K * ((w4 ? 8.0 : 16.0) * c + tokens);
+            const double us = 1.0 + passes * (2.5 + wg_bytes / (c <= 4 ? 50e3 : 40e3));
+            if (us < best.us) best = {block, c, us, passes, wg_bytes};
         }
     }
     return best;
@@ -839,7 +841,10 @@ double decode_estimate_us(const GemmArgs &a)
     // up to 32 tokens: launch, first round trip and reduction + the weight stream at 90 % of nominal HBM bandwidth
     // (fits the measured 7B decode GEMMs within 10 %); from 33 tokens the blocked plan's model
     if (a.M <= 32) return 3.5 + (double)a.N * a.K * a.bits / 8.0 / 7.2e6;
-    return plan_blocked(a.M, a.N, a.K, a.bits == 4).us;
+    const BlockedPlan plan = plan_blocked(a.M, a.N, a.K, a.bits == 4);
+    // int4, for the comparison with the tile kernels: a pass costs more and its bytes less than the common model says (512 x 1024
+    // x 4096 12.4 us where it says 9.9, 768 x 11008 x 4096 64 where it says 72); within 8 % on 40 shapes of 96..1024 tokens
+    return a.bits == 4 && plan.passes > 0.0 ? 1.0 + plan.passes * (4.0 + plan.wg_bytes / 61.5e3) : plan.us;   // (no form fits: 1e30)
 }
 
 void decode_plan(const GemmArgs &a, int *token_block, int *channel_groups)

@@ -13,9 +13,10 @@
 // What bounds it: the vector port.  Measured on gfx950, matrix and vector instructions of a SIMD add up (16 cycles per
 // 16x16x64, 2 to 4 per vector operation whichever of the two wavefronts issues it), and the fold takes two operations per
 // accumulator element and group: in registers alone 4.2 POP/s of products become 2.9 with the fold and 2.5 with the unpack.
-// The loop below runs at 2.1 (2.02 us per stage of a 256 x 256 tile per CU, + ~7 us per tile).  The former kernel
-// (32x32x32, 64 x 64 wavefront tiles in two ping-pong groups, 128 x 256 only) took 2 x 1.07 us and 2 x 9 us for the same:
-// 4096 x 4096 x 12288 237 -> 217 us, 3001 x 4096 x 4096 74 -> 58 (192 x 256), 4096 x 11008 x 4096 205 -> 184.
+// The loop below runs at 2.1 (2.02 us per stage of a 256 x 256 tile per CU, + ~7 us per tile: whole kernels at 1.9).  The
+// 32x32x32 kernel further down (64 x 64 wavefront tiles in two ping-pong groups, 128 x 256 tiles) takes 2 x 1.07 us and 2 x 9
+// us for the same: 4096 x 4096 x 12288 237 against 217 us, 3001 x 4096 x 4096 74 against 58 (192 x 256), 4096 x 11008 x
+// 4096 205 against 184 -- it is the better one where 128 x 256 tiles fit one pass.
 // Per wavefront the 8 multiplies of a token block and its 32 fold operations stay in clusters: interleaving them,
 // folding a block late, fp32 scales instead of mixed-precision multiply-adds and wave priorities all measured the
 // same or slower.
@@ -44,6 +45,34 @@ struct W4Params {
     void *part;              // split-K: partial sums [split][workgroup][wavefront][channel block][token block][64 lanes x 16 B]
     int stages_per_split;    // split-K: blockIdx.y takes stages [y * stages_per_split, ...); otherwise all of them
 };
+
+// Writes a wavefront's staged block of 32 tokens to y, 16 bytes per lane (LPR lanes per row).
+template <int LPR>
+__device__ __forceinline__ void store_rows(const W4Params &p, const char *stg, int row_bytes, int m0, int n0, int lane)
+{
+    constexpr int RPI = 64 / LPR;
+    static_assert(64 % LPR == 0 && 32 % RPI == 0, "whole rows per read-back instruction");
+    asm volatile("" ::: "memory");   // (same wavefront, LDS operations complete in order: only the compiler must keep them so)
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < 32 / RPI; ++t) {
+        const int row = t * RPI + lane / LPR, c = lane % LPR;
+        const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * row_bytes + c * 16);
+        const int mm = m0 + row, nn = n0 + c * 8;
+        if (mm < p.M && nn < p.N) {
+            __half *dst = p.y + (size_t)mm * p.ldy + nn;
+            if (nn + 7 < p.N) {
+                *reinterpret_cast<uint4 *>(dst) = v;
+            } else {
+                const unsigned w[4] = {v.x, v.y, v.z, v.w};
+                for (int e = 0; e < 8 && nn + e < p.N; ++e)
+                    dst[e] = __ushort_as_half((unsigned short)(w[e / 2] >> (16 * (e % 2))));
+            }
+        }
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
 
 // One workgroup tile: WAVES_M x WAVES_N wavefronts of 16 TB tokens x 16 CB channels; (tm, tn): the tile's position in
 // units of its own size.
@@ -254,9 +283,6 @@ __device__ __forceinline__ void w4_tile(const W4Params &p, int tm, int tn, char 
     }
 
     constexpr int ROW_BYTES = CB * 16 * 2 + 16;
-    constexpr int LPR = CB * 2;
-    constexpr int RPI = 64 / LPR;
-    static_assert(64 % LPR == 0 && 32 % RPI == 0, "whole rows per read-back instruction");
     static_assert(NW * 32 * ROW_BYTES <= STAGES * STAGE_BYTES, "staging patch fits the pipeline buffers");
     __syncthreads();
     char *stg = smem + wave * (32 * ROW_BYTES);
@@ -285,26 +311,7 @@ __device__ __forceinline__ void w4_tile(const W4Params &p, int tm, int tn, char 
                 *reinterpret_cast<h4 *>(stg + (jj * 16 + r) * ROW_BYTES + (i * 16 + 4 * ch) * 2) = o;
             }
         }
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int t = 0; t < 32 / RPI; ++t) {
-            const int row = t * RPI + lane / LPR, c = lane % LPR;
-            const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * ROW_BYTES + c * 16);
-            const int mm = m_wave0 + jb * 32 + row, nn = n_wave0 + c * 8;
-            if (mm < p.M && nn < p.N) {
-                __half *dst = p.y + (size_t)mm * p.ldy + nn;
-                if (nn + 7 < p.N) {
-                    *reinterpret_cast<uint4 *>(dst) = v;
-                } else {
-                    const unsigned w[4] = {v.x, v.y, v.z, v.w};
-                    for (int e = 0; e < 8 && nn + e < p.N; ++e)
-                        dst[e] = __ushort_as_half((unsigned short)(w[e / 2] >> (16 * (e % 2))));
-                }
-            }
-        }
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_wave_barrier();
+        store_rows<CB * 2>(p, stg, ROW_BYTES, m_wave0 + jb * 32, n_wave0, lane);
     }
 }
 
@@ -340,6 +347,191 @@ __global__ __launch_bounds__(512, 1) void gemm_w4_tail_kernel(W4Params p)
     }
 }
 
+// 128 x 256 tiles on the 32x32x32 instruction: 8 wavefronts of 64 x 64 in two ping-pong groups (w and w + 4, one of each per
+// SIMD) one phase apart -- while one reads a stage's fragments, folds the previous group's int32 sums (accf += float(sum) *
+// scale) and waits for its loads, the other unpacks and multiplies; every phase ends with the workgroup barrier.  A 64 x 64
+// wavefront tile has nothing to gain from transient sums (its unpacking is per 64 tokens either way), and the two
+// phases cover each other's LDS and barrier latency, which counts where a launch is one pass over part of the CUs: against the
+// 16x16x64 loop on the same tile 512 x 4096 x 12288 43.3 -> 37.6 us, 1536 x 11008 x 4096 104 -> 89, 3001 x 6144 x 1536
+// 58.8 -> 50.2, with all 256 CUs busy (2048 x 4096 x 4096) 45.6 -> 42.2.
+constexpr int PP_STAGES = 4, PP_TM = 128, PP_TN = 256, PP_THREADS = 512;
+constexpr int PP_STAGE_BYTES = (PP_TM / 32 * 4 + PP_TN / 32 * 2) * 1024;
+constexpr int PP_SLOTS = 8;                               // ring of scale slots: a group's scales are read one stage later than its fragments
+constexpr int PP_LDS = PP_STAGES * PP_STAGE_BYTES + 2 * PP_THREADS * 4 + PP_SLOTS * 8 * 256;
+
+template <bool SPLIT>   // split-K: raw partial sums [split][workgroup][wavefront][channel block][token block][quad][64 lanes x 16 B]
+__global__ __launch_bounds__(PP_THREADS, 1) void gemm_w4_pp_kernel(W4Params p)
+{
+    typedef int v16i __attribute__((ext_vector_type(16)));
+    constexpr int NW = 8, WB = 2;                            // 32-row blocks of a wavefront tile, either way
+    constexpr int XFR = PP_TM / 32 * 4, WOFF = XFR * 1024, FR = PP_STAGE_BYTES / 1024, LPW = FR / NW + 1;
+    static_assert(FR % NW == 0 && XFR % NW == 0 && PP_TM <= PP_THREADS && PP_TN <= PP_THREADS, "equal shares");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    float *side_sx = reinterpret_cast<float *>(smem + PP_STAGES * PP_STAGE_BYTES);
+    float *side_b = side_sx + PP_THREADS;
+    char *scale_slots = reinterpret_cast<char *>(side_b + PP_THREADS);    // [slot][wavefront] 256 bytes
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave % 2, wn = wave / 2;
+    int tm, tn;
+    tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+
+    // epilogue operands: requested in front of the first stages, stored to LDS behind them
+    int r_sx = 0;
+    short r_b = 0;
+    if (!SPLIT) {
+        r_sx = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(p.sx, (unsigned)p.M * 4u), (unsigned)(tm * PP_TM + threadIdx.x) * 4u, 0, 0);
+        r_b = __builtin_amdgcn_raw_buffer_load_b16(make_rsrc(p.bias, p.bias ? (unsigned)p.N * 2u : 0u), (unsigned)(tn * PP_TN + threadIdx.x) * 2u, 0, 0);
+    }
+    const int stage0 = SPLIT ? blockIdx.y * p.stages_per_split : 0;
+    const int nstages = SPLIT ? min(p.stages_per_split, p.K / 128 - stage0) : p.K / 128;
+    const unsigned lane16 = lane * 16, KB = p.K / 32;
+    auto issue_stage = [&](int s) {                          // as in w4_tile; the scales of a wavefront's 64 channels into a slot of its own
+        const bool live = s < nstages;
+        const __amdgpu_buffer_rsrc_t xr = make_rsrc(p.xq, live ? p.x_bytes : 0u);
+        const __amdgpu_buffer_rsrc_t wr = make_rsrc(p.wq, live ? p.w_bytes : 0u);
+        char *buf = smem + (s % PP_STAGES) * PP_STAGE_BYTES;
+#pragma unroll
+        for (int i = 0; i < FR / NW; ++i) {
+            const int f = i * NW + wave;
+            if (i < XFR / NW) {
+                const unsigned off = ((unsigned)(tm * (PP_TM / 32) + f / 4) * KB + (stage0 + s) * 4 + f % 4) * 1024u;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, LDS_PTR(buf + f * 1024), 16, lane16 + off, 0, 0, 0);
+            } else {
+                const int g = f - XFR;
+                const unsigned off = ((unsigned)(tn * (PP_TN / 32) + g / 2) * (KB / 2) + (stage0 + s) * 2 + g % 2) * 1024u;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, LDS_PTR(buf + f * 1024), 16, lane16 + off, 0, 0, 0);
+            }
+        }
+        const __amdgpu_buffer_rsrc_t sr = make_rsrc(p.wscales, live ? p.s_bytes : 0u);
+        const unsigned off = ((unsigned)(stage0 + s) * p.Npad + tn * PP_TN + wn * 64) * 2u;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(sr, LDS_PTR(scale_slots + ((s % PP_SLOTS) * NW + wave) * 256), 4, lane * 4 + off, 0, 0, 0);
+    };
+
+    // element 4 q + e of a 32x32 block (i, j): channel 8 q + 4 (lane / 32) + e, token lane % 32
+    v16i acc[WB][WB];
+    float accf[WB][WB][16];
+    h4 sg[WB][4];                                            // scales of the group whose sums sit in acc
+#pragma unroll
+    for (int i = 0; i < WB; ++i) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sg[i][q] = h4{0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < WB; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0, accf[i][j][r] = 0.0f;
+    }
+    const v16i zero16 = acc[0][0];
+    auto read_scales = [&](int g) {
+        const char *slot = scale_slots + ((g % PP_SLOTS) * NW + wave) * 256;
+#pragma unroll
+        for (int i = 0; i < WB; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) sg[i][q] = *reinterpret_cast<const h4 *>(slot + (i * 32 + 8 * q + 4 * (lane >> 5)) * 2);
+    };
+    auto fold = [&]() {
+#pragma unroll
+        for (int i = 0; i < WB; ++i)
+#pragma unroll
+            for (int j = 0; j < WB; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) accf[i][j][r] = __builtin_fmaf((float)acc[i][j][r], (float)sg[i][r / 4][r % 4], accf[i][j][r]);
+    };
+
+#pragma unroll
+    for (int s = 0; s < PP_STAGES - 1; ++s) issue_stage(s);
+    if (!SPLIT) {                                            // (entries beyond the tile are not used)
+        side_sx[threadIdx.x] = __int_as_float(r_sx);
+        side_b[threadIdx.x] = __half2float(__ushort_as_half((unsigned short)r_b));
+    }
+
+    const bool late = wave >= NW / 2;
+    v4i wp[2][WB], xf[4][WB];
+    wait_vmcnt<(PP_STAGES - 2) * LPW>();                     // stage 0 has landed (this wavefront's part)
+    __builtin_amdgcn_s_barrier();                            // ... everyone's
+    if (late) __builtin_amdgcn_s_barrier();                  // phase shift
+    for (int it = 0; it < nstages; ++it) {
+        // ---- memory phase
+        const char *buf = smem + (it % PP_STAGES) * PP_STAGE_BYTES;
+        if (it > 0) read_scales(it - 1);
+#pragma unroll
+        for (int kp = 0; kp < 2; ++kp)
+#pragma unroll
+            for (int i = 0; i < WB; ++i) wp[kp][i] = *reinterpret_cast<const v4i *>(buf + WOFF + ((wn * WB + i) * 2 + kp) * 1024 + lane16);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int j = 0; j < WB; ++j) xf[kb][j] = *reinterpret_cast<const v4i *>(buf + ((wm * WB + j) * 4 + kb) * 1024 + lane16);
+        issue_stage(it + PP_STAGES - 1);                     // into the buffer of stage it - 1: both groups have read it
+        fold();                                              // group it - 1 (the first time: zeros)
+        __builtin_amdgcn_sched_barrier(0);                   // the fold stays in front of the wait: it covers the loads' latency
+        wait_vmcnt<(PP_STAGES - 2) * LPW>();                 // own loads of stage it + 1 have landed
+        __builtin_amdgcn_s_waitcnt(0xC07F);                  // lgkmcnt(0): fragments are in registers, the buffer may be refilled
+        __builtin_amdgcn_s_barrier();
+        // ---- compute phase
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int i = 0; i < WB; ++i) {
+                const unsigned w0 = (unsigned)wp[kb / 2][i][2 * (kb % 2)], w1 = (unsigned)wp[kb / 2][i][2 * (kb % 2) + 1];
+                v4i wf;
+                wf[0] = (int)((w0 << 4) & 0xF0F0F0F0u);
+                wf[1] = (int)(w0 & 0xF0F0F0F0u);
+                wf[2] = (int)((w1 << 4) & 0xF0F0F0F0u);
+                wf[3] = (int)(w1 & 0xF0F0F0F0u);
+#pragma unroll
+                for (int j = 0; j < WB; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf, xf[kb][j], kb == 0 ? zero16 : acc[i][j], 0, 0, 0);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+    }
+    if (!late) __builtin_amdgcn_s_barrier();
+    read_scales(nstages - 1);
+    fold();
+    wait_vmcnt<0>();                                         // drain the dead tail loads before the LDS is reused
+
+    if constexpr (SPLIT) {
+        char *dst = static_cast<char *>(p.part) + (((size_t)blockIdx.y * gridDim.x + blockIdx.x) * NW + wave) * (size_t)(WB * WB * 4096);
+#pragma unroll
+        for (int i = 0; i < WB; ++i)
+#pragma unroll
+            for (int j = 0; j < WB; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4 *>(dst + ((i * WB + j) * 4 + q) * 1024 + lane16) =
+                        float4{accf[i][j][4 * q], accf[i][j][4 * q + 1], accf[i][j][4 * q + 2], accf[i][j][4 * q + 3]};
+        return;
+    }
+    constexpr int ROW_BYTES = WB * 64 + 16;
+    static_assert(NW * 32 * ROW_BYTES <= PP_STAGES * PP_STAGE_BYTES, "staging patch fits the pipeline buffers");
+    __syncthreads();
+    char *stg = smem + wave * (32 * ROW_BYTES);
+    const int n_wave0 = tn * PP_TN + wn * 64, m_wave0 = tm * PP_TM + wm * 64;
+#pragma unroll
+    for (int j = 0; j < WB; ++j) {
+        const float sxm = side_sx[(wm * WB + j) * 32 + (lane & 31)] * 0.0625f;
+#pragma unroll
+        for (int i = 0; i < WB; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 b = *reinterpret_cast<const float4 *>(side_b + (wn * WB + i) * 32 + 8 * q + 4 * (lane >> 5));
+                const float b4[4] = {b.x, b.y, b.z, b.w};
+                h4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float v = __builtin_fmaf(accf[i][j][4 * q + e], sxm, b4[e]);
+                    asm("" : "+v"(v));   // rounded to fp32, then to fp16, in every kernel variant
+                    o[e] = (_Float16)v;
+                }
+                *reinterpret_cast<h4 *>(stg + (lane & 31) * ROW_BYTES + (i * 32 + 8 * q + 4 * (lane >> 5)) * 2) = o;
+            }
+        store_rows<WB * 4>(p, stg, ROW_BYTES, m_wave0 + j * 32, n_wave0, lane);
+    }
+}
+
 // Split-K, second kernel: adds the splits' fp32 partial sums, split 0 first, then the dequantization of the fused
 // epilogue.  A workgroup per wavefront of the first kernel, a quarter of its 16 x 16 blocks per wavefront; all loads of a
 // split are issued before the first is used.
@@ -352,7 +544,8 @@ struct W4FinishParams {
     int M, N, tiles_m, tiles_n, group_m, splits;
 };
 
-template <int WAVES_M, int WAVES_N, int TB, int CB>
+// SQUARE32: the blocks of 1024 bytes are quads of 32x32 blocks (gemm_w4_pp_kernel) instead of 16x16 blocks; TB, CB as there.
+template <int WAVES_M, int WAVES_N, int TB, int CB, bool SQUARE32 = false>
 __global__ __launch_bounds__(256) void w4_finish_kernel(W4FinishParams f)
 {
     constexpr int NW = WAVES_M * WAVES_N, BLOCKS = CB * TB, PER = BLOCKS / 4;
@@ -375,8 +568,15 @@ __global__ __launch_bounds__(256) void w4_finish_kernel(W4FinishParams f)
     }
 #pragma unroll
     for (int b = 0; b < PER; ++b) {
-        const int i = (part * PER + b) / TB, j = (part * PER + b) % TB;
-        const int m = ((tm * WAVES_M + wm) * TB + j) * 16 + (lane & 15), n0 = ((tn * WAVES_N + wn) * CB + i) * 16 + 4 * (lane >> 4);
+        const int at = part * PER + b;
+        int m, n0;
+        if (SQUARE32) {
+            const int i = at / (2 * TB), j = at / 4 % (TB / 2), q = at % 4;
+            m = ((tm * WAVES_M + wm) * (TB / 2) + j) * 32 + (lane & 31), n0 = ((tn * WAVES_N + wn) * (CB / 2) + i) * 32 + 8 * q + 4 * (lane >> 5);
+        } else {
+            const int i = at / TB, j = at % TB;
+            m = ((tm * WAVES_M + wm) * TB + j) * 16 + (lane & 15), n0 = ((tn * WAVES_N + wn) * CB + i) * 16 + 4 * (lane >> 4);
+        }
         if (m >= f.M || n0 >= f.N) continue;
         const float sxm = f.sx[m] * 0.0625f;
         const float a[4] = {v[b].x, v[b].y, v[b].z, v[b].w};
@@ -459,6 +659,31 @@ int launch_w4(const GemmArgs &a, hipStream_t st, int splits = 1)
     return check_hip(hipGetLastError(), "w4_finish launch");
 }
 
+inline size_t pp_split_bytes(const GemmArgs &a, int splits) { return (size_t)splits * ceil_div(a.M, PP_TM) * ceil_div(a.N, PP_TN) * PP_TM * PP_TN * 4; }
+
+template <bool SPLIT>
+int launch_w4_pp(const GemmArgs &a, hipStream_t st, int splits = 1)
+{
+    static_assert(PP_LDS <= 160 * 1024, "LDS budget");
+    static const int attr_status = set_lds(gemm_w4_pp_kernel<SPLIT>, PP_LDS);
+    if (attr_status != QL_OK) return attr_status;
+    W4Params p = w4_params(a);
+    p.tiles_m = ceil_div(a.M, PP_TM);
+    p.tiles_n = ceil_div(a.N, PP_TN);
+    p.group_m = strip_height(p.tiles_m, p.tiles_n, PP_TM * 2, PP_TN, 1);
+    p.stages_per_split = ceil_div(a.K / 128, splits);
+    splits = ceil_div(a.K / 128, p.stages_per_split);   // no empty split
+    if (SPLIT && (!a.ws || pp_split_bytes(a, splits) > a.ws_bytes))
+        return fail(QL_ERR_WORKSPACE, "split-K needs %zu bytes of workspace", pp_split_bytes(a, splits));
+    p.part = a.ws;
+    hipLaunchKernelGGL(gemm_w4_pp_kernel<SPLIT>, dim3(p.tiles_m * p.tiles_n, splits), dim3(PP_THREADS), PP_LDS, st, p);
+    QL_TRY(check_hip(hipGetLastError(), "gemm_w4_pp launch"));
+    if (!SPLIT) return QL_OK;
+    W4FinishParams f = {static_cast<const float *>(a.ws), a.sx, a.bias, a.y, a.ldy, a.M, a.N, p.tiles_m, p.tiles_n, p.group_m, splits};
+    hipLaunchKernelGGL((w4_finish_kernel<2, 4, 4, 4, true>), dim3(p.tiles_m * p.tiles_n * 8), dim3(256), 0, st, f);
+    return check_hip(hipGetLastError(), "w4_finish launch");
+}
+
 // the first `first_tiles` channel tiles in 256 x 256 tiles, the rest in 128 x 256 (0 < first_tiles < all of them)
 int launch_w4_tail(const GemmArgs &a, int first_tiles, hipStream_t st)
 {
@@ -481,12 +706,16 @@ int launch_w4_tail(const GemmArgs &a, int first_tiles, hipStream_t st)
 
 // The automatic choice.  Estimated time of a tile shape: 3 us + passes over the 256 CUs x (o + stages x c), fitted to 25
 // shapes (64..8192 tokens, N 1536..22016, K 1536..16384; weights from HBM, every CU busy):
-//   256 x 256  o 7  c 2.02;   192 x 256  5.5  1.55;   128 x 256  5  1.10   (one workgroup per CU)
+//   256 x 256  o 7  c 2.02;   192 x 256  5  1.60;   128 x 256 (ping-pong)  3  1.12, a last pass of at most 224 tiles 2.5  1.00
 //   128 x 128  0.5  0.78 alone on its CU, 4  1.12 for two per CU; a last pass of at most 256 tiles runs alone
-// (operations per us of a full pass at K = 4096: 119, 113, 109, 106 GOP -- the largest tile wins where it fills its passes).
-// Combined form: p whole passes of 256 x 256, the remaining channels in 128 x 256 tiles.  Split-K (few tiles, long K) on
-// 128 x 128 tiles: + 8 us and 0.16 us per MB of partial sums for the second kernel; taken when 10 % ahead.
-enum W4Shape { W4_256 = 26, W4_192 = 35, W4_128X256 = 37, W4_128 = 13, W4_TAIL = 43, W4_SPLIT = 200 };   // ql_set_kernel_variant values
+// (operations per us of a full pass at K = 4096: 119, 113, 106, 106 GOP -- the largest tile wins where it fills its passes; a
+// launch that leaves CUs idle runs at a higher clock).  Over 165 shapes (96..4096 tokens, N 1536..22016, K 1024..11008) the
+// pick is within 0.3 % of the fastest form on average, 5 % at worst.
+// Combined form: p whole passes of 256 x 256, the remaining channels in 128 x 256 tiles (c 1.10, o 5: the 16x16x64 loop).
+// Split-K (few tiles, long K), taken when 10 % ahead: on 128 x 128 tiles + 8 us and 0.16 us per MB of partial sums for the second
+// kernel; on 128 x 256 tiles, one pass, 8.8 us + stages x 0.87 + 0.43 us per MB, both kernels (144 splits, within 5 % on
+// average; 1536 x 6144 x 1536 32 us, 128 x 128 unsplit 39; 512 x 11008 x 4096 42, split on 128 x 128 44).
+enum W4Shape { W4_256 = 26, W4_192 = 35, W4_128X256 = 37, W4_128 = 13, W4_TAIL = 43, W4_SPLIT = 200, W4_SPLIT256 = 300 };   // ql_set_kernel_variant values
 
 struct W4Choice {
     int shape, splits, first_tiles;
@@ -501,6 +730,12 @@ inline double w4_128_us(long tiles, int stages)
     return (double)(tiles / 512 + (rest > 256)) * (4.0 + 1.12 * stages) + (rest > 0 && rest <= 256 ? 0.5 + 0.78 * stages : 0.0);
 }
 
+inline double w4_pp_us(long tiles, int stages)
+{
+    const long rest = tiles % 256, full = tiles / 256 + (rest > 224);
+    return (double)full * (3.0 + 1.12 * stages) + (rest > 0 && rest <= 224 ? 2.5 + 1.0 * stages : 0.0);
+}
+
 inline W4Choice choose_w4(const GemmArgs &a, size_t scratch, bool dump_partials)
 {
     const int stages = a.K / 128;
@@ -509,8 +744,8 @@ inline W4Choice choose_w4(const GemmArgs &a, size_t scratch, bool dump_partials)
     auto offer = [&](int shape, int first, double us, double ahead) {
         if (us < best.us * ahead) best = {shape, 1, first, us};
     };
-    offer(W4_192, 0, 3.0 + w4_passes(tiles(192, 256), 5.5, 1.55, stages), 0.99);
-    offer(W4_128X256, 0, 3.0 + w4_passes(tiles(128, 256), 5.0, 1.10, stages), 0.99);
+    offer(W4_192, 0, 3.0 + w4_passes(tiles(192, 256), 5.0, 1.60, stages), 0.99);
+    offer(W4_128X256, 0, 3.0 + w4_pp_us(tiles(128, 256), stages), 0.99);
     offer(W4_128, 0, 3.0 + w4_128_us(tiles(128, 128), stages), 0.99);
     const int tm = ceil_div(a.M, 256), tn = ceil_div(a.N, 256);
     for (int p = 1; p * 256 / tm < tn && p * 256 >= tm; ++p) {   // (fewer than 256 token tiles: whole columns fit a pass)
@@ -521,10 +756,12 @@ inline W4Choice choose_w4(const GemmArgs &a, size_t scratch, bool dump_partials)
     if (scratch && !dump_partials) {
         W4Choice split = {W4_SPLIT, 1, 0, 1e30};
         for (int s = 2; s <= 32 && stages / s >= 4; ++s) {
-            const size_t bytes = (size_t)s * tiles(128, 128) * 128 * 128 * 4;
-            if (bytes > scratch) break;
-            const double us = 11.0 + w4_128_us(tiles(128, 128) * s, ceil_div(stages, s)) + 0.16e-6 * bytes;
-            if (us < split.us) split = {W4_SPLIT, s, 0, us};
+            auto consider = [&](int shape, size_t bytes, double us) {
+                if (bytes <= scratch && us < split.us) split = {shape, s, 0, us};
+            };
+            const size_t b128 = (size_t)s * tiles(128, 128) * 128 * 128 * 4, b256 = pp_split_bytes(a, s);
+            consider(W4_SPLIT, b128, 11.0 + w4_128_us(tiles(128, 128) * s, ceil_div(stages, s)) + 0.16e-6 * b128);
+            if (tiles(128, 256) * s <= 256) consider(W4_SPLIT256, b256, 8.8 + 0.87 * ceil_div(stages, s) + 0.43e-6 * b256);
         }
         if (split.us < best.us * 0.9) best = split;
     }
@@ -539,7 +776,7 @@ void prefill_w4_plan(const GemmArgs &a, int *variant, int *tile_tokens, int *til
 {
     const W4Choice c = choose_w4(a, a.ws ? a.ws_bytes : 0, a.partials != nullptr);
     *splits = c.splits;
-    *variant = c.shape == W4_SPLIT ? 200 + c.splits : c.shape;
+    *variant = c.shape >= W4_SPLIT ? c.shape + c.splits : c.shape;
     *tile_tokens = c.shape == W4_256 || c.shape == W4_TAIL ? 256 : c.shape == W4_192 ? 192 : 128;
     *tile_channels = c.shape == W4_128 || c.shape == W4_SPLIT ? 128 : 256;
 }
@@ -555,7 +792,9 @@ int launch_gemm_prefill_w4(const GemmArgs &a, int variant, hipStream_t st)
     case 15: case 35: c.shape = W4_192; break;
     case 4: case 11: case 13: case 19: case 20: case 39: c.shape = W4_128; break;
     case 23: case 43: c = {W4_TAIL, 1, (2 * ceil_div(a.N, 256) + 2) / 3, 0.0}; break;   // two thirds of the channel tiles in front
-    default: if (variant >= 202 && variant <= 232) c = {W4_SPLIT, variant - 200, 0, 0.0};
+    default:
+        if (variant >= 202 && variant <= 232) c = {W4_SPLIT, variant - 200, 0, 0.0};
+        if (variant >= 302 && variant <= 332 && a.ws && pp_split_bytes(a, variant - 300) <= a.ws_bytes) c = {W4_SPLIT256, variant - 300, 0, 0.0};
     }
     if (c.shape == W4_TAIL && c.first_tiles >= ceil_div(a.N, 256)) c.shape = W4_256;
     switch (c.shape) {
@@ -564,7 +803,8 @@ int launch_gemm_prefill_w4(const GemmArgs &a, int variant, hipStream_t st)
     case W4_128: return launch_w4<2, 4, 4, 2, 3, EPI_F16, 2>(a, st);
     case W4_TAIL: return launch_w4_tail(a, c.first_tiles, st);
     case W4_SPLIT: return launch_w4<2, 4, 4, 2, 3, EPI_PART, 2>(a, st, c.splits);
-    default: return launch_w4<2, 4, 4, 4, 4, EPI_F16, 1>(a, st);
+    case W4_SPLIT256: return launch_w4_pp<true>(a, st, c.splits);
+    default: return launch_w4_pp<false>(a, st);
     }
 }
 

@@ -30,8 +30,8 @@ def test_shapes_agree_with_the_oracle(G, M, K, N, bias):
     ref = oracle.linear_w4a8(x, g["canon"], g["scales"], 128, b)["y64"]
     outs = {}
     try:
-        for v in UNSPLIT + [0, 2, 202, 203]:
-            if v in (202, 203) and K < 1024:
+        for v in UNSPLIT + [0, 2, 202, 203, 302, 303]:
+            if v > 200 and K < 1024:
                 continue                                   # (at least one stage per split)
             ql.ql_set_kernel_variant(v)
             outs[v] = G.gpu_linear(x, g, b, extra_ws=64 << 20)
