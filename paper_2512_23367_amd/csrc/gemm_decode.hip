@@ -686,10 +686,26 @@ inline BlockedPlan plan_blocked(int M, int N, int K, bool w4, int force_block = 
 // The token fragments are re-read from L2 by every workgroup; their traffic relative to the weight
 // stream is (tokens rounded up to 16) / (16 * C).  More channel groups per workgroup cut it, at the
 // price of fewer workgroups, so C grows with M and shrinks again when N is too small to fill 256 CUs.
-inline void auto_shape(int M, int N, int K, bool w4, int force_block, int &block, int &c)
+// fused: int8 weights and the quantizer in the prologue (fused_slots).
+inline void auto_shape(int M, int N, int K, bool w4, int force_block, int &block, int &c, bool fused = false)
 {
     const int groups = round_up(N, TILE_ROWS) / 16;
-    if (M <= 16) {
+    if (fused && !w4) {
+        // The busiest CU: n workgroups, each 16 c K bytes of weights and 2 M K of fp16 tokens.  Alone on its CU a workgroup's
+        // ring (64 KB, whatever c is) is all that is in flight -- 18 KB/us behind the first 32 KB; two and more reach 27; four groups
+        // (the ring is two fragments deep) 17 and 22; every further workgroup costs 1 us of start and reduction.
+        // 404 shapes (1..16 tokens, N 2048..32768, K 1024..12288; weights from HBM): the pick is within 1.3 % of the best c
+        // on average, and at most 6 % slower than the better of quantizer + GEMM and the former fused rule.  The rounds below would take c = 2 in one round for 8192 x 8192, one token: 15.6 us; c = 1 in
+        // two 13.0.  At short K it is the other way round (2048 x 8192: 5.6 in one round, 7.1).
+        block = 16, c = 1;
+        double best = 1e30;
+        for (int cand = 1; cand <= 4; ++cand) {
+            const int n = ceil_div(ceil_div(groups, cand), 256);
+            const double kb = n * (16.0 * cand + 2.0 * M) * K / 1024.0;
+            const double us = n == 1 ? (kb > 32.0 ? kb - 32.0 : 0.0) / (cand == 4 ? 17.0 : 18.0) : kb / (cand == 4 ? 22.0 : 27.0) + (n - 1) * 1.0;
+            if (us < best * 0.999) best = us, c = cand;
+        }
+    } else if (M <= 16) {
         // Every workgroup streams c channel groups (16 c channels x K weight bytes) plus the tokens (M x K bytes); all
         // workgroups are resident at once up to two per CU, beyond that the rest is handed out as CUs free up.  The
         // busiest CU decides: rounds x bytes per workgroup, in units of one channel group's weights.  Measured on the
@@ -703,9 +719,9 @@ inline void auto_shape(int M, int N, int K, bool w4, int force_block, int &block
             if (w4 && (size_t)cand * (K / 128) * 32 > 16384) break;      // int4: staged scales
             const int wgs = ceil_div(groups, cand);
             const double rounds = wgs <= 512 ? (double)ceil_div(wgs, 256) : wgs / 256.0 + 1.0;
-            // (int8 and long rows: four groups leave the register ring two fragments deep and one workgroup per CU pulls too
-            // few bytes at a time -- 4096 x 14336, one token: 12.3 us with two groups per workgroup, 15.7 with four)
-            const double cost = rounds * (cand + tokens) * (!w4 && cand == 4 && K >= 4096 ? 1.12 : 1.0);
+            // (int8: four groups leave the register ring two fragments deep -- K x N, four against two groups per workgroup, GEMM of
+            // one token: 1024 x 14336 5.6 / 5.5 us, 3072 x 14336 10.4 / 9.5, 4096 x 16384 16.8 / 13.1, 8192 x 14336 27.0 / 21.3)
+            const double cost = rounds * (cand + tokens) * (!w4 && cand == 4 ? 1.12 : 1.0);
             if (cost < best * 0.999) best = cost, c = cand;
         }
     } else if (M <= 32) {
@@ -753,7 +769,7 @@ int by_m(const GemmArgs &a, int variant, hipStream_t st)
 {
     const int groups = round_up(a.N, TILE_ROWS) / 16;
     int block, c;
-    auto_shape(a.M, a.N, a.K, W4, variant == 122 ? 32 : variant == 123 ? 64 : 0, block, c);
+    auto_shape(a.M, a.N, a.K, W4, variant == 122 ? 32 : variant == 123 ? 64 : 0, block, c, a.x != nullptr);
     if (variant == 101 || variant == 111) c = 1;
     if (variant == 102 && (!W4 || (size_t)2 * (a.K / 128) * 32 <= 16384)) c = 2;
     if (variant == 103 && (!W4 || (size_t)3 * (a.K / 128) * 32 <= 16384)) c = 3;
@@ -828,10 +844,13 @@ bool decode_fuses_quant(int M, int N, int K, int bits, int variant)
 {
     const int slots = fused_slots(M, K);
     if (!slots || variant == 121 || variant == 130) return false;
-    if (bits == 4 && slots == 4 && M > 8) {   // int4 on 16 wavefronts, 9 to 16 tokens: 6.9 us fused, 6.3 not (2048 x 2048)
+    if (slots == 4 && M > 8) {
+        // 9 to 16 tokens, at most 256 channel groups (us, fused / quantizer and GEMM; 16 tokens, K x N): int4 on 16 wavefronts
+        // 2048 x 2048 6.9 / 6.3; int8 2048 x 3072 6.9 / 6.6, 1536 x 4096 6.5 / 6.4 -- beyond them 2048 x 6144 6.6 / 7.6,
+        // 1536 x 8192 6.4 / 7.3, 2048 x 24576 13.6 / 13.4
         int block, c;
-        auto_shape(M, N, K, true, 0, block, c);
-        return !sixteen_wavefronts(N, c);
+        auto_shape(M, N, K, bits == 4, 0, block, c);
+        return bits == 4 ? !sixteen_wavefronts(N, c) : round_up(N, TILE_ROWS) / 16 > 256;
     }
     return true;
 }
