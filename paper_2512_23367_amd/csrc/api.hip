@@ -138,7 +138,7 @@ int run_gemm(GemmArgs &a, hipStream_t st)
 
 int gemm_common(const int8_t *xq, const float *sx, int M, int K, const void *wq, const float *sw, int bits,
                 int group, const void *bias, int N, void *y, int64_t ldy, void *ws, size_t ws_bytes,
-                hipStream_t st)
+                hipStream_t st, bool as_fused = false)
 {
     QL_TRY(check_bits(bits, group));
     QL_TRY(check_mk(M, K));
@@ -164,6 +164,7 @@ int gemm_common(const int8_t *xq, const float *sx, int M, int K, const void *wq,
     a.group = group;
     a.ws = ws;
     a.ws_bytes = ws_bytes;
+    a.as_fused = as_fused;
     return run_gemm(a, st);
 }
 
@@ -188,8 +189,8 @@ int linear_common(const void *x, int64_t ldx, int M, int K, const void *wq, cons
     if (!aligned(wq, 256) || (sw && !aligned(sw, 16)) || (bias && !aligned(bias, 16)))
         return fail(QL_ERR_ALIGN, "wq needs 256-byte, sw/bias 16-byte alignment");
     QL_TRY(check_out(y, ldy, N));
-    if (M <= DECODE_MAX_M && (g_variant == 0 || (g_variant >= 100 && g_variant < 200)) && decode_fuses_quant(M, N, K, bits, g_variant) &&
-        !rows_overlap(x, ldx, K, y, ldy, N, M)) {
+    const bool fuses = M <= DECODE_MAX_M && (g_variant == 0 || (g_variant >= 100 && g_variant < 200)) && decode_fuses_quant(M, N, K, bits, g_variant);
+    if (fuses && !rows_overlap(x, ldx, K, y, ldy, N, M)) {
         // few tokens: the decode GEMM quantizes them itself, one launch instead of two
         GemmArgs a = {};
         a.x = static_cast<const __half *>(x);
@@ -209,7 +210,7 @@ int linear_common(const void *x, int64_t ldx, int M, int K, const void *wq, cons
     QL_TRY(launch_act_quant(static_cast<const __half *>(x), ldx, M, K, nullptr, xq, sx, st));
     // what lies behind the quantized activations is scratch for the GEMM (split-K partial sums)
     return gemm_common(xq, sx, M, K, wq, sw, bits, group, bias, N, y, ldy, static_cast<char *>(ws) + l.total,
-                       ws_bytes - l.total, st);
+                       ws_bytes - l.total, st, fuses);
 }
 
 }  // namespace

@@ -126,6 +126,7 @@ struct GemmArgs {
     int bits, group;
     void *ws;
     size_t ws_bytes;
+    bool as_fused;         // decode: the K split of the call that quantizes its tokens itself (the same bits in two launches)
 };
 int launch_gemm_prefill(const GemmArgs &a, int variant, hipStream_t st);
 int launch_gemm_decode(const GemmArgs &a, int variant, hipStream_t st);

@@ -775,8 +775,10 @@ int by_m(const GemmArgs &a, int variant, hipStream_t st)
     if (variant == 103 && (!W4 || (size_t)3 * (a.K / 128) * 32 <= 16384)) c = 3;
     if (variant == 104 && (!W4 || (size_t)4 * (a.K / 128) * 32 <= 16384)) c = 4;
     if ((variant == 106 || variant == 108) && !W4 && a.M > 32 && block == 64) c = variant - 100;
-    // 16 wavefronts (K split 16 ways) when there is at most one workgroup per CU: twice the bytes in flight
-    const bool wide = c == 1 && (sixteen_wavefronts(a.N, c) || variant == 111) && variant != 101 && a.M <= 32;
+    // 16 wavefronts (K split 16 ways) when there is at most one workgroup per CU: twice the bytes in flight.  Fused quantizer,
+    // int4, two pieces per lane: 8 (8 tokens, 2048 x 2048 5.0 us against 6.2 with 16), in two launches (y over x) as well
+    const bool eight = W4 && fused_slots(a.M, a.K) == 2;
+    const bool wide = c == 1 && (sixteen_wavefronts(a.N, c) || variant == 111) && variant != 101 && a.M <= 32 && !(eight && a.as_fused);
     // few tokens can be staged in LDS (ring slots then hold weights only).  Measured: it pays for int4 weights
     // with 8 wavefronts (gate+up at up to 5 tokens 13.5 -> 11.4 us: the short int4 ring no longer shares its
     // registers with token fragments), makes no difference for int8 weights, and costs 0.7-1.1 us with 16
@@ -791,10 +793,10 @@ int by_m(const GemmArgs &a, int variant, hipStream_t st)
 #define QL_FUSED(C)                                                                                                       \
     return single ? (slots == 2 ? launch_one<W4, 1, C, EPI, 8, true, 2, true>(a, st) : launch_one<W4, 1, C, EPI, 8, true, 4, true>(a, st)) \
                   : (slots == 2 ? launch_one<W4, 1, C, EPI, 8, true, 2>(a, st) : launch_one<W4, 1, C, EPI, 8, true, 4>(a, st))
-            // 8 wavefronts; with four pieces per lane and int4 weights as many as the two-kernel path takes (16: `wide`), so that
-            // the fp32 sums over the wavefronts' k-ranges are the same bits either way
+            // 8 wavefronts; int4 weights with four pieces per lane as many as the GEMM alone takes (16: `wide`).  Where y lies over x
+            // the two launches split K alike (`eight`), so that the fp32 sums over the wavefronts' k-ranges are the same bits.
             if constexpr (W4) {
-                if (wide && slots == 4)
+                if (wide && !eight)
                     return fused_pieces(a.M, a.K, 16) <= 128 ? launch_one<W4, 1, 1, EPI, 16, true, 2, true>(a, st)
                                                              : launch_one<W4, 1, 1, EPI, 16, true, 4, true>(a, st);
             }

@@ -47,6 +47,37 @@ def test_linear_output_over_its_input(G, bits, M, K, N):
     assert torch.equal(wide[:, :N], ref) and torch.equal(wide[:, N:], x)
 
 
+@pytest.mark.parametrize("M,K,N,never_fused", [(1, 2048, 2048, False), (4, 1536, 1536, False), (4, 4096, 4096, False),
+                                                (8, 1536, 1536, False), (8, 4096, 4096, True)])
+def test_int4_sums_do_not_depend_on_the_route(G, M, K, N, never_fused):
+    """fp16 rounding hides the order in which the wavefronts' fp32 sums are added; large codes of one sign and a bias that
+    cancels the result leave its last bits.  Fused quantizer and y over x (two launches) have one order; with four pieces
+    per lane it is also that of the quantizer that is never fused."""
+    import torch
+    rng = np.random.default_rng(K)
+    x = torch.from_numpy(rng.uniform(0.5, 1, (1, K)).astype(np.float16)).to("cuda:0").repeat(M, 1)
+    g = G.gpu_quant_weight(rng.uniform(-0.2, 1, (N, K)).astype(np.float16), 4, 128)
+    ws = torch.empty(ql.ql_workspace_bytes(M, N, K, 4), dtype=torch.uint8, device="cuda:0")
+
+    def linear(x, bias, y):
+        ql.ql_w4a8_linear(x, g["kernel"], 128, bias, N, y, ws)
+        torch.cuda.synchronize()
+        return y
+
+    fresh = lambda: torch.empty((M, N), dtype=torch.float16, device="cuda:0")
+    bias = -linear(x, None, fresh())[0].clone()
+    ref = linear(x, bias, fresh())
+    assert (ref != 0).float().mean() > 0.5                  # the residues are what is compared
+    buf = x.clone()
+    assert torch.equal(linear(buf, bias, buf[:, :N]), ref)
+    if never_fused:
+        try:
+            ql.ql_set_kernel_variant(130)
+            assert torch.equal(linear(x, bias, fresh()), ref)
+        finally:
+            ql.ql_set_kernel_variant(0)
+
+
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("N,K,block", [(200, 1536, 512), (64, 11008, 256), (100, 4096, 0), (33, 16384, 4096)])
 def test_transformed_weight_codes_over_the_weights(G, bits, N, K, block):
