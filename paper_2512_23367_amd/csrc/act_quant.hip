@@ -191,6 +191,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_kernel(const __half 
     __syncthreads();
     mx = 0;
     for (int w = 0; w < nwaves; ++w) mx = max(mx, red[w]);
+    const bool finite = MODE == 0 && finite_tokens(mx);
     float scale, inv;
     if (MODE != 0) token_scales_f32(__uint_as_float(mx), scale, inv);
     else token_scales(mx, scale, inv);
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_kernel(const __half 
         if (!have(it)) break;                        // (the chunks of a lane ascend)
         uint4 q;
         if constexpr (MODE == 0) {
-            q = quant_chunk(v[it], inv);
+            q = quant_chunk(v[it], inv, finite);
         } else if constexpr (KEEP) {
             q = quant_chunk_f32(kept[it], inv);
         } else {
@@ -288,6 +289,7 @@ __global__ __launch_bounds__(ROWS8_WAVES * 64) void act_quant_rows8_kernel(const
     __syncthreads();
     mx = 0;
     for (int w = 0; w < nwaves; ++w) mx = max(mx, red[r][w]);
+    const bool finite = MODE == 0 && finite_tokens(mx);
     float scale, inv;
     if (MODE != 0) token_scales_f32(__uint_as_float(mx), scale, inv);
     else token_scales(mx, scale, inv);
@@ -298,7 +300,7 @@ __global__ __launch_bounds__(ROWS8_WAVES * 64) void act_quant_rows8_kernel(const
         if (i < per_wave && c < nchunks && valid) {
             uint4 q;
             if constexpr (MODE == 0) {
-                q = quant_chunk(v[i], inv);
+                q = quant_chunk(v[i], inv, finite);
             } else {
                 float f[16];
                 smoothed(v[i], c, f);

@@ -210,6 +210,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_kernel(DecodeParams p)
         __syncthreads();
         unsigned a = 0;
         for (int w = 0; w < WAVES; ++w) a = max(a, amax_red[w][fq_m]);
+        const bool finite = finite_tokens(a);
         float scale, inv;
         token_scales(a, scale, inv);
         // the finishing lanes want the scale of token r: for r < M that is this lane's own token (Mp divides 16)
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_kernel(DecodeParams p)
         for (int sl = 0; sl < FQ_SLOTS; ++sl) {
             const int i = th0 + sl * fq_ppr + (lane >> fq_lg);
             if (i < th1 && fq_m < p.M) {
-                *reinterpret_cast<uint4 *>(xs + ((size_t)i * xrows + fq_m) * 16) = quant_chunk(keep[sl], inv);
+                *reinterpret_cast<uint4 *>(xs + ((size_t)i * xrows + fq_m) * 16) = quant_chunk(keep[sl], inv, finite);
                 if (fq_m == 0) *reinterpret_cast<uint4 *>(xs + ((size_t)i * xrows + p.M) * 16) = uint4{0, 0, 0, 0};
             }
         }

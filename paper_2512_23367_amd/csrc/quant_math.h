@@ -45,6 +45,14 @@ __device__ inline unsigned code_word(float t0, float t1, float t2, float t3)
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
+__device__ inline float clamped(float x, float inv) { return fminf(fmaxf(x * inv, -127.0f), 127.0f); }
+
+__device__ inline unsigned clamped_word(unsigned w0, unsigned w1, float inv)
+{
+    return code_word(clamped(half_bits_to_float(w0 & 0xffffu), inv), clamped(half_bits_to_float(w0 >> 16), inv),
+                     clamped(half_bits_to_float(w1 & 0xffffu), inv), clamped(half_bits_to_float(w1 >> 16), inv));
+}
+
 __device__ inline unsigned quant_word(unsigned w0, unsigned w1, float inv)   // 4 halves -> 4 codes
 {
     // |x| <= amax and inv = 127 / amax rounded: |x * inv| <= 127 + one ulp, which rounds to 127 -- no clamp.  The widening
@@ -53,30 +61,46 @@ __device__ inline unsigned quant_word(unsigned w0, unsigned w1, float inv)   // 
                      __builtin_fmaf(half_bits_to_float(w1 & 0xffffu), inv, 0.0f), __builtin_fmaf(half_bits_to_float(w1 >> 16), inv, 0.0f));
 }
 
-__device__ inline uint4 quant_chunk(const Half16 &v, float inv)
+// The fast codes hold for finite tokens.  One with an infinity (inv = 0) or a NaN (inv = NaN) takes the products through the
+// clamp, where a NaN becomes -127: its codes say nothing, but they are the same in every kernel and mode.  The clamp
+// changes no code of a finite token, so all lanes of a wavefront go the same way: a scalar branch, decided on the maximum
+// (`finite`), which is known before the division that gives inv.
+__device__ inline bool no_lane(bool c) { return __builtin_amdgcn_ballot_w64(c) == 0; }
+
+__device__ inline bool finite_tokens(unsigned amax_bits) { return no_lane(amax_bits >= 0x7c00u); }
+
+__device__ inline uint4 quant_chunk(const Half16 &v, float inv, bool finite)
 {
     uint4 q;
-    q.x = quant_word(v.lo.x, v.lo.y, inv);
-    q.y = quant_word(v.lo.z, v.lo.w, inv);
-    q.z = quant_word(v.hi.x, v.hi.y, inv);
-    q.w = quant_word(v.hi.z, v.hi.w, inv);
+    if (finite) [[likely]] {
+        q.x = quant_word(v.lo.x, v.lo.y, inv);
+        q.y = quant_word(v.lo.z, v.lo.w, inv);
+        q.z = quant_word(v.hi.x, v.hi.y, inv);
+        q.w = quant_word(v.hi.z, v.hi.w, inv);
+    } else {
+        asm volatile("");               // or the compiler computes both sides for every token and selects
+        q.x = clamped_word(v.lo.x, v.lo.y, inv);
+        q.y = clamped_word(v.lo.z, v.lo.w, inv);
+        q.z = clamped_word(v.hi.x, v.hi.y, inv);
+        q.w = clamped_word(v.hi.z, v.hi.w, inv);
+    }
     return q;
 }
 
-// the same code decision for fp32 values (operands after one of the paper's transforms, Eq. 3-4).  Here inv overflows when
-// amax is below 127 / FLT_MAX: such tokens take the products through the clamp (which commutes with the rounding, its
-// bounds are integers); inv is the same for the whole token, so the branch is uniform.
+// the same code decision for fp32 values (operands after one of the paper's transforms, Eq. 3-4).  Here inv also overflows,
+// when amax is below 127 / FLT_MAX: such tokens take the clamp too (which commutes with the rounding, its bounds are
+// integers).
 __device__ inline uint4 quant_chunk_f32(const float (&v)[16], float inv)
 {
     unsigned q[4];
-    if (inv <= 3.402823466e38f) {
+    if (no_lane(!(inv > 0.0f && inv <= 3.402823466e38f))) [[likely]] {
 #pragma unroll
         for (int i = 0; i < 4; ++i) q[i] = code_word(v[4 * i] * inv, v[4 * i + 1] * inv, v[4 * i + 2] * inv, v[4 * i + 3] * inv);
     } else {
-        asm volatile("");               // or the compiler computes both sides for every token and selects
-        auto clamped = [&](float x) { return fminf(fmaxf(x * inv, -127.0f), 127.0f); };
+        asm volatile("");
 #pragma unroll
-        for (int i = 0; i < 4; ++i) q[i] = code_word(clamped(v[4 * i]), clamped(v[4 * i + 1]), clamped(v[4 * i + 2]), clamped(v[4 * i + 3]));
+        for (int i = 0; i < 4; ++i)
+            q[i] = code_word(clamped(v[4 * i], inv), clamped(v[4 * i + 1], inv), clamped(v[4 * i + 2], inv), clamped(v[4 * i + 3], inv));
     }
     return make_uint4(q[0], q[1], q[2], q[3]);
 }

@@ -101,11 +101,48 @@ def test_swiglu_of_every_gate(G):
     assert (q == q_o).all()
 
 
-def test_nan_reaches_the_scale(G):
+@pytest.mark.parametrize("mode", ["plain", "smooth", "rmsnorm", "swiglu", "hadamard"])
+def test_nan_reaches_the_scale(G, mode):
     """Codes of a token that holds a NaN are unspecified, but its scale (hence its output) must not look finite."""
-    for mode in ("smooth", "rmsnorm", "swiglu"):
-        x = np.ones((9, 256 if mode == "swiglu" else 128), dtype=np.float16)
-        x[4, 100] = np.nan
-        vec = {"smooth": np.ones(128, np.float32), "rmsnorm": np.ones(128, np.float16)}.get(mode)
-        _, s, _ = _run(G, mode, x, vec, 128)
-        assert np.isnan(s[4]) and np.isfinite(np.delete(s, 4)).all()
+    x = np.ones((9, 256 if mode == "swiglu" else 128), dtype=np.float16)
+    x[4, 100] = np.nan
+    s = _non_finite(G, mode, x)[1]
+    assert np.isnan(s[4]) and np.isfinite(np.delete(s, 4)).all()
+
+
+def _non_finite(G, mode, x, K=128):
+    vec = {"smooth": np.ones(K, np.float32), "rmsnorm": np.ones(K, np.float16)}.get(mode)
+    if mode != "hadamard":
+        return _run(G, mode, x, vec, K)
+    xq = torch.empty((x.shape[0], K), dtype=torch.int8, device=G.DEV)
+    sx = torch.empty(x.shape[0], dtype=torch.float32, device=G.DEV)
+    ql.ql_quant_act_per_token_transformed(G.dev(x), None, 16, xq, None, sx)
+    return xq.cpu().numpy(), sx.cpu().numpy(), None
+
+
+@pytest.mark.parametrize("M,K", [(9, 128), (9, 20480), (3073, 128)])
+@pytest.mark.parametrize("mode", ["plain", "smooth"])
+def test_infinity_keeps_its_code(G, mode, M, K):
+    """A token with an infinity has an infinite scale; its infinite elements have code -127 and the others 0 (the clamp of
+    0 * inf), so that its outputs are infinite where such a channel has weight, not NaN throughout."""
+    x = np.ones((M, K), dtype=np.float16)
+    x[4, 100], x[7, 3] = np.inf, -np.inf
+    q, s, _ = _non_finite(G, mode, x, K)
+    want = np.full((M, K), 127, dtype=np.int8)
+    want[[4, 7]] = 0
+    want[4, 100] = want[7, 3] = -127
+    assert np.isposinf(s[[4, 7]]).all() and np.isfinite(np.delete(s, [4, 7])).all()
+    assert (q == want).all()
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M", [1, 4, 8])
+def test_infinity_through_the_fused_quantizer(G, bits, M):
+    """The decode GEMM that quantizes its tokens itself decides as the stand-alone quantizer does."""
+    K, N = 1024, 64
+    x = np.ones((M, K), dtype=np.float16)
+    x[M - 1, 5] = np.inf
+    w = np.ones((N, K), dtype=np.float16)
+    w[1::2] = -1
+    y = G.gpu_linear(x, G.gpu_quant_weight(w, bits, 0 if bits == 8 else 128))
+    assert np.isneginf(y[M - 1, 0::2]).all() and np.isposinf(y[M - 1, 1::2]).all() and np.isfinite(y[:M - 1]).all()
