@@ -515,7 +515,7 @@ __global__ void act_repack_kernel(const int8_t *__restrict__ xq_rm, int M, int K
 // (the documented limit of the row stride)
 static int check_row_stride(int64_t ldx)
 {
-    if (ldx > ((int64_t)1 << 27)) return fail(QL_ERR_SHAPE, "row stride %lld beyond 2^27 elements", (long long)ldx);
+    if (ldx > MAX_ROW_STRIDE) return fail(QL_ERR_SHAPE, "row stride %lld beyond 2^27 elements", (long long)ldx);
     return QL_OK;
 }
 

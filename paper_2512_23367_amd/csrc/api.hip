@@ -190,7 +190,7 @@ int linear_common(const void *x, int64_t ldx, int M, int K, const void *wq, cons
         return fail(QL_ERR_ALIGN, "wq needs 256-byte, sw/bias 16-byte alignment");
     QL_TRY(check_out(y, ldy, N));
     const bool fuses = M <= DECODE_MAX_M && (g_variant == 0 || (g_variant >= 100 && g_variant < 200)) && decode_fuses_quant(M, N, K, bits, g_variant);
-    if (fuses && !rows_overlap(x, ldx, K, y, ldy, N, M)) {
+    if (fuses && (ldx <= MAX_ROW_STRIDE || decode_takes_any_stride(M, K)) && !rows_overlap(x, ldx, K, y, ldy, N, M)) {
         // few tokens: the decode GEMM quantizes them itself, one launch instead of two
         GemmArgs a = {};
         a.x = static_cast<const __half *>(x);

@@ -142,5 +142,7 @@ void prefill_plan(const GemmArgs &a, int *variant, int *tile_tokens, int *tile_c
                   int *rest_variant);
 void decode_plan(const GemmArgs &a, int *token_block, int *channel_groups);
 bool decode_fuses_quant(int M, int N, int K, int bits, int variant);
+bool decode_takes_any_stride(int M, int K);
+constexpr int64_t MAX_ROW_STRIDE = (int64_t)1 << 27;   // of x (elements): the limit that the quantizers check
 
 }  // namespace ql

@@ -858,6 +858,10 @@ bool decode_fuses_quant(int M, int N, int K, int bits, int variant)
     return true;
 }
 
+// Row strides of x beyond the documented limit are refused, but for the few tokens whose fused call has always taken them (its
+// kernel addresses rows in 64 bits).
+bool decode_takes_any_stride(int M, int K) { return M <= 4 && fused_slots(M, K) == 2; }
+
 double decode_estimate_us(const GemmArgs &a)
 {
     // up to 32 tokens: launch, first round trip and reduction + the weight stream at 90 % of nominal HBM bandwidth

@@ -111,3 +111,18 @@ def test_header_is_plain_c_and_a_c_program_links(tmp_path):
                     "-Wl,-rpath," + os.path.dirname(lib_path)], check=True, capture_output=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0 and out.stdout.startswith("ok"), (out.returncode, out.stdout, out.stderr)
+
+
+@pytest.mark.skipif(__import__("torch").cuda.is_available(), reason="host pointers: nothing may be launched")
+@pytest.mark.parametrize("M,K", [(1, 13312), (3, 6144), (5, 1024), (8, 4096), (16, 2048), (17, 1024)])
+@pytest.mark.parametrize("bits", [8, 4])
+def test_row_strides_beyond_the_limit_are_refused(bits, M, K):
+    """ldx above 2^27, also where the decode GEMM quantizes the tokens itself (without a device a call that got as far as a
+    launch would report QL_ERR_HIP)."""
+    lib, vp, N = binding.lib(), ctypes.c_void_p, 512          # (x lies behind everything else: no byte shared with y)
+    wsb = binding.ql_workspace_bytes(M, N, K, bits)
+    if bits == 8:
+        status = lib.ql_w8a8_linear(vp(1 << 40), (1 << 27) + 8, M, K, vp(1 << 21), vp(1 << 22), None, N, vp(1 << 23), N, vp(1 << 24), wsb, None)
+    else:
+        status = lib.ql_w4a8_linear(vp(1 << 40), (1 << 27) + 8, M, K, vp(1 << 21), 128, None, N, vp(1 << 23), N, vp(1 << 24), wsb, None)
+    assert status == 2
