@@ -213,13 +213,18 @@ def ql_weight_bytes(N, K, bits, group):
     return a.value, b.value, c.value
 
 
-@functools.lru_cache(maxsize=4096)
+# The checks of every GEMM call ask for these two: functions of the sizes alone, kept per size and type (64 and 64.0 are
+# not the same question: the second is refused).
+@functools.lru_cache(maxsize=4096, typed=True)
 def _blob_bytes(N, K, bits, group) -> int:
-    """ql_weight_bytes(...)[2]: a function of the sizes alone."""
     return ql_weight_bytes(N, K, bits, group)[2]
 
 
-@functools.lru_cache(maxsize=4096)
+@functools.lru_cache(maxsize=4096, typed=True)
+def _act_bytes(M, K) -> int:
+    return ql_act_kernel_bytes(M, K)
+
+
 def ql_act_kernel_bytes(M, K) -> int:
     a = ctypes.c_size_t()
     _check(lib().ql_act_kernel_bytes(M, K, ctypes.byref(a)))
@@ -299,7 +304,7 @@ def _check_gemm_buffers(M, K, N, bits, group, w_kernel, sw, bias, y, xq_kernel=N
         raise ValueError("sw needs N fp32 entries")
     if bias is not None and (bias.dtype != torch.float16 or bias.numel() < N):
         raise ValueError("bias must be fp16 with N entries")
-    if xq_kernel is not None and _nbytes(xq_kernel) < ql_act_kernel_bytes(M, K):
+    if xq_kernel is not None and _nbytes(xq_kernel) < _act_bytes(M, K):
         raise ValueError("xq_kernel is smaller than ql_act_kernel_bytes")
     if sx is not None and (sx.dtype != torch.float32 or sx.numel() < M):
         raise ValueError("sx needs M fp32 entries")

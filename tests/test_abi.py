@@ -126,3 +126,16 @@ def test_row_strides_beyond_the_limit_are_refused(bits, M, K):
     else:
         status = lib.ql_w4a8_linear(vp(1 << 40), (1 << 27) + 8, M, K, vp(1 << 21), 128, None, N, vp(1 << 23), N, vp(1 << 24), wsb, None)
     assert status == 2
+
+
+def test_sizes_are_refused_by_type_whatever_was_asked_before():
+    """A size that is not a whole number is refused, also after the same number was asked for as an integer."""
+    assert binding.ql_act_kernel_bytes(64, 128) == 64 * 128
+    for bad in (64.0, "64"):
+        with pytest.raises(ctypes.ArgumentError):
+            binding.ql_act_kernel_bytes(bad, 128)
+    assert binding._act_bytes(64, 128) == 64 * 128 and binding._blob_bytes(96, 128, 8, 0) == 96 * 128
+    with pytest.raises(ctypes.ArgumentError):
+        binding._act_bytes(64.0, 128)
+    with pytest.raises(ctypes.ArgumentError):
+        binding._blob_bytes(96.0, 128, 8, 0)
