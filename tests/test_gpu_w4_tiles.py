@@ -41,19 +41,3 @@ def test_shapes_agree_with_the_oracle(G, M, K, N, bias):
         assert G.norm_err(y, ref) <= TOL, v
         if v in UNSPLIT:
             assert (y.view(np.uint16) == outs[26].view(np.uint16)).all(), v
-
-
-def test_the_choice_covers_the_shapes():
-    """Host only in effect (no launch): each form is the automatic choice somewhere, and the two-region form needs no
-    second launch."""
-    def variant(M, N, K):
-        p = ql.ql_plan_gemm(M, N, K, 4, 128, 64 << 20)
-        assert p.rest_channels == 0
-        return p.variant
-
-    assert variant(4096, 12288, 4096) == 26       # three whole passes of 256x256
-    assert variant(3001, 4096, 4096) == 35        # 256 tiles of 192x256: one pass
-    assert variant(2048, 4096, 4096) == 37        # 256 tiles of 128x256
-    assert variant(1100, 3584, 4096) == 13        # 252 tiles of 128x128, one per CU
-    assert variant(4096, 22016, 4096) == 43       # five passes of 256x256, the last 1536 channels in 128x256
-    assert 202 <= variant(200, 4096, 16384) <= 232 or variant(200, 4096, 16384) > 100

@@ -33,7 +33,7 @@ def test_few_tokens_on_7b_shapes_follow_the_measured_table():
         assert (p.family, p.tile_tokens, p.tile_channels) == (ql.QL_FAMILY_DECODE, block, channels), (N, K)
         groups = -(-N // 32) * 2
         assert -(-groups // (channels // 16)) * -(-64 // block) <= 256          # one pass over the 256 CUs
-    # int4 weights have C <= 4: the widest projection needs two passes and still beats the one int4 tile shape
+    # int4 weights have C <= 4: the widest projection needs two passes and still beats the int4 tile forms
     p = plan(64, 22016, 4096, bits=4)
     assert p.family == ql.QL_FAMILY_DECODE and p.tile_channels <= 64
 
@@ -63,10 +63,26 @@ def test_split_k_needs_scratch_and_fits_it():
     assert without.splits == 1
     small = plan(M, N, K, scratch=1 << 20)      # room for no split of this shape
     assert small.splits == 1
-    # the int4 kernel splits too, and reports the variant that selects the same split
-    p4 = plan(200, 4096, 11008, bits=4)
-    if p4.family == ql.QL_FAMILY_TILE and p4.splits > 1:
-        assert p4.variant == 200 + p4.splits
+    # the int4 kernels split too, and report the variant that selects the same split: 200 + splits on 128x128 tiles, 300 + splits
+    # on 128x256
+    for shape, variant, channels in [((512, 4096, 11008), 304, 256), ((1536, 1536, 6144), 303, 256), ((1280, 1536, 6144), 202, 128)]:
+        p4 = plan(*shape, bits=4)
+        assert (p4.family, p4.variant, p4.tile_tokens, p4.tile_channels) == (ql.QL_FAMILY_TILE, variant, 128, channels)
+        assert p4.splits == variant % 100
+        tiles = -(-shape[0] // 128) * -(-shape[1] // channels)
+        assert p4.splits * tiles * 128 * channels * 4 <= SCRATCH
+        assert plan(*shape, bits=4, scratch=0).splits == 1
+
+
+def test_each_int4_tile_form_is_the_choice_somewhere():
+    """... and the two-region form needs no second launch."""
+    for (M, N, K), variant in [((4096, 12288, 4096), 26),      # three whole passes of 256x256
+                               ((3001, 4096, 4096), 35),       # 256 tiles of 192x256: one pass
+                               ((2048, 4096, 4096), 37),       # 256 tiles of 128x256
+                               ((1100, 3584, 4096), 13),       # 252 tiles of 128x128, one per CU
+                               ((4096, 22016, 4096), 43)]:     # five passes of 256x256, the last 1536 channels in 128x256
+        p = plan(M, N, K, bits=4)
+        assert (p.family, p.variant, p.splits, p.rest_channels) == (ql.QL_FAMILY_TILE, variant, 1, 0)
 
 
 def test_estimates_are_finite_positive_and_grow_with_k():
