@@ -213,14 +213,14 @@ def ql_weight_bytes(N, K, bits, group):
     return a.value, b.value, c.value
 
 
-# The checks of every GEMM call ask for these two: functions of the sizes alone, kept per size and type (64 and 64.0 are
-# not the same question: the second is refused).
-@functools.lru_cache(maxsize=4096, typed=True)
+# The checks of every GEMM call ask for these two: functions of the sizes alone, kept by value.  (64.0 finds the size of 64
+# here and is refused by the call itself; kept per type as well the smallest call took 1 % longer.)
+@functools.lru_cache(maxsize=4096)
 def _blob_bytes(N, K, bits, group) -> int:
     return ql_weight_bytes(N, K, bits, group)[2]
 
 
-@functools.lru_cache(maxsize=4096, typed=True)
+@functools.lru_cache(maxsize=4096)
 def _act_bytes(M, K) -> int:
     return ql_act_kernel_bytes(M, K)
 

@@ -129,13 +129,15 @@ def test_row_strides_beyond_the_limit_are_refused(bits, M, K):
 
 
 def test_sizes_are_refused_by_type_whatever_was_asked_before():
-    """A size that is not a whole number is refused, also after the same number was asked for as an integer."""
+    """A size that is not a whole number is refused, also after the same number was asked for as an integer; so are the
+    GEMM calls, whose checks look kept sizes up by value."""
     assert binding.ql_act_kernel_bytes(64, 128) == 64 * 128
     for bad in (64.0, "64"):
         with pytest.raises(ctypes.ArgumentError):
             binding.ql_act_kernel_bytes(bad, 128)
-    assert binding._act_bytes(64, 128) == 64 * 128 and binding._blob_bytes(96, 128, 8, 0) == 96 * 128
-    with pytest.raises(ctypes.ArgumentError):
-        binding._act_bytes(64.0, 128)
-    with pytest.raises(ctypes.ArgumentError):
-        binding._blob_bytes(96.0, 128, 8, 0)
+    for name, n in (("ql_w8a8_linear", 7), ("ql_w4a8_linear", 7), ("ql_w8a8_gemm", 7), ("ql_w4a8_gemm", 7)):
+        fn = getattr(binding.lib(), name)
+        args = [0] * len(fn.argtypes)
+        args[n] = 64.0                                     # N
+        with pytest.raises(ctypes.ArgumentError):
+            fn(*args)
