@@ -696,8 +696,9 @@ inline void auto_shape(int M, int N, int K, bool w4, int force_block, int &block
         // ring (64 KB, whatever c is) is all that is in flight -- 18 KB/us behind the first 32 KB; two and more reach 27; four groups
         // (the ring is two fragments deep) 17 and 22; every further workgroup costs 1 us of start and reduction.
         // 404 shapes (1..16 tokens, N 2048..32768, K 1024..12288; weights from HBM): the pick is within 1.3 % of the best c
-        // on average, and at most 6 % slower than the better of quantizer + GEMM and the former fused rule.  The rounds below would take c = 2 in one round for 8192 x 8192, one token: 15.6 us; c = 1 in
-        // two 13.0.  At short K it is the other way round (2048 x 8192: 5.6 in one round, 7.1).
+        // on average, and at most 6 % slower than the better of quantizer + GEMM and the rule of the separate GEMM below.  That rule
+        // would take c = 2 in one round for 8192 x 8192, one token: 15.6 us; c = 1 in two 13.0.  At short K it is the other way
+        // round (2048 x 8192: 5.6 in one round, 7.1 in two).
         block = 16, c = 1;
         double best = 1e30;
         for (int cand = 1; cand <= 4; ++cand) {
