@@ -306,6 +306,30 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_hadamard_kernel(cons
     }
 }
 
+// A wavefront's 64 chunks of 16 fp32 values (first chunk `c_first`, this lane's is `l`) to row[0, K): through its 4 KB of LDS, so
+// that a store instruction covers 1024 contiguous bytes.  Straight from the registers it takes 16 bytes out of every lane's
+// 64: four instructions touch each 128-byte line, and 180 MB of them held the kernel at 3.6 TB/s (4096 x 11008, int4: 98 us
+// against 62).  Within a chunk the four pieces are rotated by the chunk's number, or the 64-byte stride would meet the same banks.
+// Non-temporal: nothing here reads the values again, and the fp16 weights that the next calls read stay cached
+// (calibration, scales and this kernel 98.5 against 86 us; non-temporal stores straight from the registers: 161 us here).
+__device__ inline void store_chunks(float *row, int K, float4 *stage, int c_first, int l, int lane, const float (&v)[16])
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) stage[l * 4 + (q ^ ((l >> 1) & 3))] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    asm volatile("" ::: "memory");   // (same wavefront, LDS operations complete in order: only the compiler must keep them so)
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int chunk = r * 16 + lane / 4, q = lane % 4;
+        const float4 f = stage[chunk * 4 + (q ^ ((chunk >> 1) & 3))];
+        if (c_first + chunk < K / 16)
+            __builtin_nontemporal_store(f4{f.x, f.y, f.z, f.w}, reinterpret_cast<f4 *>(row + (size_t)(c_first + chunk) * 16 + q * 4));
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __device__ inline int weight_code(float w, float s, float limit)   // the quantizer of weight_quant.hip, symmetric range
 {
     return (int)fminf(fmaxf(rintf(w / s), -limit), limit);         // IEEE fp32 division by the stored scale, ties to even
@@ -313,7 +337,7 @@ __device__ inline int weight_code(float w, float s, float limit)   // the quanti
 
 // Offline: S W and / or H^T W of one weight row (output channel) per workgroup, its fp32 values stored (w32) and quantized
 // from the registers in the same pass (bound by HBM: 2 bytes in, 4 + 2 x codes out per weight; as two kernels the
-// fp32 values were read back: 145 us for 4096 x 11008, int4, against 87 in one).  Rows N .. 32-row padding: zero codes.
+// fp32 values were read back: 145 us for 4096 x 11008, int4, against 62 in one).  Rows N .. 32-row padding: zero codes.
 // STORED: quantizes what an earlier launch left in w32 (only where the results take the place of the inputs).
 template <int LB, int BITS, bool STORED = false>
 __global__ __launch_bounds__(MAX_WAVES * 64) void weight_transform_quant_kernel(const __half *__restrict__ w, int N, int Npad, int K,
@@ -324,6 +348,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void weight_transform_quant_kernel(
 {
     constexpr int NIT = hadamard_chunks(LB);
     __shared__ float red[MAX_WAVES];
+    extern __shared__ __attribute__((aligned(16))) float4 stage[];   // 4 KB per wavefront (none if STORED)
     const int n = row_of_workgroup(Npad, 32);
     if (n >= Npad) return;
     const bool real = n < N;
@@ -352,11 +377,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void weight_transform_quant_kernel(
         amax[it] = 0.0f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) amax[it] = fmaxf(amax[it], fabsf(v[it][i]));
-        if (!STORED && real && c < K / 16) {
-#pragma unroll
-            for (int i = 0; i < 16; i += 4)
-                *reinterpret_cast<float4 *>(w32 + (size_t)n * K + (size_t)c * 16 + i) = make_float4(v[it][i], v[it][i + 1], v[it][i + 2], v[it][i + 3]);
-        }
+        if constexpr (!STORED) store_chunks(w32 + (size_t)n * K, real ? K : 0, stage + wave * 256, c0 - l + it * 64, l, lane, v[it]);
     }
     if constexpr (BITS == 8) {
         float mx = amax[0];
@@ -567,10 +588,10 @@ int launch_weight_transform_quant(const __half *w, int N, int K, int bits, int g
         constexpr int LB = decltype(lb)::value;
         const dim3 grid(workgroups_for(rows, 32)), block(ceil_div(K / 16, 64 * hadamard_chunks(LB)) * 64);
         if (bits == 8)
-            hipLaunchKernelGGL((weight_transform_quant_kernel<LB, 8>), grid, block, 0, st, w, N, rows, K, smooth, norm, w32,
+            hipLaunchKernelGGL((weight_transform_quant_kernel<LB, 8>), grid, block, block.x * 64, st, w, N, rows, K, smooth, norm, w32,
                                static_cast<uint8_t *>(canon), scales, blob, kls, klsd);
         else
-            hipLaunchKernelGGL((weight_transform_quant_kernel<LB, 4>), grid, block, 0, st, w, N, rows, K, smooth, norm, w32,
+            hipLaunchKernelGGL((weight_transform_quant_kernel<LB, 4>), grid, block, block.x * 64, st, w, N, rows, K, smooth, norm, w32,
                                static_cast<uint8_t *>(canon), scales, blob, kls, klsd);
         return check_hip(hipGetLastError(), "weight_transform_quant launch");
     });
