@@ -61,6 +61,28 @@ def test_weights_every_block(G, bits, K, block):
     assert (g["kernel"].cpu().numpy()[codes // 2:codes][lane_row >= N] == plain[codes // 2:codes][lane_row >= N]).all()
 
 
+@pytest.mark.parametrize("factor", [1.0, 1 / 3, 0.7001, 3e-5, 1e-9, 3e-41, 1e36])
+@pytest.mark.parametrize("bits", [8, 4])
+def test_weight_codes_in_the_middle(G, bits, factor):
+    """Weights in the middle between two codes, or an ulp of it away, where a product with the scale's reciprocal and the division
+    differ; scales from fp32 subnormal (zero in fp16) to infinite in fp16.  Bit for bit the division's codes."""
+    top, K = (127, 384) if bits == 8 else (7, 384)
+    k = np.resize(np.arange(-top, top), K)
+    w = np.stack([k + 0.5, np.nextafter((k + 0.5).astype(np.float16), np.float16(0)), np.nextafter((k + 0.5).astype(np.float16), np.float16(200)), k]).astype(np.float16)
+    w[:, ::128] = top                                     # every group's maximum: scale = factor
+    smooth = np.full(K, factor, np.float32)
+    with np.errstate(over="ignore"):                      # fp16 scales
+        t = oracle.smooth_weight(w, smooth)
+        if bits == 8:
+            q_o, s_o = oracle.quant_weight_int8(t)
+        else:
+            q_o, _, s_o = oracle.quant_weight_int4(t, 128)
+    g = gpu_weight(G, w, bits, smooth, 0)
+    assert (g["w32"] == t).all() and (g["scales"] == s_o).all() and (g["canon"] == q_o).all()
+    c, _ = G.gpu_export(g["kernel"], 4, K, bits, g["group"])
+    assert (c == q_o).all()
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 1, 64), (63, 511, 192), (65, 513, 320), (130, 600, 1088)])
 def test_column_maxima(G, M, N, K):
     x, w = synth.activations(M, K, 0, "single"), synth.weights(N, K, 0, "single")
