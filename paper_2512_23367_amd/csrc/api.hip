@@ -95,12 +95,6 @@ int check_out(const void *y, int64_t ldy, int N)
     return QL_OK;
 }
 
-bool bytes_overlap(const void *p, size_t np, const void *q, size_t nq)
-{
-    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
-    return a < b + nq && b < a + np;
-}
-
 // Whether rows of x and y share bytes.  The GEMM that quantizes its own tokens writes y while other workgroups still read
 // x; with the quantizer as a launch of its own all of x has been read before the first byte of y is written.
 bool rows_overlap(const void *x, int64_t ldx, int K, const void *y, int64_t ldy, int N, int M)

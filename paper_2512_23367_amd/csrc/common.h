@@ -20,6 +20,12 @@ int check_hip(hipError_t e, const char *what);
         if (_s != QL_OK) return _s;           \
     } while (0)
 
+inline bool bytes_overlap(const void *p, size_t np, const void *q, size_t nq)
+{
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return a < b + nq && b < a + np;
+}
+
 // ---- kernel layout ---------------------------------------------------------------------------
 // A tile is 32 rows x 32 k of int8 = 1024 bytes, stored in the order a wavefront feeds the
 // 32x32x32 int8 matrix instruction: lane = row % 32 + 32 * ((k % 32) / 16), 16 bytes per lane.

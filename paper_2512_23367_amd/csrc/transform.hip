@@ -15,6 +15,7 @@
 // between inside a row of 16 lanes are one lane-permuting multiply-add each, the two across the rows swap registers.
 #include "common.h"
 #include "quant_math.h"
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -501,23 +502,34 @@ __global__ __launch_bounds__(256) void channel_absmax_kernel(const __half *__res
     atomicMax(xmax_bits + k, __float_as_uint(a));
 }
 
-// s_j = xmax_j^alpha / wmax_j^(1-alpha), 1 where either maximum is 0; inv_j = 1 / s_j (IEEE fp32 division).  A workgroup
-// finds the column maxima of 64 channels over all N rows (8 channels per lane, 64 rows side by side, 8 loads of each lane in
-// flight: a strip of 128 bytes per row streams at the rate one CU can pull) -- one lane per channel walking
-// down the rows took 1570 us for 4096 x 11008.
-__global__ __launch_bounds__(512) void smooth_scales_kernel(const float *__restrict__ xmax, const __half *__restrict__ w, int N, int K,
+// s_j = xmax_j^alpha / wmax_j^(1-alpha), 1 where either maximum is 0; inv_j = 1 / s_j (IEEE fp32 division)
+__device__ inline void smooth_scale(float xm, float wmax, float alpha, float *s, float *inv_s)
+{
+    float sj = 1.0f;
+    if (xm > 0.0f && wmax > 0.0f) sj = (float)(pow((double)xm, (double)alpha) / pow((double)wmax, 1.0 - (double)alpha));
+    *s = sj;
+    *inv_s = 1.0f / sj;
+}
+
+// A workgroup finds the column maxima of 64 channels over N rows (8 channels per lane, 64 rows side by side, 8 loads of each
+// lane in flight: a strip of 128 bytes per row streams at the rate one CU can pull, about 30 GB/s) -- one lane per channel
+// walking down the rows took 1570 us for 4096 x 11008.  PART: of `rows` rows per blockIdx.y, into the larger of what inv_s holds (as
+// bits; zeroed before) and of what the other workgroups of the strip find; smooth_scales_finish_kernel does the rest.
+template <bool PART>
+__global__ __launch_bounds__(512) void smooth_scales_kernel(const float *__restrict__ xmax, const __half *__restrict__ w, int N, int K, int rows,
                                                             float alpha, float *__restrict__ s, float *__restrict__ inv_s)
 {
     __shared__ float red[8][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 7;
     const __half *base = w + (size_t)blockIdx.x * 64 + col * 8;
     float mx[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int n0 = 0; n0 < N; n0 += 512) {
+    const int end = PART ? min(N, (int)(blockIdx.y + 1) * rows) : N;
+    for (int n0 = PART ? blockIdx.y * rows : 0; n0 < end; n0 += 512) {
         uint4 h[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {   // (a row behind the last one: the last one again)
             const int n = n0 + i * 64 + wave * 8 + (lane >> 3);
-            h[i] = *reinterpret_cast<const uint4 *>(base + (size_t)(n < N ? n : N - 1) * K);
+            h[i] = *reinterpret_cast<const uint4 *>(base + (size_t)(n < end ? n : end - 1) * K);
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -541,11 +553,21 @@ __global__ __launch_bounds__(512) void smooth_scales_kernel(const float *__restr
 #pragma unroll
     for (int i = 0; i < 8; ++i) wmax = fmaxf(wmax, red[i][threadIdx.x]);
     const int k = blockIdx.x * 64 + threadIdx.x;
-    const float xm = xmax[k];
-    float sj = 1.0f;
-    if (xm > 0.0f && wmax > 0.0f) sj = (float)(pow((double)xm, (double)alpha) / pow((double)wmax, 1.0 - (double)alpha));
-    s[k] = sj;
-    inv_s[k] = 1.0f / sj;
+    if constexpr (PART) atomicMax(reinterpret_cast<unsigned *>(inv_s) + k, __float_as_uint(wmax));   // (non-negative: ordered like their bits)
+    else smooth_scale(xmax[k], wmax, alpha, s + k, inv_s + k);
+}
+
+__global__ __launch_bounds__(256) void smooth_scales_clear_kernel(int K, float *__restrict__ inv_s)
+{
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k < K) inv_s[k] = 0.0f;
+}
+
+__global__ __launch_bounds__(256) void smooth_scales_finish_kernel(const float *__restrict__ xmax, int K, float alpha, float *__restrict__ s,
+                                                                   float *__restrict__ inv_s)
+{
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k < K) smooth_scale(xmax[k], inv_s[k], alpha, s + k, inv_s + k);
 }
 
 float block_norm(int hblock) { return (float)(1.0 / std::sqrt((double)hblock)); }
@@ -641,7 +663,23 @@ int launch_channel_absmax(const __half *x, int64_t ldx, int M, int K, float *xma
 int launch_smooth_scales(const float *xmax, const __half *w, int N, int K, float alpha, float *s, float *inv_s,
                          hipStream_t st)
 {
-    hipLaunchKernelGGL(smooth_scales_kernel, dim3(K / 64), dim3(512), 0, st, xmax, w, N, K, alpha, s, inv_s);
+    // One workgroup per 64 channels pulls its N x 128 bytes in 2 + N / 235 us, however few of them there are.  Several per strip and two
+    // small launches around them take 7 us + the bytes at 4 TB/s: taken where that is a tenth less, unless a result lies over an
+    // input that a later launch reads.  N x K, us, one against several: 4608 x 1536 21.2 / 10.4, 6144 x 2048 26.7 / 13.0, 12288 x 4096
+    // 52.0 / 30.1, 4096 x 4096 20.4 / 15.8, 2048 x 2048 11.4 / 9.3; the other way 1536 x 6144 10.9 / 12.5, 3000 x 8192 16.6 / 18.0.
+    const int strips = K / 64, parts = std::min(ceil_div(384, strips), N / 512);
+    const bool several = parts > 1 && 7.0 + 0.5e-6 * N * K < 0.9 * (2.0 + N / 235.0);
+    auto over_inputs = [&](const float *p) {
+        return bytes_overlap(p, (size_t)K * 4, xmax, (size_t)K * 4) || bytes_overlap(p, (size_t)K * 4, w, (size_t)N * K * 2);
+    };
+    if (several && !over_inputs(s) && !over_inputs(inv_s)) {
+        const int rows = round_up(ceil_div(N, parts), 64);
+        hipLaunchKernelGGL(smooth_scales_clear_kernel, dim3(ceil_div(K, 256)), dim3(256), 0, st, K, inv_s);
+        hipLaunchKernelGGL(smooth_scales_kernel<true>, dim3(strips, ceil_div(N, rows)), dim3(512), 0, st, xmax, w, N, K, rows, alpha, s, inv_s);
+        hipLaunchKernelGGL(smooth_scales_finish_kernel, dim3(ceil_div(K, 256)), dim3(256), 0, st, xmax, K, alpha, s, inv_s);
+        return check_hip(hipGetLastError(), "smooth_scales launch");
+    }
+    hipLaunchKernelGGL(smooth_scales_kernel<false>, dim3(strips), dim3(512), 0, st, xmax, w, N, K, N, alpha, s, inv_s);
     return check_hip(hipGetLastError(), "smooth_scales launch");
 }
 

@@ -83,7 +83,7 @@ def test_weight_codes_in_the_middle(G, bits, factor):
     assert (c == q_o).all()
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 1, 64), (63, 511, 192), (65, 513, 320), (130, 600, 1088)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 64), (63, 511, 192), (65, 513, 320), (130, 600, 1088), (3, 4100, 192), (2, 2049, 64), (5, 6000, 1088)])   # the last three: several workgroups per strip
 def test_column_maxima(G, M, N, K):
     x, w = synth.activations(M, K, 0, "single"), synth.weights(N, K, 0, "single")
     w[-1, 7] = 3                                          # the last row, the last token decide a channel
@@ -95,5 +95,8 @@ def test_column_maxima(G, M, N, K):
     ql.ql_smooth_scales(xmax, G.dev(w), 0.5, s, inv)
     s_o, inv_o = oracle.smooth_scales(oracle.channel_absmax(x), w, 0.5)
     np.testing.assert_allclose(s.cpu().numpy(), s_o, rtol=3e-7)
+    inv_1, other = inv.clone(), xmax.clone()
     ql.ql_smooth_scales(xmax, G.dev(w), 0.5, xmax, inv)   # in place: every lane reads its maximum before it writes
-    assert (xmax == s).all()
+    assert (xmax == s).all() and (inv == inv_1).all()
+    ql.ql_smooth_scales(other, G.dev(w), 0.5, s, other)
+    assert (xmax == s).all() and (other == inv_1).all()
