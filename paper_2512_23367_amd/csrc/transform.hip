@@ -400,7 +400,6 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void weight_transform_quant_kernel(
     float amax[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int c = c0 + it * 64;
         amax[it] = 0.0f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) amax[it] = fmaxf(amax[it], fabsf(v[it][i]));
