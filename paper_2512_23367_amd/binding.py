@@ -101,7 +101,33 @@ def lib() -> ctypes.CDLL:
             fn.restype = i
             fn.argtypes = args
         _lib = l
+        _bind_native(l)
     return _lib
+
+
+# Native argument marshalling (csrc/pycall.cpp) of the calls that are made per layer: the checks below in C++, then the library, or
+# None for anything unusual, which then takes the Python below.  None before the library is loaded, or without the module.
+_native = None
+
+
+def _bind_native(l):
+    global _native
+    try:
+        from . import _qlcall
+    except ImportError:
+        return
+    names = ("ql_weight_bytes", "ql_act_kernel_bytes", "ql_w8a8_linear", "ql_w4a8_linear", "ql_w8a8_gemm", "ql_w4a8_gemm",
+             "ql_quant_act_per_token", "ql_quant_act_rmsnorm", "ql_quant_act_swiglu", "ql_quant_act_per_token_transformed")
+    _qlcall.bind(tuple(ctypes.cast(getattr(l, n), ctypes.c_void_p).value for n in names))
+    _native = _qlcall
+
+
+def _done(status) -> bool:
+    """Whether the native call was made (raises if the library refused it)."""
+    if status is None:
+        return False
+    _check(status)
+    return True
 
 
 def _check(status: int):
@@ -174,6 +200,8 @@ def ql_smooth_scales(xmax, w, alpha, smooth, inv_smooth):
 
 
 def ql_quant_act_per_token_transformed(x, inv_smooth, hadamard_block, xq_rowmajor, xq_kernel, sx):
+    if _native is not None and _done(_native.quant_transformed(x, inv_smooth, hadamard_block, xq_rowmajor, xq_kernel, sx, _stream)):
+        return
     _want(x, torch.float16, "x")
     M, K = x.shape
     _check(lib().ql_quant_act_per_token_transformed(_p(x), _ld(x) if M else K, M, K, _p(inv_smooth), hadamard_block,
@@ -244,6 +272,8 @@ def _ld(t):
 
 
 def ql_quant_act_per_token(x, xq_rowmajor=None, xq_kernel=None, sx=None):
+    if _native is not None and _done(_native.quant_act(x, xq_rowmajor, xq_kernel, sx, _stream)):
+        return
     _want(x, torch.float16, "x")
     M, K = x.shape
     _check(lib().ql_quant_act_per_token(_p(x), _ld(x) if M else K, M, K, _p(xq_rowmajor), _p(xq_kernel), _p(sx),
@@ -251,6 +281,8 @@ def ql_quant_act_per_token(x, xq_rowmajor=None, xq_kernel=None, sx=None):
 
 
 def ql_quant_act_rmsnorm(x, gamma, eps, xq_rowmajor=None, xq_kernel=None, sx=None):
+    if _native is not None and _done(_native.quant_rmsnorm(x, gamma, eps, xq_rowmajor, xq_kernel, sx, _stream)):
+        return
     _want(x, torch.float16, "x"), _want(gamma, torch.float16, "gamma")
     M, K = x.shape
     _check(lib().ql_quant_act_rmsnorm(_p(x), _ld(x) if M else K, M, K, _p(gamma), float(eps), _p(xq_rowmajor),
@@ -259,6 +291,8 @@ def ql_quant_act_rmsnorm(x, gamma, eps, xq_rowmajor=None, xq_kernel=None, sx=Non
 
 def ql_quant_act_swiglu(gate_up, xq_rowmajor=None, xq_kernel=None, sx=None):
     """gate_up: fp16 [M, 2F] (gate half, then up half); quantizes silu(gate) * up per token (K = F)."""
+    if _native is not None and _done(_native.quant_swiglu(gate_up, xq_rowmajor, xq_kernel, sx, _stream)):
+        return
     _want(gate_up, torch.float16, "gate_up")
     M, F2 = gate_up.shape
     if F2 % 2:
@@ -311,6 +345,8 @@ def _check_gemm_buffers(M, K, N, bits, group, w_kernel, sw, bias, y, xq_kernel=N
 
 
 def ql_w8a8_linear(x, wq_kernel, sw, bias, N, y, ws):
+    if _native is not None and _done(_native.w8a8_linear(x, wq_kernel, sw, bias, N, y, ws, _stream)):
+        return
     _want(x, torch.float16, "x"), _want(y, torch.float16, "y"), _want(sw, torch.float32, "sw")
     M, K = x.shape
     _check_gemm_buffers(M, K, N, 8, 0, wq_kernel, sw, bias, y)
@@ -329,6 +365,8 @@ def ql_w8a8_linear_static(x, wq_kernel, sw, bias, N, y):
 
 
 def ql_w4a8_linear(x, w4_kernel, group, bias, N, y, ws):
+    if _native is not None and _done(_native.w4a8_linear(x, w4_kernel, group, bias, N, y, ws, _stream)):
+        return
     _want(x, torch.float16, "x"), _want(y, torch.float16, "y")
     M, K = x.shape
     _check_gemm_buffers(M, K, N, 4, group, w4_kernel, None, bias, y)
@@ -338,6 +376,8 @@ def ql_w4a8_linear(x, w4_kernel, group, bias, N, y, ws):
 
 
 def ql_w8a8_gemm(xq_kernel, sx, M, K, wq_kernel, sw, bias, N, y, ws=None):
+    if _native is not None and _done(_native.w8a8_gemm(xq_kernel, sx, M, K, wq_kernel, sw, bias, N, y, ws, _stream)):
+        return
     _want(y, torch.float16, "y")
     _check_gemm_buffers(M, K, N, 8, 0, wq_kernel, sw, bias, y, xq_kernel, sx)
     wsp, wsb = _ws(ws)
@@ -346,6 +386,8 @@ def ql_w8a8_gemm(xq_kernel, sx, M, K, wq_kernel, sw, bias, N, y, ws=None):
 
 
 def ql_w4a8_gemm(xq_kernel, sx, M, K, w4_kernel, group, bias, N, y, ws=None):
+    if _native is not None and _done(_native.w4a8_gemm(xq_kernel, sx, M, K, w4_kernel, group, bias, N, y, ws, _stream)):
+        return
     _want(y, torch.float16, "y")
     _check_gemm_buffers(M, K, N, 4, group, w4_kernel, None, bias, y, xq_kernel, sx)
     wsp, wsb = _ws(ws)

@@ -5,13 +5,15 @@
 Every .hip under csrc/ is compiled to an object file in parallel and linked into
 one shared library whose exported symbols are the C ABI of include/qlinear.h.
 The benchmark's ceiling probes (bench_probe/) become a library of their own,
-libqlprobe.so, which the quantized linear layer does not depend on.
+libqlprobe.so, which the quantized linear layer does not depend on.  csrc/pycall.cpp
+(host code, against torch's and Python's headers) becomes the extension module _qlcall.
 """
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -20,6 +22,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqlinear.so")
 PROBE_LIB = os.path.join(HERE, "libqlprobe.so")
+
+CALL_MODULE = os.path.join(HERE, "_qlcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 PROBE_DIR = os.path.join(HERE, "bench_probe")
@@ -48,15 +52,29 @@ def _link(objs: list[str], lib: str) -> None:
     os.replace(tmp, lib)
 
 
+def _build_call_module() -> None:
+    import torch
+    from torch.utils import cpp_extension
+    inc = [f"-I{d}" for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = CALL_MODULE + f".tmp{os.getpid()}"
+    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", *inc,
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+                    os.path.join(CSRC, "pycall.cpp"), f"-L{libs}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", tmp], check=True)
+    os.replace(tmp, CALL_MODULE)
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     probe_src = os.path.join(PROBE_DIR, "probe.hip")
-    with ThreadPoolExecutor(max_workers=min(8, len(sources()) + 1)) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(sources()) + 2)) as ex:
+        call_module = ex.submit(_build_call_module)
         objs = list(ex.map(_compile, sources() + [probe_src]))
+        call_module.result()
     _link(objs[:-1], LIB)
     _link(objs[-1:], PROBE_LIB)
     if verbose:
-        print("built", LIB, "and", PROBE_LIB, file=sys.stderr)
+        print("built", LIB, ",", PROBE_LIB, "and", CALL_MODULE, file=sys.stderr)
     return LIB
 
 
