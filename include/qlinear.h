@@ -195,7 +195,8 @@ int ql_w4a8_gemm_acc_i32(const int8_t *xq_kernel, int M, int K, const void *w4_k
  *   1 = automatic among the prefill tile kernels (2: the same, always as one launch -- see ql_plan.rest_channels),
  *   100 = automatic among the decode kernels (M <= 1024)
  *   other values pick one implementation: 4, 6, 11, 13, 15, 17, 19, 20, 23 prefill tile shapes (26, 35, 37, 39, 43: the
- *   shapes 6, 15, 17, 19, 23 on the 16x16x64 matrix instruction); 202..232 / 302..332
+ *   shapes 6, 15, 17, 19, 23 on the 16x16x64 matrix instruction); 51..56 workgroups of four wavefronts, int8 (tokens x channels: 51
+ *   64x128, 53 96x128, 55 128x256, 56 96x256; 52 64x128 and 54 96x128 with K in two halves by eight; K % 128 != 0: 13); 202..232 / 302..332
  *   split-K with that many splits on 128x128 / 256x256 tiles; 101..104, 106, 108 decode kernels with that many
  *   groups of 16 channels per workgroup; 111 sixteen wavefronts; 121 tokens never staged in LDS; 122 / 123 token
  *   blocks of 32 / 64; 130 quantizer never fused into the decode GEMM.  int4 weights have tile forms of their own (tokens x

@@ -140,6 +140,10 @@ int launch_gemm_decode(const GemmArgs &a, int variant, hipStream_t st);
 int launch_gemm_prefill_w4(const GemmArgs &a, int variant, hipStream_t st);
 double prefill_w4_estimate_us(const GemmArgs &a);
 void prefill_w4_plan(const GemmArgs &a, int *variant, int *tile_tokens, int *tile_channels, int *splits);
+// the int8 forms of gemm_prefill_w8.hip (variants 51..56; K % 128 == 0): the best of them (0: none) and its estimated time; tile sizes
+int choose_w8_form(const GemmArgs &a, double *us);
+bool w8_form_tile(int variant, int *tile_tokens, int *tile_channels);
+int launch_gemm_w8_form(const GemmArgs &a, int variant, hipStream_t st);
 // estimated time (us) of the automatic choice of the tile kernels / of the decode kernels (33 tokens and more)
 double prefill_estimate_us(const GemmArgs &a);
 double decode_estimate_us(const GemmArgs &a);

@@ -684,7 +684,7 @@ struct Choice {
 //     layer runs), and the time of a pass is how fast one workgroup can pull its operands -- measured with the
 //     weights rotated through 768 MB on 16 layer shapes of 1.5B..70B models x 9 token counts (pick within
 //     2 % of the best on average, 28 % at worst; the warm-cache parameters gave 4.5 % / 35 % there).
-inline Choice choose_w8(const GemmArgs &a, size_t scratch, bool dump_partials)
+inline Choice choose_w8(const GemmArgs &a, size_t scratch, bool dump_partials, bool whole = true)
 {
     struct Candidate { int variant, tm, tn; double o, r; };
     // (the ping-pong configurations run on the 16x16x64 matrix instruction here: 3-8 % faster than on 32x32x32 on the
@@ -739,6 +739,10 @@ inline Choice choose_w8(const GemmArgs &a, size_t scratch, bool dump_partials)
     const double us64 = std::max(2.4 + (double)a.M * a.N * 2.0 / 6.9e6 + std::max(lone, per_cu),
                                  2.2 + 1.5 * ((double)a.N * a.K) / 6.8e6);
     if (t64 <= 1024 && us64 < best.us * 0.95) best = {20, 1, us64};
+    // workgroups of four wavefronts (gemm_prefill_w8.hip), not within a channel split: there a part's estimate decides by itself, and
+    // an optimistic one made 4096 x 1024 x 24000 a split that took 127 us instead of 103
+    double us4 = 0.0;
+    if (const int form = whole ? choose_w8_form(a, &us4) : 0; form && !dump_partials && us4 < best.us * 0.97) best = {form, 1, us4};
     return best;
 }
 
@@ -769,7 +773,7 @@ inline ColumnSplit choose_w8_columns(const GemmArgs &a, size_t scratch, bool dum
             if (n1 <= 0 || n1 >= a.N) continue;
             GemmArgs a1 = a, a2 = a;
             a1.N = (int)n1, a2.N = a.N - (int)n1;
-            const Choice c1 = choose_w8(a1, 0, dump_partials), c2 = choose_w8(a2, 0, dump_partials);
+            const Choice c1 = choose_w8(a1, 0, dump_partials, false), c2 = choose_w8(a2, 0, dump_partials, false);
             if (c1.us + c2.us < best.us * 0.97) best = {(int)n1, c1, c2, c1.us + c2.us};
         }
     }
@@ -821,6 +825,10 @@ int dispatch(const GemmArgs &a, int variant, hipStream_t st)
     }
     if (variant == 19 && a.K % 128) variant = 13;   // 128-k stages need K % 128 == 0
     if (variant == 39 && a.K % 128) variant = 13;
+    if (variant >= 51 && variant <= 56) {
+        if (a.K % 128 == 0) return launch_gemm_w8_form(a, variant, st);
+        variant = 13;
+    }
     switch (variant) {
     // 26, 43, 35, 37, 39: the configurations 6, 23, 15, 17, 19 on the 16x16x64 matrix instruction
     case 26: return launch_one<2, 4, 4, 2, 2, 4, EPI, 1, true, 1, true>(a, st);
@@ -876,6 +884,10 @@ void prefill_plan(const GemmArgs &a, int *variant, int *tile_tokens, int *tile_c
         *rest_variant = ((cs.rest.variant == 19 || cs.rest.variant == 39) && a.K % 128) ? 13 : cs.rest.variant;
     }
     if ((c.variant == 19 || c.variant == 39) && a.K % 128) c.variant = 13;
+    if (w8_form_tile(c.variant, tile_tokens, tile_channels)) {
+        *splits = 1, *variant = c.variant;
+        return;
+    }
     *splits = c.splits;
     *variant = c.variant == 200 || c.variant == 300 ? c.variant + c.splits : c.variant;
     switch (c.variant) {

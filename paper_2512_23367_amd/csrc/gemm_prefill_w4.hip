@@ -43,45 +43,6 @@ struct W4Params {
     int stages_per_split;    // split-K: part y (blockIdx.y, or the K group of a wavefront) takes stages [y * stages_per_split, ...)
 };
 
-// Writes a wavefront's staged block of ROWS tokens to y, 16 bytes per lane (LPR lanes per row).
-template <int LPR, int ROWS>
-__device__ __forceinline__ void store_rows(const W4Params &p, const char *stg, int row_bytes, int m0, int n0, int lane)
-{
-    constexpr int RPI = 64 / LPR;
-    static_assert(64 % LPR == 0 && ROWS % RPI == 0, "whole rows per read-back instruction");
-    asm volatile("" ::: "memory");   // (same wavefront, LDS operations complete in order: only the compiler must keep them so)
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int t = 0; t < ROWS / RPI; ++t) {
-        const int row = t * RPI + lane / LPR, c = lane % LPR;
-        const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * row_bytes + c * 16);
-        const int mm = m0 + row, nn = n0 + c * 8;
-        if (mm < p.M && nn < p.N) {
-            __half *dst = p.y + (size_t)mm * p.ldy + nn;
-            if (nn + 7 < p.N) {
-                *reinterpret_cast<uint4 *>(dst) = v;
-            } else {
-                const unsigned w[4] = {v.x, v.y, v.z, v.w};
-                for (int e = 0; e < 8 && nn + e < p.N; ++e)
-                    dst[e] = __ushort_as_half((unsigned short)(w[e / 2] >> (16 * (e % 2))));
-            }
-        }
-    }
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Four tokens of one channel per lane -> a 32 x 16 CB patch in LDS as fp16 [token][channel]: neighbouring lanes exchange half of
-// their values, so that each writes two channels of two tokens.
-__device__ __forceinline__ void patch_quad(char *at, int row_bytes, bool odd, const float (&v)[4])
-{
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-    const unsigned p01 = __builtin_bit_cast(unsigned, h2{(_Float16)v[0], (_Float16)v[1]}), p23 = __builtin_bit_cast(unsigned, h2{(_Float16)v[2], (_Float16)v[3]});
-    const unsigned kept = odd ? p23 : p01, got = (unsigned)__builtin_amdgcn_mov_dpp((int)(odd ? p01 : p23), 0xB1, 0xf, 0xf, true);
-    *reinterpret_cast<unsigned *>(at) = __builtin_amdgcn_perm(got, kept, odd ? 0x01000504u : 0x05040100u);
-    *reinterpret_cast<unsigned *>(at + row_bytes) = __builtin_amdgcn_perm(got, kept, odd ? 0x03020706u : 0x07060302u);
-}
-
 // A workgroup: KG groups of WAVES_M x WAVES_N wavefronts of 16 TB tokens x 16 CB channels; the groups take one part of K each.
 // WPF: stages that the weights are requested ahead.
 template <int WAVES_M, int WAVES_N, int TB, int CB, int WPF, int KG = 1>
@@ -358,7 +319,7 @@ __device__ __forceinline__ void w4_tile(const W4Params &p, int tm, int tn, char 
                 to_patch(at + b * 16 * T::ROW_BYTES + i * 32, s4, a, b_r[i]);
             }
         }
-        store_rows<CB * 2, T::PATCH_ROWS>(p, stg, T::ROW_BYTES, tm * TM + (wm * TB + group * BLOCKS) * 16, n_wave0, lane);
+        store_rows<CB * 2, T::PATCH_ROWS>(p.y, p.ldy, p.M, p.N, stg, T::ROW_BYTES, tm * TM + (wm * TB + group * BLOCKS) * 16, n_wave0, lane);
     } else {
 #pragma unroll
         for (int jb = 0; jb < TB / 2; ++jb) {
@@ -368,7 +329,7 @@ __device__ __forceinline__ void w4_tile(const W4Params &p, int tm, int tn, char 
 #pragma unroll
                 for (int i = 0; i < CB; ++i) to_patch(at + jj * 16 * T::ROW_BYTES + i * 32, s4, accf[i][2 * jb + jj], b_r[i]);
             }
-            store_rows<CB * 2, 32>(p, stg, T::ROW_BYTES, tm * TM + (wm * TB + 2 * jb) * 16, n_wave0, lane);
+            store_rows<CB * 2, 32>(p.y, p.ldy, p.M, p.N, stg, T::ROW_BYTES, tm * TM + (wm * TB + 2 * jb) * 16, n_wave0, lane);
         }
     }
 }
@@ -451,7 +412,7 @@ __global__ __launch_bounds__(256) void w4_finish_kernel(W4Params p, int splits)
         }
         patch_quad(at + jj * 16 * ROW_BYTES + i * 32, ROW_BYTES, odd, o);
     }
-    store_rows<CB * 2, 32>(p, stg, ROW_BYTES, m0, n0, lane);
+    store_rows<CB * 2, 32>(p.y, p.ldy, p.M, p.N, stg, ROW_BYTES, m0, n0, lane);
 }
 
 inline W4Params w4_params(const GemmArgs &a)

@@ -24,6 +24,45 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *p, unsigned bytes
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
 }
 
+// Writes a wavefront's staged block of ROWS tokens to y, 16 bytes per lane (LPR lanes per row).
+template <int LPR, int ROWS>
+__device__ __forceinline__ void store_rows(__half *y, int64_t ldy, int M, int N, const char *stg, int row_bytes, int m0, int n0, int lane)
+{
+    constexpr int RPI = 64 / LPR;
+    static_assert(64 % LPR == 0 && ROWS % RPI == 0, "whole rows per read-back instruction");
+    asm volatile("" ::: "memory");   // (same wavefront, LDS operations complete in order: only the compiler must keep them so)
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < ROWS / RPI; ++t) {
+        const int row = t * RPI + lane / LPR, c = lane % LPR;
+        const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * row_bytes + c * 16);
+        const int mm = m0 + row, nn = n0 + c * 8;
+        if (mm < M && nn < N) {
+            __half *dst = y + (size_t)mm * ldy + nn;
+            if (nn + 7 < N) {
+                *reinterpret_cast<uint4 *>(dst) = v;
+            } else {
+                const unsigned w[4] = {v.x, v.y, v.z, v.w};
+                for (int e = 0; e < 8 && nn + e < N; ++e)
+                    dst[e] = __ushort_as_half((unsigned short)(w[e / 2] >> (16 * (e % 2))));
+            }
+        }
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Four tokens of one channel per lane -> a patch in LDS as fp16 [token][channel]: neighbouring lanes exchange half of their
+// values, so that each writes two channels of two tokens.  `at`: the lane's first row, its pair of channels.
+__device__ __forceinline__ void patch_quad(char *at, int row_bytes, bool odd, const float (&v)[4])
+{
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    const unsigned p01 = __builtin_bit_cast(unsigned, h2{(_Float16)v[0], (_Float16)v[1]}), p23 = __builtin_bit_cast(unsigned, h2{(_Float16)v[2], (_Float16)v[3]});
+    const unsigned kept = odd ? p23 : p01, got = (unsigned)__builtin_amdgcn_mov_dpp((int)(odd ? p01 : p23), 0xB1, 0xf, 0xf, true);
+    *reinterpret_cast<unsigned *>(at) = __builtin_amdgcn_perm(got, kept, odd ? 0x01000504u : 0x05040100u);
+    *reinterpret_cast<unsigned *>(at + row_bytes) = __builtin_amdgcn_perm(got, kept, odd ? 0x03020706u : 0x07060302u);
+}
+
 // Hardware hands consecutive workgroup ids to the 8 XCDs in turn; give every XCD one contiguous
 // range of logical tiles, ordered (strips of `group` token tiles, channel tile by channel tile) so that the
 // tiles an XCD runs together form a block that shares activation and weight strips in that XCD's L2.
