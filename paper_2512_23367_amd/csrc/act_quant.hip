@@ -79,24 +79,6 @@ __device__ inline int token_of_workgroup(int M)
     return 8 * (xcd * (groups / 8) + (xcd < groups % 8 ? xcd : groups % 8)) + in_xcd;
 }
 
-// Maximum over the wavefront, or over its first 16 lanes, in steps inside the registers: a shuffle through LDS takes about a
-// hundred cycles, every token waited for six of them in turn and then read the wavefronts' maxima one by one.  us, before / after
-// (the first figure also has the branch in front of the loads): SwiGLU 512 x 11008 10.7 / 9.9, 1900 x 6144 17.8 / 16.7,
-// 4096 x 11008 50.4 / 48.9; plain 300 x 4096 3.7 / 3.2, 512 x 11008 6.9 / 6.3, 2048 x 14336 24.4 / 21.0; RMSNorm 1900 x 1536
-// 5.1 / 4.9, 2048 x 14336 33.2 / 30.7.
-template <bool WHOLE>
-__device__ inline unsigned max_over_lanes(unsigned v)
-{
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));        // row_shr:1, 2, 4, 8
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));
-    if constexpr (!WHOLE) return (unsigned)__builtin_amdgcn_readlane((int)v, 15);
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));       // row_bcast:15 into rows 1 and 3
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));       // row_bcast:31 into rows 2 and 3
-    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
-}
-
 template <int MODE, int NC>
 __global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_kernel(const __half *__restrict__ x, int64_t ldx, int M, int K,
                                                                     const float *__restrict__ inv_smooth,
@@ -153,8 +135,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_kernel(const __half 
 #pragma unroll
             for (int e = 0; e < 16; ++e) ss = __builtin_fma((double)f[e], (double)f[e], ss);
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+        ss = sum_pair<1>(sum_pair<2>(sum_pair<4>(sum_pair<8>(sum_pair<16>(sum_pair<32>(ss))))));
         if (lane == 0) red_ss[wave] = ss;
         __syncthreads();
         double tot = 0.0;

@@ -205,7 +205,11 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_kernel(DecodeParams p)
         unsigned mx = 0;
 #pragma unroll
         for (int sl = 0; sl < FQ_SLOTS; ++sl) mx = abs_max_bits(keep[sl], mx);   // pieces beyond the range hold zeros
-        for (int off = 32; off >= (1 << fq_lg); off >>= 1) mx = max(mx, (unsigned)__shfl_xor((int)mx, off, 64));
+        mx = max_pair<16>(max_pair<32>(mx));               // over the lanes of one token
+        if (fq_lg < 4) mx = max_pair<8>(mx);
+        if (fq_lg < 3) mx = max_pair<4>(mx);
+        if (fq_lg < 2) mx = max_pair<2>(mx);
+        if (fq_lg < 1) mx = max_pair<1>(mx);
         if (lane < (1 << fq_lg)) amax_red[wave][lane] = mx;
         __syncthreads();
         unsigned a = 0;
@@ -237,7 +241,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_kernel(DecodeParams p)
         v4i wv[U][C], xv[XL ? 1 : U][MH];
         const int th0 = 4 * c0, th1 = c0 < c1 ? 4 * c1 : 4 * c0;
         if constexpr (!XL && MH >= 2) {
-            // Tokens from L2, 17 tokens and more (measured on one box against conditional pointer loads: 1-9 % faster
+            // Tokens from L2, 17 tokens and more (measured against conditional pointer loads: 1-9 % faster
             // at 32 and 64 tokens, 1-5 % slower with 16 tokens or fewer, which keep the loop below): every ring slot takes C weight and MH token fragments through range-checked buffer
             // loads.  Absent channel groups and token rows get a lane offset behind the buffer, and chunks past this
             // wavefront's range a buffer of zero length: such loads return zeros and cost no traffic.  Every slot
@@ -354,7 +358,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_kernel(DecodeParams p)
         v4i wv[U][C], xv[XL ? 1 : U][2][MH];
         // 17 tokens and more (8 wavefronts; the accumulator dump runs the same loop): branch-free refills through range-checked buffer loads, as
         // in the int8 loop above (absent rows and channel groups: lane offset behind the buffer; groups past this
-        // wavefront's range: a buffer of zero length).  Measured on one box against the conditional pointer loads:
+        // wavefront's range: a buffer of zero length).  Measured against the conditional pointer loads:
         // 2-10 % faster at 64 tokens, 1-4 % at 128, 3-5 % slower with 16 wavefronts (kept on the old loop).
         constexpr bool BR = !XL && MH >= 2 && WAVES == 8;
         constexpr unsigned OOB = 0xFFFFF000u;

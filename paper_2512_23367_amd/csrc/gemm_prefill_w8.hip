@@ -268,7 +268,7 @@ int launch(const GemmArgs &a, hipStream_t st)
 // The forms and their estimated time: 3 us + the weights at 20 TB/s + the output at 7 TB/s + what the busiest CU does, in
 // rounds of as many workgroups as fit it together (a round of n takes o[n - 1] + stages x c[n - 1], groups: their steps), but not
 // less than the weights take to arrive (5.5 us + 3.6 TB/s).  Fitted to 180 shapes (48..4096 tokens, N 1536..22016, K 1536..11008,
-// weights from HBM), within 3 to 10 % on average each on the box they were fitted on; other boxes are slower by up to a tenth, hence the factor.
+// weights from HBM), within 3 to 10 % on average each on the card they were fitted on; other cards are slower by up to a tenth, hence the factor.
 struct W8Form {
     int variant, tm, tn, per_cu, groups;
     double o[4], c[4];

@@ -158,6 +158,67 @@ __device__ inline float swiglu_f32(float g, float u)
     return (g * reciprocal_of_sum(d)) * u;
 }
 
+// {a, b} = {v of this lane, v of lane ^ OFF}, in either order, without the hundred cycles of a shuffle through LDS: for operations
+// that commute, in the pairs of a butterfly.  us, shuffles / these steps: SmoothQuant + Hadamard quantizer and W4A8 GEMM of 3001 x
+// 4096 x 4096 70.5 / 67.5; decoder layer with the quantizer in the decode GEMMs, 1 token W8A8 52.4 / 51.5, 8 tokens W4A8 48.0 / 46.7;
+// RMSNorm of 2048 x 14336 31.6 / 30.8.
+template <int OFF>
+__device__ inline void lane_pair(unsigned v, unsigned &a, unsigned &b)
+{
+    static_assert(OFF == 32 || OFF == 16 || OFF == 8 || OFF == 4 || OFF == 2 || OFF == 1, "a power of two below 64");
+    a = v;
+    if constexpr (OFF == 32) {
+        const auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);     // lower halves, upper halves
+        a = s[0], b = s[1];
+    } else if constexpr (OFF == 16) {
+        const auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);     // even rows, odd rows
+        a = s[0], b = s[1];
+    } else if constexpr (OFF == 8) {
+        b = (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true);   // row_ror:8
+    } else if constexpr (OFF == 4) {
+        const int up = __builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xf, 0x5, false);   // row_shl:4 into banks 0 and 2
+        b = (unsigned)__builtin_amdgcn_update_dpp(up, (int)v, 0x114, 0xf, 0xa, false);   // row_shr:4 into banks 1 and 3
+    } else {
+        b = (unsigned)__builtin_amdgcn_mov_dpp((int)v, OFF == 2 ? 0x4E : 0xB1, 0xf, 0xf, true);   // quad_perm
+    }
+}
+
+template <int OFF>
+__device__ inline unsigned max_pair(unsigned v)
+{
+    unsigned a, b;
+    lane_pair<OFF>(v, a, b);
+    return max(a, b);
+}
+
+template <int OFF>
+__device__ inline double sum_pair(double v)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    unsigned a0, a1, b0, b1;
+    lane_pair<OFF>((unsigned)u, a0, b0);
+    lane_pair<OFF>((unsigned)(u >> 32), a1, b1);
+    return __builtin_bit_cast(double, (uint64_t)a1 << 32 | a0) + __builtin_bit_cast(double, (uint64_t)b1 << 32 | b0);
+}
+
+// Maximum over the wavefront, or over its first 16 lanes, in steps inside the registers: a shuffle through LDS takes about a
+// hundred cycles, every token waited for six of them in turn and then read the wavefronts' maxima one by one.  us, before / after
+// (the first figure also has the branch in front of the loads): SwiGLU 512 x 11008 10.7 / 9.9, 1900 x 6144 17.8 / 16.7,
+// 4096 x 11008 50.4 / 48.9; plain 300 x 4096 3.7 / 3.2, 512 x 11008 6.9 / 6.3, 2048 x 14336 24.4 / 21.0; RMSNorm 1900 x 1536
+// 5.1 / 4.9, 2048 x 14336 33.2 / 30.7.
+template <bool WHOLE>
+__device__ inline unsigned max_over_lanes(unsigned v)
+{
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));        // row_shr:1, 2, 4, 8
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));
+    if constexpr (!WHOLE) return (unsigned)__builtin_amdgcn_readlane((int)v, 15);
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));       // row_bcast:15 into rows 1 and 3
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));       // row_bcast:31 into rows 2 and 3
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 // token scale and its reciprocal from the bit pattern of the largest |x|
 __device__ inline void token_scales(unsigned amax_bits, float &scale, float &inv)
 {

@@ -277,12 +277,12 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_hadamard_kernel(cons
     float amax = 0.0f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) amax = __builtin_elementwise_maximum(amax, fabsf(v[0][i]));   // passes a NaN on
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) amax = __builtin_elementwise_maximum(amax, __shfl_xor(amax, off, 64));
+    amax = __uint_as_float(max_over_lanes<true>(__float_as_uint(amax)));   // not negative, a NaN above all: ordered like their bits
     if (nwaves > 1) {
         if (lane == 0) red[wave] = amax;
         __syncthreads();
-        for (int w = 0; w < nwaves; ++w) amax = __builtin_elementwise_maximum(amax, red[w]);
+        static_assert(MAX_WAVES <= 16, "one row of lanes takes the wavefronts' maxima");
+        amax = __uint_as_float(max_over_lanes<false>(lane < nwaves ? __float_as_uint(red[lane]) : 0u));
     }
     float scale, inv;
     token_scales_f32(amax, scale, inv);
@@ -409,11 +409,10 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void weight_transform_quant_kernel(
         float mx = amax[0];
 #pragma unroll
         for (int it = 1; it < NIT; ++it) mx = fmaxf(mx, amax[it]);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+        mx = __uint_as_float(max_over_lanes<true>(__float_as_uint(mx)));
         if (lane == 0) red[wave] = mx;
         __syncthreads();
-        for (int i = 0; i < nwaves; ++i) mx = fmaxf(mx, red[i]);
+        mx = __uint_as_float(max_over_lanes<false>(lane < nwaves ? __float_as_uint(red[lane]) : 0u));
         float s = mx / 127.0f;
         if (s == 0.0f) s = 1.0f;
         if (real && scales && threadIdx.x == 0) static_cast<float *>(scales)[n] = s;
@@ -433,9 +432,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void weight_transform_quant_kernel(
         for (int it = 0; it < NIT; ++it) {
             const int c = c0 + it * 64;
             float mx = amax[it];   // a group of 128 is the eight chunks of lanes 8i .. 8i + 7
-            mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
-            mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
-            mx = fmaxf(mx, __shfl_xor(mx, 4, 64));
+            mx = __uint_as_float(max_pair<4>(max_pair<2>(max_pair<1>(__float_as_uint(mx)))));
             __half s16 = __float2half_rn(mx / 7.0f);
             if (__half2float(s16) == 0.0f) s16 = __float2half_rn(1.0f);
             const float s = __half2float(s16);
