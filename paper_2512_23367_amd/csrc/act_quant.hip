@@ -160,7 +160,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64) void act_quant_kernel(const __half 
             float g[16];
             widen(KEEP ? gm[KEEP ? it : 0] : load_chunk(rv, at(it, 32u)), g);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) f[e] = (f[e] * rnorm) * g[e];
+            for (int e = 0; e < 16; ++e) f[e] = __builtin_fmaf(__builtin_fmaf(f[e], rnorm, 0.0f), g[e], 0.0f);   // widened in the multiply
         }
         if constexpr (MODE == 3) {
             float up[16];
