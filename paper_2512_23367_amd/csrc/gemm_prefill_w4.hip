@@ -128,7 +128,8 @@ __device__ __forceinline__ void w4_tile(const W4Params &p, int tm, int tn, char 
 #pragma unroll
         for (int i = 0; i < CB; ++i) {
             const unsigned off = soff + i * 32;
-            sc[i] = __builtin_amdgcn_raw_buffer_load_b16(sr, off, k * p.Npad * 2, 0);
+            if constexpr (EPI == EPI_ACC) sc[i] = 0;
+            else sc[i] = __builtin_amdgcn_raw_buffer_load_b16(sr, off, k * p.Npad * 2, 0);
         }
     };
 
@@ -189,7 +190,9 @@ __device__ __forceinline__ void w4_tile(const W4Params &p, int tm, int tn, char 
     // Main loop, one barrier per stage.  Token fragments are read one block ahead; in front of the last block's products the
     // wavefront hands its stage over (own reads done; its share of the next stage had landed before it unpacked this one;
     // barrier: then everyone's has) and refills the freed buffer.
-    constexpr int NEWER = XL + (WPF - 1) * 2 * CB;      // loads issued behind a stage's weights: the tokens of one stage, the weights of WPF - 1
+    // Loads issued behind a stage's weights: the tokens of one stage, the weights and scales of WPF - 1 (the accumulator dump uses no
+    // scales, and the compiler leaves their loads out: counting them let a stage be handed over before its tokens were there)
+    constexpr int NEWER = XL + (WPF - 1) * (EPI == EPI_ACC ? 1 : 2) * CB;
     auto stage = [&](int it, v4i (&w)[CB], short (&sc)[CB]) {
         wait_vmcnt<NEWER>();
         v4i wf[CB][2];
