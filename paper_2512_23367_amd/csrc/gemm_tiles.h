@@ -41,10 +41,14 @@ __device__ __forceinline__ void store_rows(__half *y, int64_t ldy, int M, int N,
             __half *dst = y + (size_t)mm * ldy + nn;
             if (nn + 7 < N) {
                 *reinterpret_cast<uint4 *>(dst) = v;
-            } else {
-                const unsigned w[4] = {v.x, v.y, v.z, v.w};
-                for (int e = 0; e < 8 && nn + e < N; ++e)
-                    dst[e] = __ushort_as_half((unsigned short)(w[e / 2] >> (16 * (e % 2))));
+            } else {   // the last N % 8 channels: four, two and one of them (as up to seven stores in a loop: 620 x 256 x 191,
+                       // int4, 5.6 us against 4.1; 4097 x 1152 x 3487 in 128 x 256 tiles 32.7 against 28.0)
+                const int left = N - nn;
+                const bool four = left & 4;
+                if (four) *reinterpret_cast<uint2 *>(dst) = make_uint2(v.x, v.y);
+                const unsigned lo = four ? v.z : v.x, hi = four ? v.w : v.y;
+                if (left & 2) *reinterpret_cast<unsigned *>(dst + (left & 4)) = lo;
+                if (left & 1) dst[left & 6] = __ushort_as_half((unsigned short)(left & 2 ? hi : lo));
             }
         }
     }
