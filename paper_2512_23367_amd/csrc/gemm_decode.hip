@@ -873,9 +873,14 @@ double decode_estimate_us(const GemmArgs &a)
     // (fits the measured 7B decode GEMMs within 10 %); from 33 tokens the blocked plan's model
     if (a.M <= 32) return 3.5 + (double)a.N * a.K * a.bits / 8.0 / 7.2e6;
     const BlockedPlan plan = plan_blocked(a.M, a.N, a.K, a.bits == 4);
-    // int4, for the comparison with the tile kernels: a pass costs more and its bytes less than the common model says (512 x 1024
-    // x 4096 12.4 us where it says 9.9, 768 x 11008 x 4096 64 where it says 72); within 8 % on 40 shapes of 96..1024 tokens
-    return a.bits == 4 && plan.passes > 0.0 ? 1.0 + plan.passes * (4.0 + plan.wg_bytes / 61.5e3) : plan.us;   // (no form fits: 1e30)
+    // int4, for the comparison with the tile kernels: what a pass costs depends on the block and the channel groups, and its bytes cost
+    // less than the common model says: one pass of blocks of 32 with one or two groups takes 3.6 us + bytes, of 64 with four 5.9, two of those
+    // 9.7.  Within 6 % on average on 2500 shapes of 33..1024 tokens, K 128..20480.  With one cost for all, fitted to K of 4096 and up
+    // (18 % off on these), short K went to the tiles: 75 x 512 x 1575 6.0 us where this takes 4.1, 298 x 768 x 704 6.0 and 4.4.
+    // (0.97: where the two come close the tiles turn out the slower ones more often; 2800 shapes, the pick 0.2..1.2 % behind the faster one.)
+    if (a.bits == 4 && plan.passes > 0.0)
+        return 0.97 * (2.0 + plan.passes * (1.55 + 0.45 * (plan.c > 2 ? plan.c - 2 : 0) + (plan.block == 64 ? 1.3 : 0.0) + plan.wg_bytes / 57.8e3));
+    return plan.us;   // (no form fits: 1e30)
 }
 
 void decode_plan(const GemmArgs &a, int *token_block, int *channel_groups)

@@ -85,6 +85,17 @@ def test_each_int4_tile_form_is_the_choice_somewhere():
         assert (p.family, p.variant, p.splits, p.rest_channels) == (ql.QL_FAMILY_TILE, variant, 1, 0)
 
 
+def test_int4_short_k_stays_with_the_kernels_that_are_faster_there():
+    """33 to about 300 tokens with K up to 1536: measured, us, decode kernels / best tile form."""
+    for M, K, N, scratch in [(75, 512, 1575, 6815744),        # 4.1 / 4.8
+                             (116, 384, 135, 334848),         # 3.6 / 5.8
+                             (227, 640, 2034, 16777216),      # 4.7 / 6.1
+                             (298, 768, 704, 6437120),        # 4.4 / 5.8
+                             (128, 1536, 1536, 6291456),      # 4.6 / 8.6
+                             (194, 2688, 4562, 0)]:           # 11.2 / 13.1
+        assert plan(M, N, K, bits=4, scratch=scratch).family == ql.QL_FAMILY_DECODE, (M, K, N)
+
+
 def test_estimates_are_finite_positive_and_grow_with_k():
     for M in (1, 64, 300, 2048):
         last = 0.0
