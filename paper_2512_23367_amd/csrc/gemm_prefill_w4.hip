@@ -517,7 +517,7 @@ int launch_w4_tail(const GemmArgs &a, int first_tiles, hipStream_t st)
 // One 128 x 256 tile per CU by eight wavefronts (1 x 8 of 128 x 32): one round only, 2048 x 4096 x 4096 39.9 us, the others 42.6..54.
 // Combined form: whole passes of 128 x 256 (512 tiles), possibly half a one, the remaining channels in 128 x 128 tiles, two
 // per CU: 2048 x 4096 x 22016 183.6 us, 128 x 256 alone 197, 128 x 128 alone 192; 3500 tokens 325 / 329 / 332.
-// K in parts (only where scratch is offered, which is how a caller allows the sums to be taken in parts):
+// K in parts (only where the scratch offered holds the partial sums, which is how a caller allows them to be taken in parts):
 //   over two or four groups of four wavefronts of one workgroup, 64 x 128 tiles, where these fit one pass: the sums meet in LDS,
 //   the scratch is not touched.  512 x 11008 x 4096 32.1 us (four; two 34.9; 64 x 128 unsplit 49.5, split over
 //   workgroups 41.5), 1280 x 6144 x 1536 18.7 / 19.2 / 24.7 / 28.8, 512 x 4096 x 4096 15.1 / 15.4 / 18.8 / 24.4.  Not up to 64 tokens,
@@ -553,6 +553,10 @@ struct W4Choice {
     double us;
 };
 
+// What a caller has to offer before K is taken in two or four parts: the bytes of the split over workgroups that the value stands for
+// (the groups touch none of it).  One rule for the automatic choice and for the values asked for.
+inline size_t groups_scratch(const GemmArgs &a, int groups) { return split_bytes(a, 128, groups == 2 ? 128 : 256, groups); }
+
 inline W4Choice choose_w4(const GemmArgs &a, size_t scratch)
 {
     const int stages = a.K / 128;
@@ -579,8 +583,8 @@ inline W4Choice choose_w4(const GemmArgs &a, size_t scratch)
     }
     if (!scratch) return best;
     if (a.M > 64 && tiles(64, 128) <= 256) {
-        offer(W4_GROUPS2, 2, 0, base + 0.6 + 0.66 * ceil_div(stages, 2));
-        offer(W4_GROUPS4, 4, 0, base + 2.1 + 1.22 * ceil_div(stages, 4));
+        if (scratch >= groups_scratch(a, 2)) offer(W4_GROUPS2, 2, 0, base + 0.6 + 0.66 * ceil_div(stages, 2));
+        if (scratch >= groups_scratch(a, 4)) offer(W4_GROUPS4, 4, 0, base + 2.1 + 1.22 * ceil_div(stages, 4));
     }
     for (int s = 2; s <= 32 && stages / s >= 4; ++s)
         for (const W4Form *f : {&mid, &one}) {
@@ -623,7 +627,7 @@ int launch_gemm_prefill_w4(const GemmArgs &a, int variant, hipStream_t st)
     case 23: case 43: c = {W4_TAIL, 1, (2 * ceil_div(a.N, 256) + 2) / 3, 0.0}; break;   // two thirds of the channel tiles in front
     default:
         if (variant >= 202 && variant <= 232) c = {variant, variant - W4_SPLIT, 0, 0.0};
-        if (variant >= 302 && variant <= 332 && split_bytes(a, 128, 256, variant - W4_SPLIT256) <= scratch)
+        if (variant >= 302 && variant <= 332 && split_bytes(a, 128, 256, variant - W4_SPLIT256) <= scratch)   // (304: groups_scratch)
             c = {variant, variant - W4_SPLIT256, 0, 0.0};
     }
     if (c.shape == W4_TAIL && c.first_tiles >= ceil_div(a.N, 256)) c.shape = W4_128X256;
@@ -636,8 +640,8 @@ int launch_gemm_prefill_w4(const GemmArgs &a, int variant, hipStream_t st)
     case W4_96X128: return launch_w4<1, 4, 6, 2, 2, EPI_F16, 3>(a, st);
     case W4_TAIL: return launch_w4_tail(a, c.first_tiles, st);
     case W4_GROUPS2:
-        if (variant == W4_GROUPS2 && split_bytes(a, 128, 128, 2) > scratch)   // asked for by value: refused as the other values are
-            return fail(QL_ERR_WORKSPACE, "split-K needs %zu bytes of workspace", split_bytes(a, 128, 128, 2));
+        if (scratch < groups_scratch(a, 2))   // asked for by value: refused as the other values are
+            return fail(QL_ERR_WORKSPACE, "split-K needs %zu bytes of workspace", groups_scratch(a, 2));
         return launch_w4<1, 4, 4, 2, 2, EPI_F16, 1, 2>(a, st);
     case W4_GROUPS4: return launch_w4<1, 4, 4, 2, 2, EPI_F16, 1, 4>(a, st);
     default:

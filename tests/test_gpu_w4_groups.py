@@ -36,3 +36,18 @@ def test_forms_and_parts_of_k(G, M, K, N, bias):
         ql.ql_set_kernel_variant(0)
     for v in (4, 17, 19) + ((202, 304) if K == 128 else ()):       # the same order of the sums: the same bits
         assert (outs[v].view(np.uint16) == outs[26].view(np.uint16)).all(), v
+
+
+@pytest.mark.parametrize("M,K,N", [(512, 2048, 1024), (200, 4096, 520)])
+def test_a_little_scratch_does_not_change_the_sums(G, M, K, N):
+    """Too little scratch for a split is as good as none: the same order of the sums, the same bits."""
+    import torch
+    x, w = synth.activations(M, K, 0, "single"), synth.weights(N, K, 0, "single")
+    g = G.gpu_quant_weight(w, 4, 128)
+    _, sx, xk = G.gpu_quant_act(x)
+    sx, outs = G.dev(sx), []
+    for ws in (None, G.empty_bytes(16), G.empty_bytes(4096)):
+        y = torch.zeros((M, N), dtype=torch.float16, device=G.DEV)
+        ql.ql_w4a8_gemm(xk, sx, M, K, g["kernel"], 128, None, N, y, ws)
+        outs.append(y)
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
