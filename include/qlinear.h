@@ -202,8 +202,8 @@ int ql_w4a8_gemm_acc_i32(const int8_t *xq_kernel, int M, int K, const void *w4_k
  *   blocks of 32 / 64; 130 quantizer never fused into the decode GEMM.  int4 weights have tile forms of their own (tokens x
  *   channels): 6, 26 = 128x256, two per CU; 15, 35 = 96x256; 4, 11 = 128x128; 13 = 64x128; 19, 20, 39 = 96x128; 23, 43 = 128x256 with
  *   the last third of the channels in 128x128 tiles; every other tile value = 128x256, one per CU.  202 / 304: K in two / four
- *   parts, each taken by a group of four wavefronts of the workgroup (64x128 tiles; the sums meet on the CU, the scratch that
- *   these values ask for stays unused); 203..232 / 302, 303, 305..332: that many workgroups per 128x128 / 128x256 tile
+ *   parts, each taken by a group of four wavefronts of the workgroup (64x128 tiles; the sums meet on the CU: the scratch of a
+ *   split over workgroups, 128x128 / 128x256 tiles, has to be offered, as it is for every other order of the sums, and stays unused); 203..232 / 302, 303, 305..332: that many workgroups per 128x128 / 128x256 tile
  *   (302..332: unsplit where the scratch does not hold the partial sums).
  *   Unknown values -> QL_ERR_UNSUPPORTED. */
 int ql_set_kernel_variant(int variant);
@@ -219,9 +219,11 @@ typedef struct ql_plan {
     int family;         /* QL_FAMILY_DECODE: weight-streaming kernels (every workgroup owns tile_channels channels and
                            the whole K for a block of tile_tokens tokens); QL_FAMILY_TILE: prefill tile kernels */
     int variant;        /* the ql_set_kernel_variant value closest to this choice */
-    int tile_tokens;    /* tokens x channels one workgroup owns; with splits > 1, that `splits` workgroups produce together */
+    int tile_tokens;    /* tokens x channels that one workgroup produces, or `splits` workgroups that share its K range */
     int tile_channels;
-    int splits;         /* parts that the K range is summed in (1: unsplit; > 1 only where scratch is offered) */
+    int splits;         /* parts that the K range is summed in (1: unsplit; > 1 only where the scratch holds the partial sums):
+                           one workgroup each, except variants 202 and 304 of int4 weights, where groups of one workgroup's
+                           wavefronts take a part each, and 52 and 54 of int8, which report 1 (their sums are exact) */
     double est_us;      /* the estimate the choice was made by, microseconds (model fitted to measurements on MI355X) */
     int rest_channels;  /* > 0: the GEMM runs as two launches on disjoint channel ranges -- the first N - rest_channels
                            channels as described above (whole passes over the CUs), the last rest_channels channels with */

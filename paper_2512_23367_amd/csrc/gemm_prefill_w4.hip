@@ -606,7 +606,8 @@ void prefill_w4_plan(const GemmArgs &a, int *variant, int *tile_tokens, int *til
     const W4Choice c = choose_w4(a, a.ws ? a.ws_bytes : 0);
     *splits = c.splits;
     *variant = c.shape;
-    *tile_tokens = 128, *tile_channels = c.shape > W4_SPLIT256 || c.shape == W4_TAIL ? 256 : 128;
+    const bool groups = c.shape == W4_GROUPS2 || c.shape == W4_GROUPS4;
+    *tile_tokens = groups ? 64 : 128, *tile_channels = !groups && (c.shape > W4_SPLIT256 || c.shape == W4_TAIL) ? 256 : 128;
     for (const W4Form &f : W4_FORMS)
         if (f.shape == c.shape) *tile_tokens = f.tm, *tile_channels = f.tn;
 }

@@ -63,12 +63,13 @@ def test_split_k_needs_scratch_and_fits_it():
     assert without.splits == 1
     small = plan(M, N, K, scratch=1 << 20)      # room for no split of this shape
     assert small.splits == 1
-    # the int4 kernels split too, and report the variant that selects the same split: 200 + splits on 128x128 tiles, 300 + splits
-    # on 128x256
-    for shape, variant, channels in [((512, 4096, 11008), 304, 256), ((1536, 1536, 6144), 303, 256), ((1280, 1536, 6144), 202, 128)]:
+    # the int4 kernels take K in parts too: 200 + splits over workgroups on 128x128 tiles, 300 + splits on 128x256, and by groups of one
+    # workgroup's wavefronts on 64x128 tiles (202, 304), for which the bytes of the split over workgroups have to be offered
+    for shape, variant, tile in [((512, 4096, 11008), 304, (64, 128)), ((1536, 1536, 6144), 303, (128, 256)), ((1280, 1536, 6144), 202, (64, 128))]:
         p4 = plan(*shape, bits=4)
-        assert (p4.family, p4.variant, p4.tile_tokens, p4.tile_channels) == (ql.QL_FAMILY_TILE, variant, 128, channels)
+        assert (p4.family, p4.variant, (p4.tile_tokens, p4.tile_channels)) == (ql.QL_FAMILY_TILE, variant, tile)
         assert p4.splits == variant % 100
+        channels = 256 if variant > 300 else 128
         tiles = -(-shape[0] // 128) * -(-shape[1] // channels)
         assert p4.splits * tiles * 128 * channels * 4 <= SCRATCH
         assert plan(*shape, bits=4, scratch=0).splits == 1
@@ -76,13 +77,15 @@ def test_split_k_needs_scratch_and_fits_it():
 
 def test_each_int4_tile_form_is_the_choice_somewhere():
     """... and the two-region form needs no second launch."""
-    for (M, N, K), variant in [((4096, 12288, 4096), 26),      # three whole passes of 256x256
-                               ((3001, 4096, 4096), 35),       # 256 tiles of 192x256: one pass
-                               ((2048, 4096, 4096), 37),       # 256 tiles of 128x256
-                               ((1100, 3584, 4096), 13),       # 252 tiles of 128x128, one per CU
-                               ((4096, 22016, 4096), 43)]:     # five passes of 256x256, the last 1536 channels in 128x256
+    for (M, N, K), variant, tile in [((4096, 12288, 4096), 26, (128, 256)),   # 1536 tiles, two per CU: three whole rounds
+                                     ((3001, 4096, 4096), 35, (96, 256)),     # 512 tiles, two per CU: one round
+                                     ((2048, 4096, 4096), 37, (128, 256)),    # 256 tiles, one per CU, by eight wavefronts
+                                     ((1600, 12288, 4096), 4, (128, 128)),    # 1248 tiles, three per CU: two rounds less a little
+                                     ((1100, 3584, 4096), 13, (64, 128)),     # 504 tiles, two of four per CU
+                                     ((1100, 8192, 2048), 19, (96, 128)),     # 768 tiles, three per CU: one round
+                                     ((4096, 22016, 4096), 43, (128, 256))]:  # five rounds of 128x256, the last 1536 channels in 128x128
         p = plan(M, N, K, bits=4)
-        assert (p.family, p.variant, p.splits, p.rest_channels) == (ql.QL_FAMILY_TILE, variant, 1, 0)
+        assert (p.family, p.variant, (p.tile_tokens, p.tile_channels), p.splits, p.rest_channels) == (ql.QL_FAMILY_TILE, variant, tile, 1, 0)
 
 
 def test_int4_short_k_stays_with_the_kernels_that_are_faster_there():

@@ -4,12 +4,11 @@ import pytest
 from paper_2512_23367_amd import binding as ql
 
 
-@pytest.mark.parametrize("M,N,K", [(65, 4096, 4096), (200, 4096, 11008), (512, 4096, 8192), (300, 1536, 16384), (1024, 2048, 6144)])
-def test_groups_fit_one_pass_and_need_the_callers_leave(M, N, K):
+@pytest.mark.parametrize("M,N,K,variant", [(200, 8192, 11008, 304), (512, 4096, 8192, 304), (1024, 2048, 6144, 202), (1280, 1536, 6144, 202)])
+def test_groups_fit_one_pass_and_need_the_callers_leave(M, N, K, variant):
     p = ql.ql_plan_gemm(M, N, K, 4, 128, 64 << 20)
-    if p.variant in (202, 304):
-        assert M > 64 and -(-M // 64) * -(-N // 128) <= 256 and p.splits == p.variant % 100
-        assert p.tile_tokens * p.tile_channels == p.splits * 64 * 128
+    assert (p.variant, p.splits, p.tile_tokens, p.tile_channels) == (variant, variant % 100, 64, 128)
+    assert M > 64 and -(-M // 64) * -(-N // 128) <= 256
     bare = ql.ql_plan_gemm(M, N, K, 4, 128, 0)
     assert bare.splits == 1 and bare.est_us >= p.est_us
 
