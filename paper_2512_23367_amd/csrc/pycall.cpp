@@ -31,6 +31,8 @@ struct Library {
 
 // An argument that is not in order: the caller returns None.
 struct NotPlain {};
+// A Python exception on its way (a keyboard interrupt may arrive wherever Python code runs): the caller passes it on.
+struct Raised {};
 
 const at::Tensor &tensor(PyObject *o)
 {
@@ -72,9 +74,10 @@ float as_float(PyObject *o)
 void *stream_from(PyObject *ask)
 {
     PyObject *o = PyObject_CallNoArgs(ask);
-    void *p = o && PyLong_Check(o) ? PyLong_AsVoidPtr(o) : nullptr;
-    const bool failed = !o || !PyLong_Check(o) || PyErr_Occurred();
-    Py_XDECREF(o);
+    if (!o) throw Raised();
+    void *p = PyLong_Check(o) ? PyLong_AsVoidPtr(o) : nullptr;
+    const bool failed = !PyLong_Check(o) || PyErr_Occurred();
+    Py_DECREF(o);
     if (failed) throw NotPlain();   // (binding.py asks again and reports what is wrong)
     return p;
 }
@@ -159,6 +162,8 @@ PyObject *call(Py_ssize_t given, Py_ssize_t wanted, Prepare prepare)
         PyThreadState *state = PyEval_SaveThread();
         status = launch();
         PyEval_RestoreThread(state);
+    } catch (const Raised &) {
+        return nullptr;
     } catch (...) {   // NotPlain, or what a tensor throws when it is asked for its storage
         PyErr_Clear();
         Py_RETURN_NONE;

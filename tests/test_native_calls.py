@@ -215,3 +215,19 @@ def test_no_wrong_argument_passes_the_native_checks(monkeypatch):
         assert called == []
     finally:
         ql._bind_native(ql.lib())
+
+
+@pytest.mark.gpu
+def test_an_exception_while_the_stream_is_asked_for_is_passed_on():
+    """A keyboard interrupt may arrive wherever Python code runs; here that is the function that knows the stream."""
+    def interrupted():
+        raise KeyboardInterrupt
+
+    ql.lib()
+    try:
+        called, kept = bind_stand_ins(ql._native)
+        with pytest.raises(KeyboardInterrupt):
+            ql._native.quant_act(*good_arguments()["quant_act"], interrupted)
+        assert called == [] and ql._native.quant_act(*good_arguments()["quant_act"], lambda: "no stream") is None
+    finally:
+        ql._bind_native(ql.lib())
