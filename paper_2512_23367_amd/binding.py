@@ -9,6 +9,8 @@ from __future__ import annotations
 import ctypes
 import functools
 import os
+import warnings
+from importlib import import_module
 
 import torch
 
@@ -113,8 +115,12 @@ _native = None
 def _bind_native(l):
     global _native
     try:
-        from . import _qlcall
-    except ImportError:
+        _qlcall = import_module(f"{__package__}._qlcall")
+    except ModuleNotFoundError:
+        return
+    except ImportError as e:
+        warnings.warn(f"the call module _qlcall does not load, calls are marshalled in Python, 2 to 3 us slower each (built against another "
+                      f"torch? rebuild with `python -m paper_2512_23367_amd.build`): {e}", RuntimeWarning)
         return
     names = ("ql_weight_bytes", "ql_act_kernel_bytes", "ql_w8a8_linear", "ql_w4a8_linear", "ql_w8a8_gemm", "ql_w4a8_gemm",
              "ql_quant_act_per_token", "ql_quant_act_rmsnorm", "ql_quant_act_swiglu", "ql_quant_act_per_token_transformed")
