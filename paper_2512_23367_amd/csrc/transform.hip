@@ -661,10 +661,13 @@ int launch_smooth_scales(const float *xmax, const __half *w, int N, int K, float
 {
     // One workgroup per 64 channels pulls its N x 128 bytes in 2 + N / 235 us, however few of them there are.  Several per strip and two
     // small launches around them take 7 us + the bytes at 4 TB/s: taken where that is a tenth less, unless a result lies over an
-    // input that a later launch reads.  N x K, us, one against several: 4608 x 1536 21.2 / 10.4, 6144 x 2048 26.7 / 13.0, 12288 x 4096
-    // 52.0 / 30.1, 4096 x 4096 20.4 / 15.8, 2048 x 2048 11.4 / 9.3; the other way 1536 x 6144 10.9 / 12.5, 3000 x 8192 16.6 / 18.0.
+    // input that a later launch reads.  N x K, us, one against several, weights from HBM: 4608 x 1536 21.2 / 10.4, 6144 x 2048 26.7 / 13.0,
+    // 12288 x 4096 52.0 / 30.1, 4096 x 4096 20.4 / 15.8, 2048 x 2048 11.4 / 9.3; the other way 1536 x 6144 10.9 / 12.5, 3000 x 8192 16.6 /
+    // 18.0.  Not below 2048 rows: there one workgroup takes anything from 5.8 to 10.7 us by the row's length (fewest where it is no multiple
+    // of 1 KB) and several 8.0 to 9.9 (1484 x 512 6.3 / 8.1, 2007 x 512 7.4 / 8.2, 1992 x 1920 9.4 / 9.9; 1902 x 1024 10.7 / 9.7).
+    // Weights that are still in a cache have one the faster up to 3800 rows: 2048 x 2048 6.0 / 7.5, 3072 x 1024 7.0 / 7.7, 4096 x 1024 8.0 / 7.8.
     const int strips = K / 64, parts = std::min(ceil_div(384, strips), N / 512);
-    const bool several = parts > 1 && 7.0 + 0.5e-6 * N * K < 0.9 * (2.0 + N / 235.0);
+    const bool several = N >= 2048 && parts > 1 && 7.0 + 0.5e-6 * N * K < 0.9 * (2.0 + N / 235.0);
     auto over_inputs = [&](const float *p) {
         return bytes_overlap(p, (size_t)K * 4, xmax, (size_t)K * 4) || bytes_overlap(p, (size_t)K * 4, w, (size_t)N * K * 2);
     };
