@@ -740,9 +740,12 @@ inline Choice choose_w8(const GemmArgs &a, size_t scratch, bool dump_partials, b
                                  2.2 + 1.5 * ((double)a.N * a.K) / 6.8e6);
     if (t64 <= 1024 && us64 < best.us * 0.95) best = {20, 1, us64};
     // workgroups of four wavefronts (gemm_prefill_w8.hip), not within a channel split: there a part's estimate decides by itself, and
-    // an optimistic one made 4096 x 1024 x 24000 a split that took 127 us instead of 103
+    // an optimistic one made 4096 x 1024 x 24000 a split that took 127 us instead of 103.  How far ahead of the other estimate they have to be
+    // (800 shapes where that differs): 3 % is enough but for split-K (656 x 9216 x 1792 26.5 us, in form 52 27.6; 954 x 11008 x 1600
+    // 31.8 and 33.0, both 5 % ahead on paper) and for 256 x 256 tiles (1424 x 9344 x 8263 100 us, in form 56 107; 5 %).
     double us4 = 0.0;
-    if (const int form = whole ? choose_w8_form(a, &us4) : 0; form && !dump_partials && us4 < best.us * 0.97) best = {form, 1, us4};
+    const double ahead = best.splits > 1 ? 0.94 : best.variant == 26 ? 0.9 : 0.97;
+    if (const int form = whole ? choose_w8_form(a, &us4) : 0; form && !dump_partials && us4 < best.us * ahead) best = {form, 1, us4};
     return best;
 }
 

@@ -99,6 +99,26 @@ def test_int4_short_k_stays_with_the_kernels_that_are_faster_there():
         assert plan(M, N, K, bits=4, scratch=scratch).family == ql.QL_FAMILY_DECODE, (M, K, N)
 
 
+def test_int8_forms_of_four_wavefronts_are_the_choice_where_they_are_ahead():
+    """Measured with the weights from HBM, us, best of the other kernels / this form."""
+    for (M, K, N), scratch, variant, tile in [((260, 4096, 12288), 0, 51, (64, 128)),         # 31.8 / 25.5
+                                              ((512, 4096, 4096), SCRATCH, 52, (64, 128)),    # 18.8 / 15.3
+                                              ((900, 4096, 6144), 0, 53, (96, 128)),          # 34.1 / 29.1
+                                              ((640, 11008, 4096), SCRATCH, 54, (96, 128)),   # 47.1 / 39.0
+                                              ((300, 8192, 8192), 0, 54, (96, 128)),          # 34.0 / 30.8
+                                              ((768, 8192, 8192), 0, 56, (96, 256))]:         # 65.5 / 51.8
+        p = plan(M, N, K, scratch=scratch)
+        assert (p.family, p.variant, (p.tile_tokens, p.tile_channels), p.splits, p.rest_channels) == (ql.QL_FAMILY_TILE, variant, tile, 1, 0), (M, K, N)
+    # and not where split-K or 256 x 256 tiles are as fast (27.4 / 27.9, 32.1 / 33.2, 97.7 / 107, 45.9 / 48.7)
+    for (M, K, N), scratch, variant in [((656, 9216, 1792), 16194560, 202), ((954, 11008, 1600), 54525952, 202), ((1424, 9344, 8263), 0, 26),
+                                        ((1029, 3840, 11434), 0, 26)]:
+        assert plan(M, N, K, scratch=scratch).variant == variant, (M, K, N)
+    # up to 64 tokens, and where K is not in whole 128s: none of them
+    for M, N in [(64, 4096), (260, 12288), (900, 6144)]:
+        for K in (4160, 4096 if M == 64 else 4032):
+            assert not 51 <= plan(M, N, K).variant <= 56
+
+
 def test_estimates_are_finite_positive_and_grow_with_k():
     for M in (1, 64, 300, 2048):
         last = 0.0
