@@ -258,7 +258,7 @@ def test_split_k_linear_within_tolerance_and_deterministic(G, bits, M, K, N, var
     assert (y1.view(np.uint16) == y2.view(np.uint16)).all()
     # and the unsplit kernels agree to rounding (int8: same integer sums -- tested above -- so at most the last
     # fp32 bit of the dequantized value differs, which moves an fp16 result across a rounding boundary rarely)
-    ql.ql_set_kernel_variant(13 if bits == 8 else 6)   # unsplit (int4: 256x256 tiles)
+    ql.ql_set_kernel_variant(13 if bits == 8 else 6)   # unsplit (int4: 128x256 tiles)
     y0 = G.gpu_linear(x, g, b)
     if bits == 8:
         diff = y1.view(np.uint16) != y0.view(np.uint16)

@@ -36,7 +36,8 @@ def test_activations_every_block(G, M, K, block):
         assert (G.repack_act(q_o).cpu().numpy()[rows < M] == xk.cpu().numpy()[rows < M]).all()
 
 
-@pytest.mark.parametrize("K,block", [b for b in BLOCKS if b[0] % 128 == 0] + [(1024, 0), (11008, 256)])
+# (from K = 15424 on with blocks up to 1024 sixteen wavefronts stage 64 KB, beside the static LDS)
+@pytest.mark.parametrize("K,block", [b for b in BLOCKS if b[0] % 128 == 0] + [(1024, 0), (11008, 256), (15488, 128), (16384, 64), (16384, 1024), (16384, 0)])
 @pytest.mark.parametrize("bits", [8, 4])
 def test_weights_every_block(G, bits, K, block):
     N = 37                                                # rows 37 .. 63 are padding of the kernel layout
