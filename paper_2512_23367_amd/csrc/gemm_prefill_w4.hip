@@ -7,12 +7,14 @@
 // instructions cover the group for a 16 x 16 block; their int32 sums are folded into the fp32 accumulators
 // (accf += float(sum) * scale) and dropped, so a wavefront holds up to 128 tokens x 64 channels.
 //
-// What bounds it: issue slots and power.  Measured on gfx950: a 16x16x64 instruction takes 16 cycles and leaves room for two vector
+// What bounds it: issue slots.  Measured on gfx950: a 16x16x64 instruction takes 16 cycles and leaves room for two vector
 // operations of ANOTHER wavefront; a wavefront alone issues one vector operation per 4.7 cycles and none of its own while its
 // matrix instruction runs.  The fold needs two operations per accumulator and group (four per instruction), so two or more
 // wavefronts per SIMD, out of step, are what fills both pipes: workgroups of four wavefronts, two to four of them per
-// CU, each with barriers of its own -- one workgroup of eight in step ran the same products at 2.02 us per 256 x 256 x 128 (now
-// 1.83; register-only loops with the fold stop at 1.50, at 2.0 GHz: power).  Within a wavefront a block's fold is spread between
+// CU, each with barriers of its own -- one workgroup of eight in step ran the same products at 2.02 us per 256 x 256 x 128, now
+// 1.83.  That is 4000 cycles and more (2.16 GHz in a continuous run, 2.3 to 2.4 in single launches, matrix pipes busy 41 to 45 % of the
+// cycles, half of that beside vector work); register-only loops with the fold take 3000 (1.50 us, held to 2.0 GHz by power): a third of the
+// cycles is neither these two pipes nor power, and has not been taken apart.  Within a wavefront a block's fold is spread between
 // the next block's matrix instructions: where a CU has one workgroup only, 64 multiplies + 128 folds take 1.05 instead of 1.40 us.
 // Tokens go through LDS (global -> LDS loads, three stages); weights and scales, which no other wavefront of a workgroup wants,
 // straight to registers, one or two stages ahead (two: 5 % at one workgroup per CU).

@@ -6,11 +6,14 @@
 // workgroup wants, straight to registers, one or two stages ahead of the multiply.  The matrix instruction is 16x16x64 with the tokens as its
 // first operand, so a lane ends up with four tokens of one channel.
 //
-// What bounds it: what a CU can pull, 65..70 GB/s when the weights come from HBM, whatever the number of groups or of stages
-// ahead -- so the tile is chosen by the bytes per product and by how evenly the tiles fill the CUs.  Measured against the best of the
-// forms in gemm_prefill.hip (us, weights from HBM): 512 x 4096 x 4096 18.8 -> 15.7, 640 x 11008 x 4096 48 -> 39, 1300 x 11008 x
-// 4096 88 -> 62, 1900 x 6144 x 1536 25.0 -> 22.2, 768 x 8192 x 8192 64 -> 50; 180 shapes of 48..4096 tokens 4 % on average.  Not faster
-// with the weights' or tokens' loads non-temporal, or with every channel tile starting at another k.
+// What bounds it: what a CU can pull when the weights come from HBM, whatever the number of groups or of stages ahead: 45..57 GB/s over
+// whole launches, 49..64 in the fastest, so about 70 in the loop (96 channels and fewer; 128 x 256 and 96 x 256 less).  So the tile is chosen by
+// the bytes per product and by how evenly the tiles fill the CUs.  Calls that take them, us before and now (tokens x K x N, weights from
+// HBM): 260 x 4096 x 12288 31.8 / 25.5, 512 x 4096 x 4096 18.8 / 15.3, 640 x 11008 x 4096 48.2 / 39.0, 900 x 4096 x 6144 34.3 / 29.1, 768 x
+// 8192 x 8192 65.5 / 51.8; 492 shapes of 65 tokens and more where a form is the choice 1.23 times on average, 2 % slower at worst.
+// Above 1024 tokens nearly none: the other kernels are estimated there by rates of warm weights, too low by up to a quarter, and forms that
+// would be ahead are passed over (1300 x 11008 x 4096: taken 84, form 56 65; 1900 x 6144 x 1536: taken 23.3, form 53 21.4).
+// Not faster with the weights' or tokens' loads non-temporal, or with every channel tile starting at another k.
 #include "gemm_tiles.h"
 #include <algorithm>
 #include <type_traits>
@@ -267,7 +270,8 @@ int launch(const GemmArgs &a, hipStream_t st)
 
 // The forms and their estimated time: 3 us + the weights at 20 TB/s + the output at 7 TB/s + what the busiest CU does, in
 // rounds of as many workgroups as fit it together (a round of n takes o[n - 1] + stages x c[n - 1], groups: their steps), but not
-// less than the weights take to arrive (5.5 us + 3.6 TB/s).  Fitted to 180 shapes (48..4096 tokens, N 1536..22016, K 1536..11008,
+// less than the weights take to arrive (5.5 us + 3.6 TB/s).  128 x 256 is rarely the choice (5 of 60000 shapes), though measured the fastest at 470 x 6016
+// x 13745 (45.2 us, taken 51.4) and 1342 x 6272 x 4800 (48.4, taken 51.5).  Fitted to 180 shapes (48..4096 tokens, N 1536..22016, K 1536..11008,
 // weights from HBM), within 3 to 10 % on average each on the card they were fitted on; other cards are slower by up to a tenth, hence the factor.
 struct W8Form {
     int variant, tm, tn, per_cu, groups;
